@@ -30,10 +30,11 @@ def build(verbose: bool = False) -> str:
     """Compile every source and link libmsp.so (always recompiles)."""
     os.makedirs(BUILD, exist_ok=True)
     objs = []
-    host = os.path.join(BUILD, "msp_host.o")
-    _run(["g++", *HOSTFLAGS, "-c", os.path.join(CSRC, "msp_host.cpp"), "-o", host], verbose)
-    objs.append(host)
-    for src in ("msp_kernels.hip", "msp_chain.hip", "msp_api.cpp"):
+    for src in ("msp_host.cpp", "msp_nd.cpp"):
+        obj = os.path.join(BUILD, os.path.splitext(src)[0] + "_host.o")
+        _run(["g++", *HOSTFLAGS, "-c", os.path.join(CSRC, src), "-o", obj], verbose)
+        objs.append(obj)
+    for src in ("msp_kernels.hip", "msp_chain.hip", "msp_nd.hip", "msp_api.cpp"):
         obj = os.path.join(BUILD, os.path.splitext(src)[0] + ".o")
         _run(["hipcc", *HIPFLAGS, "-x", "hip", "-c", os.path.join(CSRC, src), "-o", obj], verbose)
         objs.append(obj)

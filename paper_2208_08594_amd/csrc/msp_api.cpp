@@ -20,6 +20,7 @@
 #include "msp_chain.h"
 #include "msp_host.h"
 #include "msp_kernels.h"
+#include "msp_nd_device.h"
 #include "msp_stages.h"
 
 namespace {
@@ -168,6 +169,14 @@ struct msp_ctx {
     // triangular, both nL x nL with leading dimension ldL) and its FP64 work
     // vector
     double *cinv = nullptr, *cY = nullptr, *ct = nullptr;
+    // the same solver in nested-dissection order (msp_nd.h): in use while
+    // nd.n > 0, with the plan's order as the coarsest level's positions.
+    // nd_gen: pattern_gen of a plan made for level 0, -1 for other plans.
+    NdSolve nd;
+    NdPlan nd_plan;
+    long long nd_gen = -1;
+    void *nd_stage = nullptr;  // page-locked source of the plan's device copy
+    size_t nd_stage_bytes = 0;
     BiluData bilu;
     NStage ns;
     void *e_nat = nullptr, *ybuf = nullptr;
@@ -337,6 +346,7 @@ void release_B(msp_ctx *c)
     c->hasB = false;
     c->omega = nullptr;
     c->cinv = c->cY = c->ct = nullptr;
+    c->nd = NdSolve();
     c->e_nat = c->ybuf = nullptr;
     c->tC = c->tA = c->tB = nullptr;
 }
@@ -422,6 +432,13 @@ void build_level_device(msp_ctx *c, int l, bool last, LevelLayout *lay, const Le
     L.f = c->dalloc(tsz * std::max(L.n, 1), c->allocB);
     L.x = c->dalloc(tsz * std::max(L.n, 1), c->allocB);
     if (last) {
+        if (c->nd.n > 0) {
+            L.perm = c->nd_plan.perm;
+            L.iperm = c->nd_plan.iperm;
+            L.perm_d = c->upload(L.perm, c->allocB);
+            L.iperm_d = c->upload(L.iperm, c->allocB);
+            return;
+        }
         L.perm.resize(L.n);
         std::iota(L.perm.begin(), L.perm.end(), 0);
         L.iperm = L.perm;
@@ -550,13 +567,132 @@ void make_gj_streams(msp_ctx *c)
     }
 }
 
-// Starts the coarsest-level solver and returns without waiting: the dense
-// matrix is scattered on `stream`, and a host thread queues the solver's
-// kernels on the solver streams (several thousand launches, off the setup's
-// own thread).  The returned future completes once everything is queued;
-// then `stream` must wait for gj.ev_done.  flag[0] is set on a singular
-// pivot block.  The upload and work buffers go to `tmp`, which the caller
-// releases after the streams have drained.
+// fill bound of each block step of the natural-order block LU: a row first
+// takes part in the step of the block holding its first stored column, a
+// column in that of its first stored row
+void coarse_band(const Csr &A, std::vector<int> &rows_end, std::vector<int> &cols_end)
+{
+    const int m = A.n, steps = (m + kLuBlock - 1) / kLuBlock;
+    rows_end.assign(steps, 0);
+    cols_end.assign(steps, 0);
+    std::vector<int> first_row(m, m);
+    for (int i = 0; i < m; ++i) {
+        const int s0 = A.ci[A.rp[i]] / kLuBlock;  // columns ascending
+        rows_end[s0] = std::max(rows_end[s0], i + 1);
+        for (int k = A.rp[i]; k < A.rp[i + 1]; ++k)
+            first_row[A.ci[k]] = std::min(first_row[A.ci[k]], i);
+    }
+    for (int j = 0; j < m; ++j) {
+        const int s0 = first_row[j] / kLuBlock;
+        cols_end[s0] = std::max(cols_end[s0], j + 1);
+    }
+    for (int s = 1; s < steps; ++s) {
+        rows_end[s] = std::max(rows_end[s], rows_end[s - 1]);
+        cols_end[s] = std::max(cols_end[s], cols_end[s - 1]);
+    }
+}
+
+// The nested-dissection solver of the coarsest level, queued on `stream`;
+// false (with nothing queued) if it does not serve this matrix: some row is
+// not strictly diagonally dominant (the natural-order solver pivots inside
+// its blocks), or its graph does not separate.  val_d: the matrix values on
+// the device if they are there already (level 0), else nullptr.
+bool launch_coarse_nd(msp_ctx *c, const Csr &A, bool level0, const double *val_d,
+                      std::vector<void *> &tmp)
+{
+    const int m = A.n;
+    if (!nd_dominant(m, A.rp.data(), A.ci.data(), A.val.data())) return false;
+    NdPlan &P = c->nd_plan;
+    // level 0's pattern stays for the whole Newton sequence, and so does its plan
+    if (!level0 || c->nd_gen != c->pattern_gen || P.n != m) {
+        c->nd_gen = -1;
+        if (!nd_plan(m, A.rp.data(), A.ci.data(), P)) {
+            P.clear();
+            return false;
+        }
+        if (level0) c->nd_gen = c->pattern_gen;
+    }
+    // one page-locked block [solve lists | factorisation lists | values], two
+    // device blocks: the first stays with the preconditioner
+    struct Part {
+        const void *src;
+        size_t bytes, off;
+    };
+    std::vector<Part> part;
+    size_t total = 0;
+    auto add = [&](const auto &v) {
+        part.push_back({v.data(), sizeof(v[0]) * v.size(), total});
+        total += (part.back().bytes + 255) & ~(size_t)255;
+        return part.back().off;
+    };
+    const size_t o_yrow = add(P.yrow), o_wrow = add(P.wrow), o_cmap = add(P.cmap);
+    const size_t keep = total;
+    const size_t o_node = add(P.node), o_nodeof = add(P.nodeof), o_ep = add(P.ent_ptr),
+                 o_ent = add(P.ent), o_sp = add(P.self_ptr), o_self = add(P.self),
+                 o_rows = add(P.rows), o_first = add(P.first), o_prod = add(P.prod),
+                 o_inv = add(P.inv);
+    size_t o_val = 0;
+    if (!val_d) o_val = add(A.val);
+    if (c->nd_stage_bytes < total) {
+        if (c->nd_stage) (void)hipHostFree(c->nd_stage);
+        c->nd_stage = nullptr;
+        c->nd_stage_bytes = 0;
+        HIPCHK(hipHostMalloc(&c->nd_stage, total + total / 8, hipHostMallocDefault));
+        c->nd_stage_bytes = total + total / 8;
+    }
+    for (const Part &q : part)
+        if (q.bytes) std::memcpy((char *)c->nd_stage + q.off, q.src, q.bytes);
+    char *kept = (char *)c->dalloc(keep, c->allocB);
+    char *work = (char *)c->dalloc(total - keep, tmp) - keep;
+    HIPCHK(hipMemcpyAsync(kept, c->nd_stage, keep, hipMemcpyHostToDevice, c->stream));
+    HIPCHK(hipMemcpyAsync(work + keep, (char *)c->nd_stage + keep, total - keep,
+                          hipMemcpyHostToDevice, c->stream));
+    auto dbl = [&](size_t k, std::vector<void *> &list) {
+        return (double *)c->dalloc(sizeof(double) * std::max<size_t>(k, 2), list);
+    };
+    NdDev d;
+    d.node = (const NdNode *)(work + o_node);
+    d.nodeof = (const int *)(work + o_nodeof);
+    d.cmap = (const int *)(kept + o_cmap);
+    d.ent_ptr = (const int *)(work + o_ep);
+    d.ent = (const int4 *)(work + o_ent);
+    d.self_ptr = (const int *)(work + o_sp);
+    d.self = (const int2 *)(work + o_self);
+    d.rows = (const int *)(work + o_rows);
+    d.first = (const int *)(work + o_first);
+    d.prod = (const int4 *)(work + o_prod);
+    d.inv = (const int4 *)(work + o_inv);
+    d.val = val_d ? val_d : (const double *)(work + o_val);
+    d.W = dbl(P.wtot, c->allocB);
+    d.Y = dbl(P.qtot, c->allocB);
+    d.Yt = dbl(P.wtot, tmp);
+    d.L = dbl(P.qtot, tmp);
+    d.Ut = dbl(P.qtot, tmp);
+    d.X = dbl(P.xtot, tmp);
+    d.S0 = dbl(P.stot, tmp);
+    d.S1 = dbl(P.stot, tmp);
+    d.Dk = dbl(P.node.size() * 2 * kNdTile * kNdTile, tmp);
+    c->nL = m;
+    c->ldL = (m + 15) & ~15;
+    c->ct = (double *)c->dalloc(sizeof(double) * (size_t)m, c->allocB);
+    c->nd.n = m;
+    c->nd.nlong = P.nlong;
+    c->nd.yrow = (const int4 *)(kept + o_yrow);
+    c->nd.wrow = (const int4 *)(kept + o_wrow);
+    c->nd.cmap = d.cmap;
+    c->nd.W = d.W;
+    c->nd.Y = d.Y;
+    HIPCHK(launch_nd_factor(P, d, c->stream));
+    return true;
+}
+
+// Starts the natural-order coarsest-level solver and returns without waiting:
+// the dense matrix is scattered on `stream`, and a host thread queues the
+// solver's kernels on the solver streams (several thousand launches, off the
+// setup's own thread).  The returned future completes once everything is
+// queued; then `stream` must wait for gj.ev_done.  flag[0] is set on a
+// singular pivot block.  The upload and work buffers go to `tmp`, which the
+// caller releases after the streams have drained.
 std::future<void> launch_coarse(msp_ctx *c, const Csr &A, std::vector<void *> &tmp)
 {
     const int m = A.n;
@@ -572,31 +708,10 @@ std::future<void> launch_coarse(msp_ctx *c, const Csr &A, std::vector<void *> &t
     HIPCHK(launch_fill((long long)m * c->ldL, 0.0, c->cinv, c->stream));
     HIPCHK(launch_dense_scatter(m, c->ldL, rp, ci, val, c->cinv, c->stream));
     if (!c->gj.aux) make_gj_streams(c);
-    // fill bound of each block step: a row first takes part in the step of
-    // the block holding its first stored column, a column in that of its
-    // first stored row
-    const int steps = (m + kLuBlock - 1) / kLuBlock;
-    std::vector<int> rows_end(steps, 0), cols_end(steps, 0);
-    {
-        std::vector<int> first_row(m, m);
-        for (int i = 0; i < m; ++i) {
-            const int s0 = A.ci[A.rp[i]] / kLuBlock;  // columns ascending
-            rows_end[s0] = std::max(rows_end[s0], i + 1);
-            for (int k = A.rp[i]; k < A.rp[i + 1]; ++k)
-                first_row[A.ci[k]] = std::min(first_row[A.ci[k]], i);
-        }
-        for (int j = 0; j < m; ++j) {
-            const int s0 = first_row[j] / kLuBlock;
-            cols_end[s0] = std::max(cols_end[s0], j + 1);
-        }
-        for (int s = 1; s < steps; ++s) {
-            rows_end[s] = std::max(rows_end[s], rows_end[s - 1]);
-            cols_end[s] = std::max(cols_end[s], cols_end[s - 1]);
-        }
-    }
+    std::vector<int> rows_end, cols_end;
+    coarse_band(A, rows_end, cols_end);
     double *lband =
         (double *)c->dalloc(sizeof(double) * (dense_inverse_lband(m, rows_end.data()) + 1), tmp);
-    c->sweepK = dense_inverse_sweep_k(m, cols_end.data());
     c->clear_flag(0);
     HIPCHK(hipEventRecord(c->gj.ev_start, c->stream));
     return std::async(std::launch::async, [c, m, lband, work, re = std::move(rows_end),
@@ -604,6 +719,17 @@ std::future<void> launch_coarse(msp_ctx *c, const Csr &A, std::vector<void *> &t
         HIPCHK(dense_inverse(m, c->ldL, c->cinv, c->cY, lband, work, c->flag, c->stream, &c->gj,
                              re.data(), ce.data()));
     });
+}
+
+// x = A_L^-1 f on the coarsest level, in its positions.
+template <typename T>
+void coarse_solve(msp_ctx *c, const T *f, T *x)
+{
+    if (c->nd.n > 0)
+        HIPCHK(launch_nd_solve<T>(c->nd, f, c->ct, x, c->stream));
+    else
+        HIPCHK(launch_coarse_solve<T>(c->nL, c->ldL, kLuBlock, c->cY, c->cinv, f, c->ct, x,
+                                      c->stream));
 }
 
 // A posteriori check of the coarsest-level direct solve.  Its block LU makes
@@ -618,18 +744,21 @@ std::future<void> launch_coarse(msp_ctx *c, const Csr &A, std::vector<void *> &t
 constexpr double kCoarseBackwardTol = 1e-8;
 bool coarse_solve_accurate(msp_ctx *c, std::vector<void *> &tmp)
 {
-    const Csr &A = c->lev.back().A;
+    const Level &L = c->lev.back();
+    const Csr &A = L.A;
     const int m = A.n;
-    std::vector<double> f(m), x(m);
-    for (int i = 0; i < m; ++i)  // a fixed, sign-changing right-hand side
+    std::vector<double> f(m), fp(m), xp(m), x(m);
+    for (int i = 0; i < m; ++i) {  // a fixed, sign-changing right-hand side
         f[i] = (double)((unsigned)(i + 1) * 2654435761u % 2001u) / 1000.0 - 1.0;
-    double *fd = c->upload(f, tmp);
+        fp[L.perm[i]] = f[i];
+    }
+    double *fd = c->upload(fp, tmp);
     double *xd = (double *)c->dalloc(sizeof(double) * (size_t)std::max(m, 1), tmp);
-    HIPCHK(launch_coarse_solve<double>(m, c->ldL, kLuBlock, c->cY, c->cinv, fd, c->ct, xd,
-                                       c->stream));
-    HIPCHK(hipMemcpyAsync(x.data(), xd, sizeof(double) * (size_t)m, hipMemcpyDeviceToHost,
+    coarse_solve<double>(c, fd, xd);
+    HIPCHK(hipMemcpyAsync(xp.data(), xd, sizeof(double) * (size_t)m, hipMemcpyDeviceToHost,
                           c->stream));
     c->sync();
+    for (int i = 0; i < m; ++i) x[i] = xp[L.perm[i]];
     for (int i = 0; i < m; ++i) {
         double r = -f[i], sc = std::fabs(f[i]);
         for (int k = A.rp[i]; k < A.rp[i + 1]; ++k) {
@@ -877,7 +1006,8 @@ void *chain_staging(msp_ctx *c, int l, size_t bytes)
     return b.first;
 }
 
-void rebuild_B(msp_ctx *c, const double *vals)
+// nd_ok: the coarsest level may take the nested-dissection solver.
+void rebuild_B(msp_ctx *c, const double *vals, bool nd_ok = true)
 {
     // Level 0 of the previous hierarchy has the same pattern arrays when the
     // pattern has not changed since: its host arrays are taken over (the
@@ -1011,7 +1141,9 @@ void rebuild_B(msp_ctx *c, const double *vals)
     if (st == -3) fail(MSP_ERR_SINGULAR);
     if (st == -9) fail(MSP_ERR_COARSE);
     const int nlev = (int)H.A.size();
-    std::future<void> coarse_queued = launch_coarse(c, H.A.back(), tmp);
+    std::future<void> coarse_queued;
+    if (!(nd_ok && launch_coarse_nd(c, H.A.back(), nlev == 1, nlev == 1 ? ap : nullptr, tmp)))
+        coarse_queued = launch_coarse(c, H.A.back(), tmp);
     // zero diagonals on the smoothed levels (the device chain leaves this
     // test to here, behind the coarsest inverse already queued)
     a0_ready.get();
@@ -1101,15 +1233,23 @@ void rebuild_B(msp_ctx *c, const double *vals)
             --left;
         }
     }
-    coarse_queued.get();
-    HIPCHK(hipStreamWaitEvent(c->stream, c->gj.ev_done, 0));
+    const bool natural = coarse_queued.valid();
+    if (natural) {
+        coarse_queued.get();
+        HIPCHK(hipStreamWaitEvent(c->stream, c->gj.ev_done, 0));
+    }
     HIPCHK(hipEventRecord(c->ev_side, c->side));
     HIPCHK(hipStreamWaitEvent(c->stream, c->ev_side, 0));
     const int bad_bilu = c->read_flag(1) | (c->ns.on ? c->read_flag(2) : 0);
     phase(6);
-    const int bad_coarse = c->read_flag(0) || !coarse_solve_accurate(c, tmp);
+    const int bad_coarse = (natural && c->read_flag(0)) || !coarse_solve_accurate(c, tmp);
     c->release(tmp);
-    if (bad_coarse || bad_bilu) fail(MSP_ERR_SINGULAR);
+    if (bad_bilu) fail(MSP_ERR_SINGULAR);
+    if (bad_coarse) {
+        // (dominance bounds the growth, so this is not expected)
+        if (!natural) return rebuild_B(c, vals, false);
+        fail(MSP_ERR_SINGULAR);
+    }
     phase(5);
     const size_t tsz = c->fp32() ? sizeof(float) : sizeof(double);
     c->e_nat = c->dalloc(tsz * n, c->allocB);
@@ -1194,8 +1334,7 @@ void vcycle(msp_ctx *c, int l, bool first_done = false)
 {
     Level &L = c->lev[l];
     if (l == (int)c->lev.size() - 1) {
-        HIPCHK(launch_coarse_solve<T>(L.n, c->ldL, kLuBlock, c->cY, c->cinv, (const T *)L.f,
-                                      c->ct, (T *)L.x, c->stream));
+        coarse_solve<T>(c, (const T *)L.f, (T *)L.x);
         return;
     }
     Level &C = c->lev[l + 1];
@@ -1898,6 +2037,7 @@ int msp_destroy(msp_ctx *c)
         if (c->hhost) (void)hipHostFree(c->hhost);
         if (c->flag_host) (void)hipHostFree(c->flag_host);
         if (c->chain_host) (void)hipHostFree(c->chain_host);
+        if (c->nd_stage) (void)hipHostFree(c->nd_stage);
         for (auto &b : c->chain_stage)
             if (b.first) (void)hipHostFree(b.first);
         return MSP_OK;
@@ -2335,7 +2475,13 @@ int msp_stage_repeat(msp_ctx *c, int stage, int reps, const double *in, double *
             // with B (P the block size); C is overwritten, so every
             // repetition does the same work
             constexpr int P = kLuBlock;
-            const int m = c->nL, kd = std::max(c->sweepK, 1);
+            const int m = c->nL;
+            if (!c->tC) {
+                std::vector<int> re, ce;
+                coarse_band(c->lev.back().A, re, ce);
+                c->sweepK = dense_inverse_sweep_k(m, ce.data());
+            }
+            const int kd = std::max(c->sweepK, 1);
             const int mr = std::max((m - 1) / P * P, 1);
             if (!c->tC) {
                 c->tC = (double *)c->dalloc(sizeof(double) * (size_t)mr * P, c->allocB);
@@ -2370,13 +2516,9 @@ int msp_stage_repeat(msp_ctx *c, int stage, int reps, const double *in, double *
             case MSP_STAGE_COARSE: {
                 Level &L = c->lev.back();
                 if (f32)
-                    HIPCHK(launch_coarse_solve<float>(L.n, c->ldL, kLuBlock, c->cY, c->cinv,
-                                                      (const float *)L.f, c->ct, (float *)L.x,
-                                                      c->stream));
+                    coarse_solve<float>(c, (const float *)L.f, (float *)L.x);
                 else
-                    HIPCHK(launch_coarse_solve<double>(L.n, c->ldL, kLuBlock, c->cY, c->cinv,
-                                                       (const double *)L.f, c->ct,
-                                                       (double *)L.x, c->stream));
+                    coarse_solve<double>(c, (const double *)L.f, (double *)L.x);
                 break;
             }
             }

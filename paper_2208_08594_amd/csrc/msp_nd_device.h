@@ -1,0 +1,39 @@
+// Device side of the nested-dissection coarsest-level solver: launchers (see
+// msp_nd.h for the method and the plan).
+#pragma once
+
+#include <hip/hip_runtime.h>
+
+#include "msp_nd.h"
+
+namespace msp {
+
+// Device pointers of a factorisation: copies of the plan's lists, the matrix
+// values (natural CSR order) and the work and result arrays.
+struct NdDev {
+    const NdNode *node;
+    const int *nodeof, *cmap, *ent_ptr, *self_ptr, *rows, *first;
+    const int4 *ent, *prod, *inv;
+    const int2 *self;
+    const double *val;
+    double *W, *Yt;      // packed rows (wtot each)
+    double *Y, *L, *Ut;  // qtot each
+    double *X;           // xtot
+    double *S0, *S1;     // stot each
+    double *Dk;          // 2 tiles per node
+};
+// Computes W and Y (d.W and d.Y), queued on st.
+hipError_t launch_nd_factor(const NdPlan &P, const NdDev &d, hipStream_t st);
+
+// What the solve reads (kept with the preconditioner).
+struct NdSolve {
+    int n = 0, nlong = 0;
+    const int4 *yrow = nullptr, *wrow = nullptr;
+    const int *cmap = nullptr;
+    const double *W = nullptr, *Y = nullptr;
+};
+// x = A^-1 f = W (Y f), vectors in permuted order; t: FP64 work vector of n.
+template <typename T>
+hipError_t launch_nd_solve(const NdSolve &s, const T *f, double *t, T *x, hipStream_t st);
+
+}  // namespace msp
