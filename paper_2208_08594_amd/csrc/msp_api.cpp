@@ -1123,12 +1123,10 @@ void rebuild_B(msp_ctx *c, const double *vals, bool nd_ok = true)
     // the chain on the device (structurally symmetric patterns), else on the host
     int st = 1;
     if (c->opt.host_chain == 0) {
-        if (!c->cap_stream)
-            HIPCHK(hipStreamCreateWithFlags(&c->cap_stream, hipStreamNonBlocking));
         device_levels = true;  // no level callback runs if the chain declines (st == 1)
         st = device_hierarchy(
             A0, c->rp_d, c->ci_d, ap, c->opt.max_coarse, MSP_MAX_LEVELS, 16384, H, start_level,
-            [&a0_ready]() { a0_ready.get(); }, c->stream, c->cap_stream, c->chain_copy,
+            [&a0_ready]() { a0_ready.get(); }, c->stream, c->chain_copy,
             [c, &tmp](size_t bytes) { return c->dalloc(bytes, tmp); }, fail_hip, c->chain_host,
             [c](int l, size_t bytes) { return chain_staging(c, l, bytes); });
     }

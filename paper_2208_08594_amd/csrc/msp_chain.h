@@ -7,11 +7,13 @@
 // equals).  Row i only ever pairs with a candidate j > i (every lower row is
 // already placed when i is visited), so the pass is the greedy maximal
 // matching of the directed edge list {(i, j) : j a candidate of i, j > i}
-// taken in the order (i ascending, candidate rank ascending).  That matching
-// is the lexicographically first maximal matching for this edge order, and
-// it is also what repeated rounds of "take every free edge that comes first
-// at both of its endpoints" produce; the device pass runs those rounds.  The
-// smallest free row always decides in a round, so there are at most n rounds.
+// taken in the order (i ascending, candidate rank ascending).  What the pass
+// does at row v is a function of the decisions of lower rows alone: whether
+// one of them took v, and which of v's candidates they took.  On the device
+// every row waits for just the decisions that its own needs and then makes
+// it, all rows at once; each decision is made once, so the result is that of
+// the ascending pass whatever the schedule.  The smallest undecided row can
+// always decide.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -47,8 +49,7 @@ using HipFail = void (*)(hipError_t);
 // the coarsest level.  Returns 1 without touching
 // A0 or H when the level-0 pattern is not structurally symmetric (the pass
 // reads a_ji through the mirror entry); the caller then runs the host chain.
-// `cap` is an idle stream used only to capture batches of matching rounds
-// into a graph (nothing runs on it).  `pinned` is a host-pinned buffer of at
+// `pinned` is a host-pinned buffer of at
 // least 16 ints.  With `staging`, each new level is copied to page-locked
 // memory first (a fast DMA), on_smoothed gets its pattern there (so the
 // level's host work starts before the copy into H.A is done), and H.A is
@@ -62,7 +63,7 @@ size_t device_chain_bytes(int n0, long long nnz0);
 int device_hierarchy(Csr &A0, const int *rp0, const int *ci0, const double *val0,
                      int max_coarse, int max_levels, int max_dense, Hierarchy &H,
                      const LevelCallback &on_smoothed, const std::function<void()> &level0_values,
-                     hipStream_t st, hipStream_t cap, hipStream_t copy_st,
+                     hipStream_t st, hipStream_t copy_st,
                      const DeviceAlloc &alloc, HipFail hip_fail, int *pinned,
                      const PinnedBuffer &staging = nullptr);
 

@@ -20,9 +20,9 @@ namespace {
 
 constexpr int kThreads = 256;
 constexpr int kScanTile = 1024;  // elements per block of the scan (4 per thread)
-constexpr int kFree = 0, kSingle = 1, kLow = 2, kHigh = 3;
-constexpr int kNone = 0x7fffffff;
-constexpr int kBatch = 8;  // rounds queued between two reads of the free count (even)
+// state word of a row in the matching: undecided, alone, taken by a lower
+// row, or ~j: it has taken row j
+constexpr int kFree = 0, kSingle = 1, kHigh = 2;
 
 inline unsigned nblocks(long long n, int per = kThreads)
 {
@@ -76,226 +76,191 @@ __global__ void k_strength(int n, const int *__restrict__ rp, const int *__restr
     elig[i] = (coupled && any && mx > 0.0) ? 1 : 0;
 }
 
-// Candidates of an eligible row i: eligible j > i with s_ij >= 0.25 max_k
-// s_ik, ordered by s_ij descending then j ascending, written over the row's
-// own slots [rp[i], rp[i] + ncand[i]).  (Candidates j < i never matter: they
-// are placed before i is visited.)
-__global__ void k_candidates(int n, const int *__restrict__ rp, const int *__restrict__ ci,
-                             const double *__restrict__ s, const double *__restrict__ smax,
-                             const unsigned char *__restrict__ elig, int *__restrict__ cj,
-                             double *__restrict__ cs, int *__restrict__ ncand)
+// The two lists of every row i that the matching reads, over the row's own
+// slots: its candidates (eligible j > i with s_ij >= 0.25 max_k s_ik, ordered
+// by s_ij descending then j ascending) at lst[rp[i] ..), then its in-rows
+// (the lower rows j whose candidate it is: s is symmetric, so j < i in row i
+// with s_ij >= 0.25 max_k s_jk; any order) behind them.  (Candidates j < i
+// never matter: they are placed before i is visited.)  The first kRec entries
+// of both lists are also held inline in two records, so that the matching
+// loads a whole list at once; kOver in a record's first slot: the list is
+// longer.  Unused slots are -1.  The row's state word is cleared.
+constexpr int kRec = 4;
+constexpr int kOver = -2;
+__global__ void k_lists(int n, const int *__restrict__ rp, const int *__restrict__ ci,
+                        const double *__restrict__ s, const double *__restrict__ smax,
+                        const unsigned char *__restrict__ elig, int *__restrict__ lst,
+                        double *__restrict__ cs, int *__restrict__ ncand, int *__restrict__ nin,
+                        int4 *__restrict__ rin, int4 *__restrict__ rcand, int *__restrict__ word)
 {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
-    int m = 0;
+    int m = 0, mi = 0;
+    const int b0 = rp[i], b1 = rp[i + 1];
     if (elig[i]) {
         const double thr = 0.25 * smax[i];
-        const int b0 = rp[i];
-        for (int k = rp[i]; k < rp[i + 1]; ++k) {
+        // candidates from the front, in-rows from the back of the row's slots
+        for (int k = b0; k < b1; ++k) {
             const int j = ci[k];
-            if (j <= i || !elig[j]) continue;
+            if (j == i || !elig[j]) continue;
             const double sj = s[k];
+            if (j < i) {
+                if (sj >= 0.25 * smax[j]) lst[b1 - ++mi] = j;
+                continue;
+            }
             if (!(sj >= thr)) continue;
             int r = m;
-            while (r > 0 && (cs[b0 + r - 1] < sj || (cs[b0 + r - 1] == sj && cj[b0 + r - 1] > j))) {
-                cj[b0 + r] = cj[b0 + r - 1];
+            while (r > 0 && (cs[b0 + r - 1] < sj || (cs[b0 + r - 1] == sj && lst[b0 + r - 1] > j))) {
+                lst[b0 + r] = lst[b0 + r - 1];
                 cs[b0 + r] = cs[b0 + r - 1];
                 --r;
             }
-            cj[b0 + r] = j;
+            lst[b0 + r] = j;
             cs[b0 + r] = sj;
             ++m;
         }
     }
-    ncand[i] = m;
-}
-
-// Lists of the lower rows pointing at each row: in_ptr/in_row, the
-// transpose of the candidate lists (order inside a list is free).
-__global__ void k_in_count(int n, const int *__restrict__ rp, const int *__restrict__ cj,
-                           const int *__restrict__ ncand, int *__restrict__ indeg)
-{
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    for (int q = 0; q < ncand[i]; ++q) atomicAdd(&indeg[cj[rp[i] + q]], 1);
-}
-
-__global__ void k_in_fill(int n, const int *__restrict__ rp, const int *__restrict__ cj,
-                          const int *__restrict__ ncand, const int *__restrict__ in_ptr,
-                          int *__restrict__ cursor, int *__restrict__ in_row)
-{
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    for (int q = 0; q < ncand[i]; ++q) {
-        const int j = cj[rp[i] + q];
-        in_row[in_ptr[j] + atomicAdd(&cursor[j], 1)] = i;
-    }
-}
-
-// lowest free row with a candidate edge into v (kNone if there is none)
-__device__ inline int lowest_free_in(int v, const int *__restrict__ in_ptr,
-                                     const int *__restrict__ in_row, const int *__restrict__ st)
-{
-    int m = kNone;
-    for (int q = in_ptr[v]; q < in_ptr[v + 1]; ++q) {
-        const int k = in_row[q];
-        if (k < m && st[k] == kFree) m = k;
-    }
-    return m;
-}
-
-// first free candidate of v (its proposal), -1 if none is left
-__device__ inline int first_free_cand(int v, const int *__restrict__ rp, const int *__restrict__ cj,
-                                      const int *__restrict__ ncand, const int *__restrict__ st)
-{
-    const int b0 = rp[v], m = ncand[v];
-    for (int q = 0; q < m; ++q) {
-        const int j = cj[b0 + q];
-        if (st[j] == kFree) return j;
-    }
-    return -1;
-}
-
-// Each row's first kRec in-rows and first kRec candidates (in order) held
-// inline, so that a round loads the states of a whole list at once instead of
-// walking it one dependent load after another.  kOver in a record's first
-// slot: the list is longer, and the round walks it in full.  Unused slots are
-// kNone (in-rows) and -1 (candidates).
-constexpr int kRec = 4;
-constexpr int kOver = -2;
-__global__ void k_records(int n, const int *__restrict__ rp, const int *__restrict__ cj,
-                          const int *__restrict__ ncand, const int *__restrict__ in_ptr,
-                          const int *__restrict__ in_row, int4 *__restrict__ rin,
-                          int4 *__restrict__ rcand)
-{
-    const int v = blockIdx.x * blockDim.x + threadIdx.x;
-    if (v >= n) return;
-    int a[kRec] = {kNone, kNone, kNone, kNone};
-    const int q0 = in_ptr[v], q1 = in_ptr[v + 1];
-    if (q1 - q0 > kRec)
+    int a[kRec] = {-1, -1, -1, -1}, c[kRec] = {-1, -1, -1, -1};
+    if (mi > kRec)
         a[0] = kOver;
     else
-        for (int q = q0; q < q1; ++q) a[q - q0] = in_row[q];
-    rin[v] = make_int4(a[0], a[1], a[2], a[3]);
-    int c[kRec] = {-1, -1, -1, -1};
-    const int m = ncand[v], b0 = rp[v];
+#pragma unroll
+        for (int q = 0; q < kRec; ++q)
+            if (q < mi) a[q] = lst[b1 - 1 - q];
     if (m > kRec)
         c[0] = kOver;
     else
-        for (int q = 0; q < m; ++q) c[q] = cj[b0 + q];
-    rcand[v] = make_int4(c[0], c[1], c[2], c[3]);
+#pragma unroll
+        for (int q = 0; q < kRec; ++q)
+            if (q < m) c[q] = lst[b0 + q];
+    rin[i] = make_int4(a[0], a[1], a[2], a[3]);
+    rcand[i] = make_int4(c[0], c[1], c[2], c[3]);
+    ncand[i] = m;
+    nin[i] = mi;
+    word[i] = kFree;
 }
 
-// lowest_free_in / first_free_cand through the records
-__device__ inline int lowest_free_in_rec(int v, const int4 *__restrict__ rin,
-                                         const int *__restrict__ in_ptr,
-                                         const int *__restrict__ in_row,
-                                         const int *__restrict__ st)
+// The pairwise pass: every row decides for itself, in any order, what the
+// ascending pass decides when it visits the row.  Row v
+//  - is taken (kHigh) if some in-row has taken it;
+//  - otherwise, once all its in-rows are decided, takes the first candidate
+//    that no lower row has taken: a candidate j is known to be taken when one
+//    of j's in-rows below v has taken it, and known to be free when all of
+//    them are decided and none has; while neither is known, v waits;
+//  - stays alone when every candidate is taken.
+// A decision reads only state words of lower rows, each written once, so
+// stale reads only delay it and the result does not depend on the schedule.
+// The words of the work-group's own rows are held in LDS, those of lower
+// work-groups read with device-scope loads.  The vote keeps the wavefront's
+// lanes together, so that none spins ahead of a lane it waits for.  A thread
+// looks at most `polls` times; rows still undecided then are counted in *left
+// and the kernel is run again.  (Work-groups start in order and the lowest
+// undecided row can always decide, so a second run is rare.)
+// Work-groups of 256 or 512 rows are no faster (128x128x64 cells, all ten
+// passes: 8.7 and 8.4 ms, 8.1 with 1024), several rows per thread are slower
+// (a lane that starts on its next row stalls the others).
+constexpr int kMatchThreads = 1024;
+constexpr int kMatchPolls = 32768;
+__global__ void __launch_bounds__(kMatchThreads)
+k_match(int n, int polls, const int *__restrict__ rp, const int *__restrict__ lst,
+        const int *__restrict__ ncand, const int *__restrict__ nin, const int4 *__restrict__ rin,
+        const int4 *__restrict__ rcand, int *word, int *__restrict__ partner,
+        int *__restrict__ left)
 {
-    const int4 a = rin[v];
-    if (a.x == kOver) return lowest_free_in(v, in_ptr, in_row, st);
-    const bool f0 = a.x != kNone && st[a.x] == kFree;
-    const bool f1 = a.y != kNone && st[a.y] == kFree;
-    const bool f2 = a.z != kNone && st[a.z] == kFree;
-    const bool f3 = a.w != kNone && st[a.w] == kFree;
-    int m = kNone;
-    if (f0) m = a.x;
-    if (f1 && a.y < m) m = a.y;
-    if (f2 && a.z < m) m = a.z;
-    if (f3 && a.w < m) m = a.w;
-    return m;
-}
-
-__device__ inline int first_free_cand_rec(int v, const int4 *__restrict__ rcand,
-                                          const int *__restrict__ rp, const int *__restrict__ cj,
-                                          const int *__restrict__ ncand,
-                                          const int *__restrict__ st)
-{
-    const int4 c = rcand[v];
-    if (c.x == kOver) return first_free_cand(v, rp, cj, ncand, st);
-    const bool f0 = c.x >= 0 && st[c.x] == kFree;
-    const bool f1 = c.y >= 0 && st[c.y] == kFree;
-    const bool f2 = c.z >= 0 && st[c.z] == kFree;
-    const bool f3 = c.w >= 0 && st[c.w] == kFree;
-    return f0 ? c.x : f1 ? c.y : f2 ? c.z : f3 ? c.w : -1;
-}
-
-// One round.  An edge (i, j) between free rows is taken when i has no free
-// lower row pointing at it, j is i's first free candidate, and i is the
-// lowest free row pointing at j: the edge then comes first at both of its
-// ends.  A free row with no free lower row pointing at it and no free
-// candidate stays alone.  Every row evaluates this from the round's input
-// states (st) and writes only its own output state (st_next), so the two
-// ends of a taken edge reach the same decision independently.  If nfree is
-// set, the free rows of the input are counted into it (the host reads the
-// count of one round per batch only: counting in every round would put
-// thousands of atomics on one address each time); a set nfree_next is
-// cleared for the next round's count.
-__global__ void __launch_bounds__(kThreads)
-k_round(int n, const int *__restrict__ rp, const int *__restrict__ cj,
-        const int *__restrict__ ncand, const int *__restrict__ in_ptr,
-        const int *__restrict__ in_row, const int4 *__restrict__ rin,
-        const int4 *__restrict__ rcand, const int *__restrict__ st, int *__restrict__ st_next,
-        int *__restrict__ partner, int *__restrict__ nfree, int *__restrict__ nfree_next)
-{
-    const int v = blockIdx.x * blockDim.x + threadIdx.x;
-    if (v == 0 && nfree_next) *nfree_next = 0;
-    bool fr = false;
-    if (v < n) {
-        const int s0 = st[v];
-        int s1 = s0;
-        if (s0 == kFree) {
-            fr = true;
-            const int m = lowest_free_in_rec(v, rin, in_ptr, in_row, st);
-            if (m == kNone) {
-                const int p = first_free_cand_rec(v, rcand, rp, cj, ncand, st);
-                if (p < 0) {
-                    s1 = kSingle;
-                } else if (lowest_free_in_rec(p, rin, in_ptr, in_row, st) == v) {
-                    s1 = kLow;
-                    partner[v] = p;
-                }
-            } else if (lowest_free_in_rec(m, rin, in_ptr, in_row, st) == kNone &&
-                       first_free_cand_rec(m, rcand, rp, cj, ncand, st) == v) {
-                s1 = kHigh;
-                partner[v] = m;
+    __shared__ int own[kMatchThreads];
+    const int b0 = blockIdx.x * kMatchThreads, v = b0 + threadIdx.x;
+    own[threadIdx.x] = v < n ? word[v] : kSingle;
+    __syncthreads();
+    bool open = own[threadIdx.x] == kFree;
+    // what v waits for: the in-rows below v of `target` (v itself, then its
+    // candidates in order), up to four entries at a time
+    int target = v, pos = -1, cq = -1, nc = 0;
+    int4 a = make_int4(-1, -1, -1, -1), cand = a, rec0 = a;
+    // the next entries, from number pos on, of a list longer than a record
+    const auto next = [&]() {
+        int r[4] = {-1, -1, -1, -1};
+        const int e = rp[target + 1], m = nin[target];
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            while (pos < m && r[u] < 0) {
+                const int k = lst[e - 1 - pos++];
+                if (k < v) r[u] = k;
+            }
+        a = make_int4(r[0], r[1], r[2], r[3]);
+    };
+    const auto begin = [&](const int4 rec) {
+        pos = -1;
+        a = rec;
+        if (rec.x == kOver) {
+            pos = 0;
+            next();
+        } else {
+            if (a.x >= v) a.x = -1;
+            if (a.y >= v) a.y = -1;
+            if (a.z >= v) a.z = -1;
+            if (a.w >= v) a.w = -1;
+        }
+    };
+    if (open) {
+        cand = rcand[v];
+        nc = ncand[v];
+        begin(rin[v]);
+        if (cand.x >= 0) rec0 = rin[cand.x];  // (read ahead)
+    }
+    for (int it = 0; it < polls && __any(open); ++it) {
+        if (!open) continue;
+        const auto state = [&](int k) -> int {
+            if (k < 0) return kSingle;
+            const int o = k - b0;  // (no row above v is read)
+            if (o >= 0)
+                return __hip_atomic_load(&own[o], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            return __hip_atomic_load(word + k, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        };
+        const int w0 = state(a.x), w1 = state(a.y), w2 = state(a.z), w3 = state(a.w);
+        int by = -1;  // the row that has taken the target
+        if (w0 == ~target) by = a.x;
+        if (w1 == ~target) by = a.y;
+        if (w2 == ~target) by = a.z;
+        if (w3 == ~target) by = a.w;
+        if (w0 != kFree) a.x = -1;
+        if (w1 != kFree) a.y = -1;
+        if (w2 != kFree) a.z = -1;
+        if (w3 != kFree) a.w = -1;
+        if (by < 0) {
+            if ((a.x & a.y & a.z & a.w) != -1) continue;
+            if (pos >= 0) {
+                next();
+                if ((a.x & a.y & a.z & a.w) != -1) continue;
             }
         }
-        st_next[v] = s1;
+        int dec = kFree;
+        if (cq < 0 && by >= 0) {
+            partner[v] = by;
+            dec = kHigh;
+        } else if (cq >= 0 && by < 0) {
+            dec = ~target;  // no lower row took this candidate
+        } else if (++cq == nc) {
+            dec = kSingle;
+        } else {
+            target = cand.x == kOver ? lst[rp[v] + cq]
+                     : cq == 0       ? cand.x
+                     : cq == 1       ? cand.y
+                     : cq == 2       ? cand.z
+                                     : cand.w;
+            begin(cq == 0 && cand.x != kOver ? rec0 : rin[target]);
+        }
+        if (dec != kFree) {
+            __hip_atomic_store(&own[threadIdx.x], dec, __ATOMIC_RELAXED,
+                               __HIP_MEMORY_SCOPE_WORKGROUP);
+            __hip_atomic_store(word + v, dec, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            open = false;
+        }
     }
-    if (nfree) {  // the same for every block
-        const int cnt = __syncthreads_count(fr);
-        if (threadIdx.x == 0 && cnt) atomicAdd(nfree, cnt);
-    }
+    const int cnt = __syncthreads_count(open);
+    if (threadIdx.x == 0 && cnt) atomicAdd(left, cnt);
 }
 
-// A row opens an aggregate when it is alone or the lower row of its pair.
-__global__ void k_leaders(int n, const int *__restrict__ state, int *__restrict__ flag)
-{
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) flag[i] = state[i] != kHigh;
-}
-
-// Aggregate numbers in order of their lowest row (= creation order of the
-// ascending visit) and the member rows of every aggregate.
-__global__ void k_number(int n, const int *__restrict__ state, const int *__restrict__ partner,
-                         const int *__restrict__ pos, int *__restrict__ agg,
-                         int *__restrict__ mem0, int *__restrict__ mem1)
-{
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    const int st = state[i];
-    if (st == kHigh) {
-        agg[i] = pos[partner[i]];
-        return;
-    }
-    const int I = pos[i];
-    agg[i] = I;
-    mem0[I] = i;
-    mem1[I] = st == kLow ? partner[i] : -1;
-}
-
-// ---- exclusive scan of n ints: out[0..n], out[n] = total ----------------
+// ---- exclusive scan -----------------------------------------------------
 __device__ inline int block_inclusive(int *sh, int t)
 {
     sh[threadIdx.x] = t;
@@ -309,6 +274,11 @@ __device__ inline int block_inclusive(int *sh, int t)
     return sh[threadIdx.x];
 }
 
+// Exclusive scan inside each tile of kScanTile elements, tile totals to
+// tile_sum (which k_scan_sums turns into tile offsets): the scan of element i
+// is out[i] + tile_sum[i / kScanTile].  LEAD: in holds state words, and a row
+// counts one if it opens an aggregate (it is alone or has taken a row).
+template <bool LEAD>
 __global__ void __launch_bounds__(kThreads)
 k_scan_tile(const int *__restrict__ in, int *__restrict__ out, int *__restrict__ tile_sum, int n)
 {
@@ -317,7 +287,7 @@ k_scan_tile(const int *__restrict__ in, int *__restrict__ out, int *__restrict__
     int v[4], t = 0;
     for (int q = 0; q < 4; ++q) {
         const long long i = base + q;
-        v[q] = i < n ? in[i] : 0;
+        v[q] = i < n ? (LEAD ? in[i] != kHigh : in[i]) : 0;
         t += v[q];
     }
     const int incl = block_inclusive(sh, t);
@@ -350,10 +320,25 @@ k_scan_sums(int *__restrict__ tile_sum, int ntiles, int *__restrict__ total)
     if (threadIdx.x == 0) *total = carry_s;
 }
 
-__global__ void k_scan_add(int *__restrict__ out, const int *__restrict__ tile_sum, int n)
+// Aggregate numbers in order of their lowest row (= creation order of the
+// ascending visit) and the member rows of every aggregate; pos, tile: the
+// scan of the rows that open one.
+__global__ void k_number(int n, const int *__restrict__ word, const int *__restrict__ partner,
+                         const int *__restrict__ pos, const int *__restrict__ tile,
+                         int *__restrict__ agg, int *__restrict__ mem0, int *__restrict__ mem1)
 {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) out[i] += tile_sum[i / kScanTile];
+    if (i >= n) return;
+    const int w = word[i];
+    if (w == kHigh) {
+        const int p = partner[i];
+        agg[i] = pos[p] + tile[p / kScanTile];
+        return;
+    }
+    const int I = pos[i] + tile[i / kScanTile];
+    agg[i] = I;
+    mem0[I] = i;
+    mem1[I] = w < 0 ? ~w : -1;
 }
 
 // ---- Galerkin product for aggregates of one or two rows -----------------
@@ -411,9 +396,12 @@ __global__ void k_gal_rows(int nc, const int *__restrict__ rp, const int *__rest
     cnt[I] = m;
 }
 
+// rpc[0..nc) holds the rows' offsets inside their scan tile on entry and the
+// row pointers on return.
 __global__ void k_gal_fill(int nc, const int *__restrict__ rp, const int *__restrict__ mem0,
                            const int *__restrict__ mem1, const int *__restrict__ wj,
-                           const double *__restrict__ wv, const int *__restrict__ rpc,
+                           const double *__restrict__ wv, const int *__restrict__ cnt,
+                           const int *__restrict__ tile, int *__restrict__ rpc,
                            int *__restrict__ cic, double *__restrict__ valc)
 {
     const int I = blockIdx.x * blockDim.x + threadIdx.x;
@@ -421,7 +409,8 @@ __global__ void k_gal_fill(int nc, const int *__restrict__ rp, const int *__rest
     const int r0 = mem0[I], r1 = mem1[I];
     const int b0 = rp[r0], len0 = rp[r0 + 1] - b0;
     const int b1 = r1 >= 0 ? rp[r1] : 0;
-    const int o = rpc[I], m = rpc[I + 1] - o;
+    const int o = rpc[I] + tile[I / kScanTile], m = cnt[I];
+    rpc[I] = o;
     for (int t = 0; t < m; ++t) {
         const int q = gal_slot(t, b0, len0, b1);
         cic[o + t] = wj[q];
@@ -449,16 +438,12 @@ struct Chain {
     hipStream_t st = nullptr;
     HipFail hip_fail = nullptr;
     int *pinned = nullptr;
-    hipEvent_t ev[3] = {nullptr, nullptr, nullptr};
     hipEvent_t ev_lvl = nullptr;  // a new level is on the device
     // work arrays, sized for level 0 (no later matrix is larger)
     double *s = nullptr, *cs = nullptr, *smax = nullptr;
-    int *cj = nullptr, *ncand = nullptr, *partner = nullptr;
-    int *state[2] = {nullptr, nullptr};  // round input / output, alternating
-    int *in_ptr = nullptr, *in_row = nullptr;
+    int *lst = nullptr, *ncand = nullptr, *nin = nullptr, *partner = nullptr, *word = nullptr;
     int4 *rin = nullptr, *rcand = nullptr;  // per-row records of the two lists
-    hipStream_t cap = nullptr;            // capture stream for the round batches
-    int *pos = nullptr, *flag = nullptr, *cnt = nullptr, *tiles = nullptr, *ctr = nullptr;
+    int *pos = nullptr, *cnt = nullptr, *tiles = nullptr, *ctr = nullptr;
     int *a1 = nullptr, *a2 = nullptr, *aggf = nullptr, *mem0 = nullptr, *mem1 = nullptr;
     unsigned char *elig = nullptr;
     DevLevel set[3];  // M1 and two alternating coarse levels
@@ -483,15 +468,14 @@ struct Chain {
         k_fill_i32<<<nblocks(n), kThreads, 0, st>>>(p, v, n);
         launched();
     }
-    // out[0..n] = exclusive scan of in[0..n), out[n] = total
-    void scan(const int *in, int *out, int n)
+    // tile-wise exclusive scan of in[0..n) (see k_scan_tile), the total to *total
+    template <bool LEAD>
+    void scan(const int *in, int *out, int *total, int n)
     {
         const int ntiles = (int)std::max<long long>(1, ((long long)n + kScanTile - 1) / kScanTile);
-        k_scan_tile<<<ntiles, kThreads, 0, st>>>(in, out, tiles, n);
+        k_scan_tile<LEAD><<<ntiles, kThreads, 0, st>>>(in, out, tiles, n);
         launched();
-        k_scan_sums<<<1, kThreads, 0, st>>>(tiles, ntiles, out + n);
-        launched();
-        k_scan_add<<<nblocks(n), kThreads, 0, st>>>(out, tiles, n);
+        k_scan_sums<<<1, kThreads, 0, st>>>(tiles, ntiles, total);
         launched();
     }
     void strength(const DevLevel &L)
@@ -506,88 +490,36 @@ struct Chain {
     {
         const int n = L.n;
         if (!have_s) strength(L);
-        k_candidates<<<nblocks(n), kThreads, 0, st>>>(n, L.rp, L.ci, s, smax, elig, cj, cs, ncand);
+        k_lists<<<nblocks(n), kThreads, 0, st>>>(n, L.rp, L.ci, s, smax, elig, lst, cs, ncand, nin,
+                                                 rin, rcand, word);
         launched();
-        // in-lists (cnt counts, flag serves as the fill cursor)
-        fill(cnt, 0, n);
-        fill(flag, 0, n);
-        k_in_count<<<nblocks(n), kThreads, 0, st>>>(n, L.rp, cj, ncand, cnt);
-        launched();
-        scan(cnt, in_ptr, n);
-        k_in_fill<<<nblocks(n), kThreads, 0, st>>>(n, L.rp, cj, ncand, in_ptr, flag, in_row);
-        launched();
-        k_records<<<nblocks(n), kThreads, 0, st>>>(n, L.rp, cj, ncand, in_ptr, in_row, rin,
-                                                   rcand);
-        launched();
-        fill(state[0], kFree, n);
-        fill(ctr, 0, 2);
-        // kBatch rounds (an even number: the states end in state[0]) as one graph
-        hipGraphExec_t exec = nullptr;
-        {
-            ck(hipStreamBeginCapture(cap, hipStreamCaptureModeThreadLocal));
-            // only the batch's last round counts its free rows (into ctr[1],
-            // cleared by the round before it)
-            for (int q = 0; q < kBatch; ++q) {
-                const int a = q & 1;
-                k_round<<<nblocks(n), kThreads, 0, cap>>>(
-                    n, L.rp, cj, ncand, in_ptr, in_row, rin, rcand, state[a], state[a ^ 1], partner,
-                    q == kBatch - 1 ? ctr + 1 : nullptr, q == kBatch - 2 ? ctr + 1 : nullptr);
-            }
-            hipGraph_t g = nullptr;
-            const hipError_t e1 = hipStreamEndCapture(cap, &g);
-            const hipError_t e2 = e1 == hipSuccess ? hipGraphInstantiate(&exec, g, nullptr, nullptr, 0)
-                                                   : e1;
-            if (g) (void)hipGraphDestroy(g);
-            ck(e2);
+        // every run of the matching decides at least the lowest undecided row
+        for (long long run = 0;; ++run) {
+            if (run > (long long)n + 1) hip_fail(hipErrorUnknown);
+            fill(ctr + 1, 0, 1);
+            k_match<<<nblocks(n, kMatchThreads), kMatchThreads, 0, st>>>(
+                n, kMatchPolls, L.rp, lst, ncand, nin, rin, rcand, word, partner, ctr + 1);
+            launched();
+            scan<true>(word, pos, ctr, n);
+            k_number<<<nblocks(n), kThreads, 0, st>>>(n, word, partner, pos, tiles, agg, mem0, mem1);
+            launched();
+            ck(hipMemcpyAsync(pinned, ctr, 2 * sizeof(int), hipMemcpyDeviceToHost, st));
+            ck(hipStreamSynchronize(st));
+            if (pinned[1] == 0) return pinned[0];
         }
-        struct ExecGuard {
-            hipGraphExec_t e;
-            hipStream_t s;
-            ~ExecGuard()
-            {
-                (void)hipStreamSynchronize(s);
-                (void)hipGraphExecDestroy(e);
-            }
-        } exec_guard{exec, st};
-        // batches are queued two ahead of the one whose free count is read,
-        // so the device always has rounds queued while the host checks
-        long long r = 0;
-        const long long cap_rounds = (long long)n + 6LL * kBatch + 4;
-        for (int batch = 0;; ++batch) {
-            ck(hipGraphLaunch(exec, st));
-            r += kBatch;
-            // free rows at the start of the batch's last round
-            const int slot = batch % 3;
-            ck(hipMemcpyAsync(pinned + slot, ctr + 1, sizeof(int),
-                              hipMemcpyDeviceToHost, st));
-            ck(hipEventRecord(ev[slot], st));
-            if (batch >= 2) {
-                const int old = (batch - 2) % 3;
-                ck(hipEventSynchronize(ev[old]));
-                if (pinned[old] == 0) break;
-            }
-            // every round settles at least the lowest free row
-            if (r > cap_rounds) hip_fail(hipErrorUnknown);
-        }
-        k_leaders<<<nblocks(n), kThreads, 0, st>>>(n, state[0], flag);
-        launched();
-        scan(flag, pos, n);
-        k_number<<<nblocks(n), kThreads, 0, st>>>(n, state[0], partner, pos, agg, mem0, mem1);
-        launched();
-        return read_int(pos + n, 4);
     }
     // C = P^T L P for the pass just numbered (aggregates of one or two rows),
-    // queued without a wait (nnz(C) is C.rp[nc] on the device).  The
-    // candidate arrays serve as the row lists.
+    // queued without a wait (nnz(C) is C.rp[nc] on the device).  The list
+    // arrays serve as the row lists.
     void galerkin(const DevLevel &L, const int *agg, int nc, DevLevel &C)
     {
         C.n = nc;
-        k_gal_rows<<<nblocks(nc), kThreads, 0, st>>>(nc, L.rp, L.ci, L.val, agg, mem0, mem1, cj,
+        k_gal_rows<<<nblocks(nc), kThreads, 0, st>>>(nc, L.rp, L.ci, L.val, agg, mem0, mem1, lst,
                                                      s, cnt);
         launched();
-        scan(cnt, C.rp, nc);
-        k_gal_fill<<<nblocks(nc), kThreads, 0, st>>>(nc, L.rp, mem0, mem1, cj, s, C.rp, C.ci,
-                                                     C.val);
+        scan<false>(cnt, C.rp, C.rp + nc, nc);
+        k_gal_fill<<<nblocks(nc), kThreads, 0, st>>>(nc, L.rp, mem0, mem1, lst, s, cnt, tiles, C.rp,
+                                                     C.ci, C.val);
         launched();
     }
     void to_device(const Csr &H, DevLevel &C)
@@ -605,12 +537,9 @@ struct Chain {
 
 struct EventGuard {
     hipEvent_t *ev;
-    hipEvent_t *ev_lvl;
     ~EventGuard()
     {
-        for (int i = 0; i < 3; ++i)
-            if (ev[i]) (void)hipEventDestroy(ev[i]);
-        if (*ev_lvl) (void)hipEventDestroy(*ev_lvl);
+        if (*ev) (void)hipEventDestroy(*ev);
     }
 };
 
@@ -629,21 +558,18 @@ size_t place(Chain &X, char *base, int n0, long long nnz0)
     X.s = (double *)take(nnz0, sizeof(double));
     X.cs = (double *)take(nnz0, sizeof(double));
     X.smax = (double *)take(n0, sizeof(double));
-    X.cj = (int *)take(nnz0, sizeof(int));
-    X.in_row = (int *)take(nnz0, sizeof(int));
+    X.lst = (int *)take(nnz0, sizeof(int));
     X.ncand = (int *)take(n0, sizeof(int));
-    X.state[0] = (int *)take(n0, sizeof(int));
-    X.state[1] = (int *)take(n0, sizeof(int));
+    X.nin = (int *)take(n0, sizeof(int));
+    X.word = (int *)take(n0, sizeof(int));
     X.partner = (int *)take(n0, sizeof(int));
     X.a1 = (int *)take(n0, sizeof(int));
     X.a2 = (int *)take(n0, sizeof(int));
     X.aggf = (int *)take(n0, sizeof(int));
-    X.in_ptr = (int *)take(n1, sizeof(int));
     X.mem0 = (int *)take(n1, sizeof(int));
     X.mem1 = (int *)take(n1, sizeof(int));
     X.pos = (int *)take(n1, sizeof(int));
     X.cnt = (int *)take(n1, sizeof(int));
-    X.flag = (int *)take(n1, sizeof(int));
     X.tiles = (int *)take(ntiles, sizeof(int));
     X.ctr = (int *)take(4, sizeof(int));
     X.elig = (unsigned char *)take(n0, 1);
@@ -668,7 +594,7 @@ size_t device_chain_bytes(int n0, long long nnz0)
 int device_hierarchy(Csr &A0, const int *rp0, const int *ci0, const double *val0,
                      int max_coarse, int max_levels, int max_dense, Hierarchy &H,
                      const LevelCallback &on_smoothed, const std::function<void()> &level0_values,
-                     hipStream_t st, hipStream_t cap, hipStream_t copy_st,
+                     hipStream_t st, hipStream_t copy_st,
                      const DeviceAlloc &alloc, HipFail hip_fail, int *pinned,
                      const PinnedBuffer &staging)
 {
@@ -682,11 +608,9 @@ int device_hierarchy(Csr &A0, const int *rp0, const int *ci0, const double *val0
     }
     Chain X;
     X.st = st;
-    X.cap = cap;
     X.hip_fail = hip_fail;
     X.pinned = pinned;
-    EventGuard guard{X.ev, &X.ev_lvl};
-    for (int i = 0; i < 3; ++i) X.ck(hipEventCreateWithFlags(&X.ev[i], hipEventDisableTiming));
+    EventGuard guard{&X.ev_lvl};
     X.ck(hipEventCreateWithFlags(&X.ev_lvl, hipEventDisableTiming));
     // one allocation for every work array
     char *base = (char *)alloc(place(X, nullptr, n0, nnz0));
