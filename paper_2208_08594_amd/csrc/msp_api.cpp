@@ -217,7 +217,7 @@ struct msp_ctx {
     // apply, Gram-Schmidt step): summed ms and counts over the last solve
     bool timing = false;
     hipEvent_t tev[4] = {nullptr, nullptr, nullptr, nullptr};
-    hipEvent_t ev_step = nullptr;  // end of the solve's last queued step
+    hipEvent_t ev_step[2] = {nullptr, nullptr};  // ends of the solve's last two queued steps
     double t_ms[kTimedParts] = {0, 0, 0};
     int t_calls[kTimedParts] = {0, 0, 0};
 
@@ -1462,15 +1462,41 @@ void capture_apply(msp_ctx *c)
     }
 }
 
-void apply(msp_ctx *c, const double *v, double *z, bool capture_ok = true)
+// Kernel launches of one apply (the N stage's groups included).
+int apply_launches(const msp_ctx *c)
 {
-    if (!c->opt.use_graphs || (!c->apply_exec && !capture_ok)) {
+    int k = 6;
+    for (const Level &L : c->lev) k += (c->opt.nu_pre + c->opt.nu_post) * L.g + 4;
+    if (c->opt.full_smoother == 0) k += c->bilu.L.nseg() + c->bilu.U.nseg();
+    if (c->ns.on) k += (int)c->ns.grp_ptr.size() + 4;
+    return k;
+}
+
+// Applies of up to this many launches are launched one by one: a step queued
+// ahead keeps the stream filled, and a graph launch costs 20 to 30 us of idle
+// device around it (eight 20^3 systems solved together, 11 launches each:
+// 7.4 ms with graphs, 4.3 without; 60x220x85 cells layered, 140 launches:
+// 111.3 and 110.4 ms).  Longer ones (the dependency levels of the natural
+// elimination order) would keep the host busy for as long as they run
+// (16x14x19 cells: 3.06 ms with graphs, 3.17 without).
+constexpr int kEagerLaunches = 160;
+
+bool apply_by_graph(const msp_ctx *c, bool capture_ok)
+{
+    return c->opt.use_graphs && (c->apply_exec || capture_ok) &&
+           apply_launches(c) > kEagerLaunches;
+}
+
+// io_set: *c->io already holds v and z (set by work queued before).
+void apply(msp_ctx *c, const double *v, double *z, bool capture_ok = true, bool io_set = false)
+{
+    if (!apply_by_graph(c, capture_ok)) {
         apply_eager(c, v, z);
         return;
     }
     if (!c->apply_exec) capture_apply(c);
     if (apply_via_io(c)) {
-        HIPCHK(launch_set_io(c->io, v, z, c->stream));
+        if (!io_set) HIPCHK(launch_set_io(c->io, v, z, c->stream));
         HIPCHK(hipGraphLaunch(c->apply_exec, c->stream));
         return;
     }
@@ -1550,7 +1576,14 @@ void ensure_workspace(msp_ctx *c)
 // the same either way.  graph_ok = false keeps the preconditioner apply eager
 // unless its graph already exists, so the solve itself creates nothing on the
 // device.
+// An Arnoldi step needs nothing from the host's part of the step before it
+// (its vector is scaled by the norm on the device), so while the residual is
+// still kAheadFactor above the tolerance the next step is queued before the
+// host has seen this one, which hides the host's turn (25 us of about 120 us
+// per step on 4,000 unknowns).  A step queued past the end of a cycle leaves
+// only entries of V, Z and w that nothing reads.
 struct Fgmres {
+    static constexpr double kAheadFactor = 20.0;
     msp_ctx *c = nullptr;
     Krylov K;
     bool graph_ok = true;
@@ -1562,21 +1595,29 @@ struct Fgmres {
     std::vector<double> H, cs, sn, g, y;
     double bnorm = 0.0, tol = 0.0, beta = 0.0, relres = 0.0;
     int iters = 0, restarts = 0, j = 0, status = MSP_OK;
-    enum Stage { kBnorm, kBeta, kStep, kDone } stage = kBnorm;
+    int queued = -1;  // last Arnoldi step of the cycle that is queued
+    enum Stage { kStart, kBeta, kStep, kDone } stage = kStart;
     double t0 = 0.0, ms = 0.0;
 
     double *h1() const { return K.hbuf; }
     double *h2() const { return K.hbuf + (m + 1); }
     double *hn() const { return K.hbuf + 2 * (m + 1); }
-    void mark() { HIPCHK(hipEventRecord(c->ev_step, c->stream)); }
-    // queue sum_i v_i^2 into hhost[0]
-    void queue_norm2(const double *v)
+    int nscal() const { return 2 * (m + 1) + 1; }
+    // pinned: the scalars of even and of odd steps, then y
+    double *host_slot(int step) const { return c->hhost + (step & 1) * nscal(); }
+    double *host_y() const { return c->hhost + 2 * nscal(); }
+    GsTail tail(double *out, int nhost = 0, double *host = nullptr) const
     {
-        HIPCHK(launch_dot_multi(N, 1, v, N, v, K.partial, c->stream));
-        HIPCHK(launch_reduce_partials(1, K.partial, K.hbuf, 0, c->stream));
-        HIPCHK(hipMemcpyAsync(c->hhost, K.hbuf, sizeof(double), hipMemcpyDeviceToHost,
-                              c->stream));
-        mark();
+        return GsTail{c->flag + 3, out, K.hbuf, nhost, host};
+    }
+    void mark(int step) { HIPCHK(hipEventRecord(c->ev_step[step & 1], c->stream)); }
+    hipEvent_t event() const { return c->ev_step[stage == kStep ? j & 1 : 0]; }
+    // queue sum_i v_i^2 (and first_i^2) into host slot 0
+    void queue_norm2(const double *v, const double *first = nullptr)
+    {
+        HIPCHK(launch_norm2(N, v, first, K.partial, tail(K.hbuf, first ? 2 : 1, host_slot(0)),
+                            c->stream));
+        mark(0);
     }
     void finish(int st)
     {
@@ -1598,43 +1639,54 @@ struct Fgmres {
             c->t_ms[q] = 0.0;
             c->t_calls[q] = 0;
         }
-        stage = kBnorm;
-        queue_norm2(rhs);
+        stage = kStart;
+        HIPCHK(launch_clear_i32(c->flag + 3, c->stream));
+        spmv(c, x, rhs, K.w);
+        queue_norm2(K.w, rhs);
     }
-    // Arnoldi step j: z_j = B v_j, w = A z_j, classical Gram-Schmidt twice
-    // (h1 = V^T w, w -= V h1, h2 = V^T w, w -= V h2, hn = w^T w; each update
-    // pass also forms the next dot products: three passes over V), the
-    // coefficients to the host
-    void queue_step()
+    // Arnoldi step q: v_q = w / sqrt(s2), z_q = B v_q, w = A z_q, classical
+    // Gram-Schmidt twice (h1 = V^T w, w -= V h1, h2 = V^T w, w -= V h2, hn =
+    // w^T w; each update pass also forms the next dot products: three passes
+    // over V), the coefficients to the host
+    void queue_step(int q, const double *s2)
     {
-        double *vj = K.V + (size_t)j * N;
-        double *zj = K.Z + (size_t)j * N;
+        double *vq = K.V + (size_t)q * N;
+        double *zq = K.Z + (size_t)q * N;
+        const bool io = apply_by_graph(c, graph_ok) && apply_via_io(c);
+        HIPCHK(launch_scale(N, K.w, s2, vq, io ? c->io : nullptr, zq, c->stream));
         if (c->timing) HIPCHK(hipEventRecord(c->tev[0], c->stream));
-        apply(c, vj, zj, graph_ok);
+        apply(c, vq, zq, graph_ok, io);
         if (c->timing) HIPCHK(hipEventRecord(c->tev[1], c->stream));
-        spmv(c, zj, nullptr, K.w);
+        spmv(c, zq, nullptr, K.w);
         if (c->timing) HIPCHK(hipEventRecord(c->tev[2], c->stream));
-        const int nv = j + 1;
+        const int nv = q + 1;
         if (nv <= kFusedGsMax) {
-            HIPCHK(launch_gs_pass(0, N, nv, K.V, N, nullptr, K.w, K.partial, c->stream));
-            HIPCHK(launch_reduce_partials(nv, K.partial, h1(), 0, c->stream));
-            HIPCHK(launch_gs_pass(1, N, nv, K.V, N, h1(), K.w, K.partial, c->stream));
-            HIPCHK(launch_reduce_partials(nv, K.partial, h2(), 0, c->stream));
-            HIPCHK(launch_gs_pass(2, N, nv, K.V, N, h2(), K.w, K.partial, c->stream));
+            HIPCHK(launch_gs_pass(0, N, nv, K.V, N, nullptr, K.w, K.partial, tail(h1()),
+                                  c->stream));
+            HIPCHK(launch_gs_pass(1, N, nv, K.V, N, h1(), K.w, K.partial, tail(h2()), c->stream));
+            HIPCHK(launch_gs_pass(2, N, nv, K.V, N, h2(), K.w, K.partial,
+                                  tail(hn(), nscal(), host_slot(q)), c->stream));
         } else {
-            HIPCHK(launch_dot_multi(N, nv, K.V, N, K.w, K.partial, c->stream));
-            HIPCHK(launch_reduce_partials(nv, K.partial, h1(), 0, c->stream));
-            HIPCHK(launch_axpy_multi(N, nv, K.V, N, h1(), K.w, c->stream));
-            HIPCHK(launch_dot_multi(N, nv, K.V, N, K.w, K.partial, c->stream));
-            HIPCHK(launch_reduce_partials(nv, K.partial, h2(), 0, c->stream));
-            HIPCHK(launch_axpy_multi(N, nv, K.V, N, h2(), K.w, c->stream));
-            HIPCHK(launch_dot_multi(N, 1, K.w, N, K.w, K.partial, c->stream));
+            for (double *h : {h1(), h2()}) {
+                HIPCHK(launch_dot_multi(N, nv, K.V, N, K.w, K.partial, c->stream));
+                HIPCHK(launch_reduce_partials(nv, kDotBlocks, K.partial, h, nullptr, 0, nullptr,
+                                              c->stream));
+                HIPCHK(launch_axpy_multi(N, nv, K.V, N, h, K.w, c->stream));
+            }
+            HIPCHK(launch_norm2(N, K.w, nullptr, K.partial, tail(hn(), nscal(), host_slot(q)),
+                                c->stream));
         }
-        HIPCHK(launch_reduce_partials(1, K.partial, hn(), 0, c->stream));
         if (c->timing) HIPCHK(hipEventRecord(c->tev[3], c->stream));
-        HIPCHK(hipMemcpyAsync(c->hhost, K.hbuf, sizeof(double) * (2 * (m + 1) + 1),
-                              hipMemcpyDeviceToHost, c->stream));
-        mark();
+        mark(q);
+        queued = q;
+    }
+    // The step after the last queued one, if it will surely be taken as far
+    // as is known.  (Timed solves read each step's events before the next.)
+    void queue_ahead()
+    {
+        if (c->timing || queued != j || j + 1 >= m || iters + 1 >= c->opt.max_iter) return;
+        if (!(std::fabs(g[j]) > kAheadFactor * tol)) return;
+        queue_step(j + 1, hn());
     }
     // x += Z y for the k steps of the cycle, then the true residual's norm
     void queue_update(int k)
@@ -1644,9 +1696,9 @@ struct Fgmres {
             for (int q = i + 1; q < k; ++q) acc -= H[(size_t)i * m + q] * y[q];
             y[i] = acc / H[(size_t)i * m + i];
         }
-        std::memcpy(c->hhost + 2 * (m + 2), y.data(), sizeof(double) * k);
-        HIPCHK(hipMemcpyAsync(K.ydev, c->hhost + 2 * (m + 2), sizeof(double) * k,
-                              hipMemcpyHostToDevice, c->stream));
+        std::memcpy(host_y(), y.data(), sizeof(double) * k);
+        HIPCHK(hipMemcpyAsync(K.ydev, host_y(), sizeof(double) * k, hipMemcpyHostToDevice,
+                              c->stream));
         HIPCHK(launch_update_x(N, k, K.Z, N, K.ydev, x, c->stream));
         spmv(c, x, rhs, K.w);
         queue_norm2(K.w);
@@ -1656,8 +1708,8 @@ struct Fgmres {
     // The step just waited for is complete: do the host part, queue the next.
     void advance()
     {
-        if (stage == kBnorm) {
-            const double bn2 = c->hhost[0];
+        if (stage == kStart) {
+            const double bn2 = host_slot(0)[1];
             if (!std::isfinite(bn2)) return finish(MSP_ERR_NONFINITE);
             bnorm = std::sqrt(bn2);
             if (bnorm == 0.0) {
@@ -1666,26 +1718,23 @@ struct Fgmres {
                 return finish(MSP_OK);
             }
             tol = rtol * bnorm;
-            spmv(c, x, rhs, K.w);
-            queue_norm2(K.w);
             stage = kBeta;
-            return;
         }
         if (stage == kBeta) {
-            beta = std::sqrt(c->hhost[0]);
+            beta = std::sqrt(host_slot(0)[0]);
             if (!std::isfinite(beta)) return finish(MSP_ERR_NONFINITE);
             relres = beta / bnorm;
             if (beta <= tol) return finish(MSP_OK);
             if (iters >= c->opt.max_iter) return finish(MSP_NOT_CONVERGED);
-            HIPCHK(launch_scale(N, K.w, beta, K.V, c->stream));
             std::fill(g.begin(), g.end(), 0.0);
             g[0] = beta;
             j = 0;
             stage = kStep;
-            queue_step();
+            queue_step(0, K.hbuf);
+            queue_ahead();
             return;
         }
-        // kStep: the coefficients of Arnoldi step j are in hhost
+        // kStep: the coefficients of Arnoldi step j are in its host slot
         if (c->timing) {
             for (int q = 0; q < kTimedParts; ++q) {
                 // events 0..3 bracket apply (0,1), SpMV (1,2), Gram-Schmidt (2,3)
@@ -1696,8 +1745,8 @@ struct Fgmres {
                 c->t_calls[q]++;
             }
         }
-        const double *hh1 = c->hhost, *hh2 = c->hhost + (m + 1);
-        const double hnorm = std::sqrt(c->hhost[2 * (m + 1)]);
+        const double *hh1 = host_slot(j), *hh2 = hh1 + (m + 1);
+        const double hnorm = std::sqrt(hh1[2 * (m + 1)]);
         if (!std::isfinite(hnorm)) return finish(MSP_ERR_NONFINITE);
         for (int i = 0; i <= j; ++i) H[(size_t)i * m + j] = hh1[i] + hh2[i];
         H[(size_t)(j + 1) * m + j] = hnorm;
@@ -1718,9 +1767,9 @@ struct Fgmres {
         if (hnorm == 0.0 || std::fabs(g[j + 1]) <= tol || iters >= c->opt.max_iter ||
             j + 1 == m)
             return queue_update(j + 1);
-        HIPCHK(launch_scale(N, K.w, hnorm, K.V + (size_t)(j + 1) * N, c->stream));
         ++j;
-        queue_step();
+        if (queued < j) queue_step(j, hn());
+        queue_ahead();
     }
 };
 
@@ -1747,7 +1796,7 @@ void run_solves(std::vector<Fgmres> &runs)
             if (r.stage == Fgmres::kDone) continue;
             busy = true;
             guard(r, [&]() {
-                HIPCHK(hipEventSynchronize(r.c->ev_step));
+                HIPCHK(hipEventSynchronize(r.event()));
                 r.advance();
             });
         }
@@ -1970,7 +2019,7 @@ int msp_create(msp_ctx **ctx, const msp_options *opt)
         HIPCHK(hipGetDevice(&c->device));
         if (int e = init_scratch(c->device)) return e;
         c->stream = (hipStream_t)o.stream;
-        HIPCHK(hipEventCreateWithFlags(&c->ev_step, hipEventDisableTiming));
+        for (auto &e : c->ev_step) HIPCHK(hipEventCreateWithFlags(&e, hipEventDisableTiming));
         HIPCHK(hipHostMalloc((void **)&c->hhost, sizeof(double) * 1024, hipHostMallocDefault));
         HIPCHK(hipHostMalloc((void **)&c->flag_host, sizeof(int) * 4, hipHostMallocDefault));
         HIPCHK(hipHostMalloc((void **)&c->chain_host, sizeof(int) * 16, hipHostMallocDefault));
@@ -2017,7 +2066,7 @@ int msp_destroy(msp_ctx *c)
         kill_stream(c->chain_copy);
         kill_event(c->ev_a0);
         for (auto &e : c->tev) kill_event(e);
-        kill_event(c->ev_step);
+        for (auto &e : c->ev_step) kill_event(e);
         kill_stream(c->side);
         kill_stream(c->gj.aux);
         kill_stream(c->gj.main);

@@ -201,21 +201,45 @@ constexpr int kDotBlocks = 1024;
 // partial[blk * nv + i] = sum over the block's chunk of V_i . w  (V_i = V + i*ldv)
 hipError_t launch_dot_multi(long long N, int nv, const double *V, long long ldv, const double *w,
                             double *partial, hipStream_t st);
-// out[i] = sum_blk partial[blk*nv + i] (+ out[i] if accumulate)
-hipError_t launch_reduce_partials(int nv, const double *partial, double *out, int accumulate,
-                                  hipStream_t st);
+// out[i] = sum_blk partial[blk*nv + i] over nblk blocks; with host != nullptr
+// then copies the nhost doubles at src (device) to page-locked host memory.
+hipError_t launch_reduce_partials(int nv, int nblk, const double *partial, double *out,
+                                  const double *src, int nhost, double *host, hipStream_t st);
 // w -= sum_i h[i] V_i
 hipError_t launch_axpy_multi(long long N, int nv, const double *V, long long ldv,
                              const double *h, double *w, hipStream_t st);
+// Work-groups of the Gram-Schmidt and norm passes over N entries: four entries
+// per thread while that gives at most kDotBlocksFused work-groups (262,144
+// entries), whose last one then adds up the partials itself (one launch less
+// per pass), else kDotBlocks and a reduction launch.  Stretching the 256
+// work-groups over more entries costs more than the launch: 553,000 unknowns,
+// one FGMRES solve of 10 iterations 2.94 -> 3.20 ms.
+constexpr int kDotBlocksFused = 256;
+int gs_blocks(long long N);
+// Where a pass's sums go: out (device); with host != nullptr also, with the
+// nhost doubles at src (out among them), to page-locked host memory.  ctr: an
+// int that is zero between passes (one pass at a time).
+struct GsTail {
+    int *ctr;
+    double *out;
+    const double *src;
+    int nhost;
+    double *host;
+};
 // One pass of the Gram-Schmidt step over nv <= kFusedGsMax basis vectors,
-// each V entry read once: mode 0 the partials of V_i . w (as
-// launch_dot_multi), mode 1 w -= sum_i h[i] V_i then the partials of V_i . w,
-// mode 2 the same update then the partials of w . w (one value per block).
+// each V entry read once: mode 0 the sums V_i . w, mode 1 w -= sum_i h[i] V_i
+// then the sums V_i . w, mode 2 the same update then w . w (one sum).
 constexpr int kFusedGsMax = 32;
 hipError_t launch_gs_pass(int mode, long long N, int nv, const double *V, long long ldv,
-                          const double *h, double *w, double *partial, hipStream_t st);
-// y = x / s
-hipError_t launch_scale(long long N, const double *x, double s, double *y, hipStream_t st);
+                          const double *h, double *w, double *partial, const GsTail &tail,
+                          hipStream_t st);
+// tail.out[0] = x . x, and tail.out[1] = first . first if first != nullptr
+hipError_t launch_norm2(long long N, const double *x, const double *first, double *partial,
+                        const GsTail &tail, hipStream_t st);
+hipError_t launch_clear_i32(int *x, hipStream_t st);
+// y = x / sqrt(*s2); with io != nullptr also sets io->v = y, io->z = z
+hipError_t launch_scale(long long N, const double *x, const double *s2, double *y, ApplyIo *io,
+                        double *z, hipStream_t st);
 // x += sum_i y[i] Z_i
 hipError_t launch_update_x(long long N, int k, const double *Z, long long ldz, const double *y,
                            double *x, hipStream_t st);

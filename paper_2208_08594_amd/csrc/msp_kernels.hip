@@ -1189,17 +1189,51 @@ __global__ __launch_bounds__(kThreads) void k_dot_multi(long long N, int nv,
 // out[i] = sum over the nblk blocks of partial[b * nv + i]: one wave per
 // vector i (lane l adds blocks l, l + 64, ... in order, then a fixed
 // butterfly across the wave), so every sum has a fixed order.
-constexpr int kReduceThreads = 1024;
-__global__ __launch_bounds__(kReduceThreads) void k_reduce_partials(
-    int nv, int nblk, const double *__restrict__ partial, double *__restrict__ out,
-    int accumulate)
+__device__ __forceinline__ void sum_partials(int nv, int nblk, const double *partial, double *out,
+                                             int nwaves)
 {
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    for (int i = wave; i < nv; i += kReduceThreads / 64) {
+    for (int i = wave; i < nv; i += nwaves) {
         double s = 0.0;
         for (int b = lane; b < nblk; b += 64) s += partial[(long long)b * nv + i];
         s = wave_sum(s);
-        if (lane == 0) out[i] = accumulate ? out[i] + s : s;
+        if (lane == 0) out[i] = s;
+    }
+}
+
+// host != nullptr: then also copies the nhost doubles at src (out among them)
+// to page-locked host memory, which saves the copy a launch of its own.
+constexpr int kReduceThreads = 1024;
+__global__ __launch_bounds__(kReduceThreads) void k_reduce_partials(
+    int nv, int nblk, const double *__restrict__ partial, double *out, const double *src,
+    int nhost, double *host)
+{
+    sum_partials(nv, nblk, partial, out, kReduceThreads / 64);
+    if (host) {
+        __syncthreads();
+        for (int q = threadIdx.x; q < nhost; q += kReduceThreads) host[q] = src[q];
+    }
+}
+
+// The reduction of a pass's partial sums by the last of its work-groups to
+// finish (ctr: zero before the pass, and again after it), instead of a launch
+// of its own: for grids of at most kDotBlocksFused work-groups, whose partials
+// one work-group reads in a few microseconds.
+__device__ __forceinline__ void reduce_in_last_block(int nv, const double *partial,
+                                                     const GsTail &t)
+{
+    __shared__ int last;
+    __threadfence();  // this work-group's partials, before it counts itself
+    __syncthreads();
+    if (threadIdx.x == 0) last = atomicAdd(t.ctr, 1) == (int)gridDim.x - 1;
+    __syncthreads();
+    if (!last) return;
+    __threadfence();  // the others' partials
+    sum_partials(nv, gridDim.x, partial, t.out, kThreads / 64);
+    if (threadIdx.x == 0) *t.ctr = 0;
+    if (t.host) {
+        __syncthreads();
+        for (int q = threadIdx.x; q < t.nhost; q += kThreads) t.host[q] = t.src[q];
     }
 }
 
@@ -1234,7 +1268,7 @@ __global__ __launch_bounds__(kThreads) void k_gs_pass(long long N, const double 
                                                       long long ldv,
                                                       const double *__restrict__ h,
                                                       double *__restrict__ w,
-                                                      double *__restrict__ partial)
+                                                      double *partial, GsTail tail)
 {
     constexpr int NOUT = MODE == 2 ? 1 : NV;
     __shared__ double hs[NV];
@@ -1278,11 +1312,53 @@ __global__ __launch_bounds__(kThreads) void k_gs_pass(long long N, const double 
     if (threadIdx.x < NOUT)
         partial[(long long)blockIdx.x * NOUT + threadIdx.x] =
             (red[0][threadIdx.x] + red[1][threadIdx.x]) + (red[2][threadIdx.x] + red[3][threadIdx.x]);
+    if (tail.ctr) reduce_in_last_block(NOUT, partial, tail);
 }
 
-__global__ __launch_bounds__(kThreads) void k_scale(long long N, const double *__restrict__ x,
-                                                    double s, double *__restrict__ y)
+// Partial sums of x . x (first != nullptr: and of first . first beside it),
+// each with the grid and order of k_gs_pass.
+__global__ __launch_bounds__(kThreads) void k_norm2(long long N, const double *__restrict__ x,
+                                                    const double *__restrict__ first,
+                                                    double *partial, GsTail tail)
 {
+    __shared__ double red[4][2];
+    const long long chunk = ((N + gridDim.x - 1) / gridDim.x + 63) & ~63LL;
+    const long long b0 = (long long)blockIdx.x * chunk;
+    const long long b1 = b0 + chunk < N ? b0 + chunk : N;
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, nv = first ? 2 : 1;
+    double a0 = 0.0, a1 = 0.0;
+    for (long long q = b0 + threadIdx.x; q < b1; q += kThreads) {
+        const double v = x[q];
+        a0 += v * v;
+        if (first) {
+            const double u = first[q];
+            a1 += u * u;
+        }
+    }
+    a0 = wave_sum(a0);
+    a1 = wave_sum(a1);
+    if (lane == 0) {
+        red[wave][0] = a0;
+        red[wave][1] = a1;
+    }
+    __syncthreads();
+    if ((int)threadIdx.x < nv)
+        partial[(long long)blockIdx.x * nv + threadIdx.x] =
+            (red[0][threadIdx.x] + red[1][threadIdx.x]) + (red[2][threadIdx.x] + red[3][threadIdx.x]);
+    if (tail.ctr) reduce_in_last_block(nv, partial, tail);
+}
+
+// y = x / sqrt(*s2); also hands the next preconditioner apply its vectors
+__global__ __launch_bounds__(kThreads) void k_scale(long long N, const double *__restrict__ x,
+                                                    const double *__restrict__ s2,
+                                                    double *__restrict__ y, ApplyIo *io,
+                                                    double *z)
+{
+    if (io && blockIdx.x == 0 && threadIdx.x == 0) {
+        io->v = y;
+        io->z = z;
+    }
+    const double s = sqrt(*s2);
     for (long long q = (long long)blockIdx.x * kThreads + threadIdx.x; q < N;
          q += (long long)gridDim.x * kThreads)
         y[q] = x[q] / s;
@@ -2226,11 +2302,17 @@ hipError_t launch_dot_multi(long long N, int nv, const double *V, long long ldv,
     return hipGetLastError();
 }
 
-hipError_t launch_reduce_partials(int nv, const double *partial, double *out, int accumulate,
-                                  hipStream_t st)
+hipError_t launch_reduce_partials(int nv, int nblk, const double *partial, double *out,
+                                  const double *src, int nhost, double *host, hipStream_t st)
 {
-    k_reduce_partials<<<1, kReduceThreads, 0, st>>>(nv, kDotBlocks, partial, out, accumulate);
+    k_reduce_partials<<<1, kReduceThreads, 0, st>>>(nv, nblk, partial, out, src, nhost, host);
     return hipGetLastError();
+}
+
+int gs_blocks(long long N)
+{
+    const long long b = (N + 1023) / 1024;
+    return b <= kDotBlocksFused ? (int)std::max<long long>(b, 1) : kDotBlocks;
 }
 
 static unsigned stream_blocks(long long N)
@@ -2249,12 +2331,13 @@ hipError_t launch_axpy_multi(long long N, int nv, const double *V, long long ldv
 
 template <int MODE>
 static hipError_t gs_pass(long long N, int nv, const double *V, long long ldv, const double *h,
-                          double *w, double *partial, hipStream_t st)
+                          double *w, double *partial, const GsTail &tail, hipStream_t st)
 {
+    const int nb = gs_blocks(N);
     switch (nv) {
 #define MSP_GS_CASE(K)                                                                    \
     case K:                                                                               \
-        k_gs_pass<K, MODE><<<kDotBlocks, kThreads, 0, st>>>(N, V, ldv, h, w, partial);    \
+        k_gs_pass<K, MODE><<<nb, kThreads, 0, st>>>(N, V, ldv, h, w, partial, tail);      \
         break;
         MSP_GS_CASE(1) MSP_GS_CASE(2) MSP_GS_CASE(3) MSP_GS_CASE(4) MSP_GS_CASE(5)
         MSP_GS_CASE(6) MSP_GS_CASE(7) MSP_GS_CASE(8) MSP_GS_CASE(9) MSP_GS_CASE(10)
@@ -2270,19 +2353,52 @@ static hipError_t gs_pass(long long N, int nv, const double *V, long long ldv, c
     return hipGetLastError();
 }
 
+// The pass's reduction runs in its last work-group, or in a launch of its own.
 hipError_t launch_gs_pass(int mode, long long N, int nv, const double *V, long long ldv,
-                          const double *h, double *w, double *partial, hipStream_t st)
+                          const double *h, double *w, double *partial, const GsTail &tail,
+                          hipStream_t st)
 {
     if (nv < 1 || nv > kFusedGsMax) return hipErrorInvalidValue;
-    if (mode == 0) return gs_pass<0>(N, nv, V, ldv, h, w, partial, st);
-    if (mode == 1) return gs_pass<1>(N, nv, V, ldv, h, w, partial, st);
-    if (mode == 2) return gs_pass<2>(N, nv, V, ldv, h, w, partial, st);
-    return hipErrorInvalidValue;
+    const bool fused = gs_blocks(N) <= kDotBlocksFused;
+    GsTail t = tail;
+    if (!fused) t.ctr = nullptr;
+    hipError_t e = hipErrorInvalidValue;
+    if (mode == 0) e = gs_pass<0>(N, nv, V, ldv, h, w, partial, t, st);
+    if (mode == 1) e = gs_pass<1>(N, nv, V, ldv, h, w, partial, t, st);
+    if (mode == 2) e = gs_pass<2>(N, nv, V, ldv, h, w, partial, t, st);
+    if (e != hipSuccess || fused) return e;
+    return launch_reduce_partials(mode == 2 ? 1 : nv, gs_blocks(N), partial, tail.out, tail.src,
+                                  tail.nhost, tail.host, st);
 }
 
-hipError_t launch_scale(long long N, const double *x, double s, double *y, hipStream_t st)
+hipError_t launch_norm2(long long N, const double *x, const double *first, double *partial,
+                        const GsTail &tail, hipStream_t st)
 {
-    k_scale<<<stream_blocks(N), kThreads, 0, st>>>(N, x, s, y);
+    const int nb = gs_blocks(N);
+    const bool fused = nb <= kDotBlocksFused;
+    GsTail t = tail;
+    if (!fused) t.ctr = nullptr;
+    k_norm2<<<nb, kThreads, 0, st>>>(N, x, first, partial, t);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess || fused) return e;
+    return launch_reduce_partials(first ? 2 : 1, nb, partial, tail.out, tail.src, tail.nhost,
+                                  tail.host, st);
+}
+
+__global__ void k_clear_i32(int *x)
+{
+    *x = 0;
+}
+hipError_t launch_clear_i32(int *x, hipStream_t st)
+{
+    k_clear_i32<<<1, 1, 0, st>>>(x);
+    return hipGetLastError();
+}
+
+hipError_t launch_scale(long long N, const double *x, const double *s2, double *y, ApplyIo *io,
+                        double *z, hipStream_t st)
+{
+    k_scale<<<stream_blocks(N), kThreads, 0, st>>>(N, x, s2, y, io, z);
     return hipGetLastError();
 }
 
