@@ -102,6 +102,11 @@ struct Level {
     int *natc_d = nullptr, *mptr_nat_d = nullptr, *mem_nat_d = nullptr;
     std::vector<int> natc_h, mptr_nat_h, mem_nat_h, mem_ptr_h;
     void *f = nullptr, *x = nullptr, *r = nullptr;  // work vectors in the precond precision
+    // entries of higher colors in coarse-row order (launch_restrict_upper), in
+    // the precond precision; null where the cycle forms the residual instead
+    int *ru_ptr = nullptr, *ru_col = nullptr;
+    void *ru_val = nullptr;
+    int ru_lanes = 8;
 };
 
 // N stage (concentration block, block Gauss-Seidel in the groups of the
@@ -122,6 +127,7 @@ struct BiluData {
     std::vector<int> fwd_rows, fwd_ptr, bwd_rows, bwd_ptr;
     std::vector<int> fwd_vpos, bwd_vpos;  // elimination position of each level-ordered row
     std::vector<char> fwd_live;           // forward level with at least one stored entry
+    bool turn = false;  // the last forward level is the first backward level reversed
     DevSell L, U;
     int *fwd_rows_d = nullptr, *bwd_rows_d = nullptr;
     int *pos_d = nullptr;  // elimination position of each block row: the solves' vector order
@@ -498,10 +504,18 @@ void prepare_link(msp_ctx *c, int l, std::vector<void *> &tmp)
     L.mem_nat_d = c->upload(mem, tmp);
 }
 
+// Coarse rows whose entry lists are longer than this on average take a
+// wavefront each in launch_restrict_upper, others 8 lanes: a level whose stalled
+// coarsening joined many rows per aggregate (21,099 -> 1,000 rows on the layered
+// 60x220x85 grid, 190 entries per coarse row) took 32 us with one thread per
+// coarse row and its members one after another.
+constexpr int kWideRestrict = 64;
+
 // Aggregation maps between level l and level l + 1 in position space (both
 // levels built, level l's link prepared): the member offsets by coarse
-// position on the host, the rest on the device.
-void link_level(msp_ctx *c, int l)
+// position on the host, the rest on the device; and the entries of the
+// restricted residual (csr: level l's matrix on the device).
+void link_level(msp_ctx *c, int l, const LevelCsr &csr, std::vector<void *> &tmp)
 {
     Level &L = c->lev[l];
     const Level &C = c->lev[l + 1];
@@ -514,6 +528,30 @@ void link_level(msp_ctx *c, int l)
     L.mem = (int *)c->dalloc(sizeof(int) * std::max(L.n, 1), c->allocB);
     HIPCHK(launch_link(L.n, C.n, L.natc_d, L.mptr_nat_d, L.mem_nat_d, C.perm_d, L.mem_ptr,
                        L.agg_pos, L.mem, c->copy_stream ? c->copy_stream : c->stream));
+    if (c->opt.smoother != 0 || c->opt.nu_pre != 1) return;
+    // one sweep from zero before the restriction: only entries of higher
+    // colors contribute (each pair of a symmetric pattern has one of them)
+    const hipStream_t st = c->copy_stream ? c->copy_stream : c->stream;
+    const long long off = L.A.nnz() - L.n, cap = c->pattern_sym ? off / 2 : off;
+    const size_t tsz = c->fp32() ? sizeof(float) : sizeof(double);
+    int *cnt = (int *)c->dalloc(sizeof(int) * (size_t)L.n, tmp);
+    int *pos = (int *)c->dalloc(sizeof(int) * (size_t)L.n, tmp);
+    int *tiles = (int *)c->dalloc(sizeof(int) * (scan_tiles(L.n) + 1), tmp);
+    int *total = tiles + scan_tiles(L.n);
+    L.ru_ptr = (int *)c->dalloc(sizeof(int) * (C.n + 1), c->allocB);
+    L.ru_col = (int *)c->dalloc(sizeof(int) * (size_t)std::max<long long>(cap, 1), c->allocB);
+    L.ru_val = c->dalloc(tsz * (size_t)std::max<long long>(cap, 1), c->allocB);
+    L.ru_lanes = cap > (long long)kWideRestrict * C.n ? 64 : 8;
+    HIPCHK(launch_ru_count(L.n, L.mem, L.perm_d, L.iperm_d, csr.rp, csr.ci, cnt, st));
+    HIPCHK(launch_tile_scan(cnt, pos, tiles, total, L.n, st));
+    if (c->fp32())
+        HIPCHK(launch_ru_fill<float>(L.n, C.n, L.mem_ptr, L.mem, L.perm_d, L.iperm_d, csr.rp,
+                                     csr.ci, csr.val, pos, tiles, kScanTile, total, L.ru_ptr,
+                                     L.ru_col, (float *)L.ru_val, st));
+    else
+        HIPCHK(launch_ru_fill<double>(L.n, C.n, L.mem_ptr, L.mem, L.perm_d, L.iperm_d, csr.rp,
+                                      csr.ci, csr.val, pos, tiles, kScanTile, total, L.ru_ptr,
+                                      L.ru_col, (double *)L.ru_val, st));
 }
 
 // Streams of the coarsest-level solver: the update stream and the stream of
@@ -721,12 +759,14 @@ std::future<void> launch_coarse(msp_ctx *c, const Csr &A, std::vector<void *> &t
     });
 }
 
-// x = A_L^-1 f on the coarsest level, in its positions.
+// x = A_L^-1 f on the coarsest level, in its positions; map != nullptr: entry
+// t goes to x[map[t]] (the positions of the natural-order solver are the
+// natural order itself).
 template <typename T>
-void coarse_solve(msp_ctx *c, const T *f, T *x)
+void coarse_solve(msp_ctx *c, const T *f, T *x, const int *map = nullptr)
 {
     if (c->nd.n > 0)
-        HIPCHK(launch_nd_solve<T>(c->nd, f, c->ct, x, c->stream));
+        HIPCHK(launch_nd_solve<T>(c->nd, f, c->ct, x, map, c->stream));
     else
         HIPCHK(launch_coarse_solve<T>(c->nL, c->ldL, kLuBlock, c->cY, c->cinv, f, c->ct, x,
                                       c->stream));
@@ -851,6 +891,9 @@ void bilu_plan(const msp_ctx *c, const std::vector<int> &color, int g, BiluData 
     for (int g2 = 0; g2 < D.L.nseg(); ++g2)
         for (int q = D.L.lay.seg_slice[g2]; q < D.L.lay.seg_slice[g2 + 1]; ++q)
             if (D.L.lay.slice_width[q] > 0) D.fwd_live[g2] = 1;
+    const int f0 = D.fwd_ptr[D.fwd_ptr.size() - 2], nt = n - f0;
+    D.turn = D.fwd_live.back() && D.bwd_ptr[1] == nt &&
+             std::equal(D.bwd_rows.begin(), D.bwd_rows.begin() + nt, D.fwd_rows.rbegin());
 }
 
 // Device part: factorise level by level and lay the factors out, on the side
@@ -1215,8 +1258,8 @@ void rebuild_B(msp_ctx *c, const double *vals, bool nd_ok = true)
             build_level_device(c, l, l == nlev - 1, &lays[l], csr[l]);
             if (l + 1 < nlev) prepare_link(c, l, tmp);
             built[l] = 1;
-            if (l > 0 && built[l - 1]) link_level(c, l - 1);
-            if (l + 1 < nlev && built[l + 1]) link_level(c, l);
+            if (l > 0 && built[l - 1]) link_level(c, l - 1, csr[l - 1], tmp);
+            if (l + 1 < nlev && built[l + 1]) link_level(c, l, csr[l], tmp);
             phase(4);
         };
         for (int left = nlev; left > 0;) {
@@ -1285,8 +1328,12 @@ const float *lev_diag<float>(const Level &L) { return L.diag32; }
 // point Jacobi is direction-free and uses L.r for its residual.
 // first_done: the first color of the first forward sweep from zero has
 // already been applied (by the restriction into this level).
+// Backward sweeps on a level of one lane per row: xc != nullptr, the first
+// color reads x prolongated (fold_prolong); nat != nullptr, the last sweep
+// writes x in natural order too.
 template <typename T>
-void smooth(msp_ctx *c, Level &L, bool forward, bool from_zero, int nu, bool first_done = false)
+void smooth(msp_ctx *c, Level &L, bool forward, bool from_zero, int nu, bool first_done = false,
+            const T *xc = nullptr, T *nat = nullptr)
 {
     T *f = (T *)L.f, *x = (T *)L.x;
     const T *val = lev_val<T>(L);
@@ -1320,38 +1367,78 @@ void smooth(msp_ctx *c, Level &L, bool forward, bool from_zero, int nu, bool fir
             for (int g = g0; g < L.g; ++g)
                 HIPCHK(launch_gs_color<T>(L.S.view(g), val, diag, f, x, c->stream));
         } else {
-            for (int g = L.g - 1; g >= 0; --g)
-                HIPCHK(launch_gs_color<T>(L.S.view(g), val, diag, f, x, c->stream));
+            for (int g = L.g - 1; g >= 0; --g) {
+                GsColorExtra<T> ex;
+                if (xc && s == 0 && g == L.g - 1) {
+                    ex.agg = L.agg_pos;
+                    ex.xc = xc;
+                }
+                if (nat && s == nu - 1) {
+                    ex.iperm = L.iperm_d;
+                    ex.nat = nat;
+                }
+                HIPCHK(launch_gs_color<T>(L.S.view(g), val, diag, f, x, c->stream, ex));
+            }
         }
     }
 }
 
-// first_done: level l's first pre-smoothing color is already applied.
+// On a two-color level (every 7-point level 0) the backward sweep overwrites
+// color 2 from the prolongated color 1, then color 1 from color 2: only color
+// 1's prolongated values are read, once, so the sweep forms them itself and
+// the prolongation needs no pass.
+bool fold_prolong(const msp_ctx *c, const Level &L)
+{
+    return c->opt.smoother == 0 && c->opt.nu_post > 0 && L.g == 2 && L.S.lanes == 1;
+}
+
+// True if the cycle's last sweep on level 0 can write its result in natural
+// order (or the coarsest solve can, if level 0 is the coarsest).
+bool natural_out(const msp_ctx *c)
+{
+    const Level &L = c->lev[0];
+    if (c->lev.size() == 1) return true;
+    return c->opt.smoother == 0 && c->opt.nu_post > 0 && L.S.lanes == 1;
+}
+
+// first_done: level l's first pre-smoothing color is already applied.  nat
+// (level 0, natural_out): the result in natural order.
 template <typename T>
-void vcycle(msp_ctx *c, int l, bool first_done = false)
+void vcycle(msp_ctx *c, int l, bool first_done = false, T *nat = nullptr)
 {
     Level &L = c->lev[l];
     if (l == (int)c->lev.size() - 1) {
-        coarse_solve<T>(c, (const T *)L.f, (T *)L.x);
+        if (nat)
+            coarse_solve<T>(c, (const T *)L.f, nat, L.iperm_d);
+        else
+            coarse_solve<T>(c, (const T *)L.f, (T *)L.x);
         return;
     }
     Level &C = c->lev[l + 1];
     smooth<T>(c, L, true, true, c->opt.nu_pre, first_done);
-    HIPCHK(launch_residual<T>(L.S.all(), lev_val<T>(L), lev_diag<T>(L), (const T *)L.f,
-                              (const T *)L.x, (T *)L.r, c->stream));
     // a smoothed coarse level whose pre-smoothing starts with a Gauss-Seidel
     // color from zero gets that color from the restriction itself
     const bool fuse = l + 1 < (int)c->lev.size() - 1 && c->opt.smoother == 0 &&
                       c->opt.nu_pre > 0 && C.g > 0;
-    if (fuse)
-        HIPCHK(launch_restrict_first<T>(C.n, L.mem_ptr, L.mem, (const T *)L.r, (T *)C.f,
-                                        C.seg_row[0], C.seg_row[1], lev_diag<T>(C), (T *)C.x,
-                                        c->stream));
-    else
-        HIPCHK(launch_restrict<T>(C.n, L.mem_ptr, L.mem, (const T *)L.r, (T *)C.f, c->stream));
+    const int p0 = fuse ? C.seg_row[0] : 0, p1 = fuse ? C.seg_row[1] : 0;
+    const T *dc = fuse ? lev_diag<T>(C) : nullptr;
+    T *xc = fuse ? (T *)C.x : nullptr;
+    if (L.ru_ptr) {
+        HIPCHK(launch_restrict_upper<T>(C.n, L.ru_lanes, L.ru_ptr, L.ru_col, (const T *)L.ru_val,
+                                        (const T *)L.x, (T *)C.f, p0, p1, dc, xc, c->stream));
+    } else {
+        HIPCHK(launch_residual<T>(L.S.all(), lev_val<T>(L), lev_diag<T>(L), (const T *)L.f,
+                                  (const T *)L.x, (T *)L.r, c->stream));
+        if (fuse)
+            HIPCHK(launch_restrict_first<T>(C.n, L.mem_ptr, L.mem, (const T *)L.r, (T *)C.f, p0,
+                                            p1, dc, xc, c->stream));
+        else
+            HIPCHK(launch_restrict<T>(C.n, L.mem_ptr, L.mem, (const T *)L.r, (T *)C.f, c->stream));
+    }
     vcycle<T>(c, l + 1, fuse);
-    HIPCHK(launch_prolong<T>(L.n, L.agg_pos, (const T *)C.x, (T *)L.x, c->stream));
-    smooth<T>(c, L, false, false, c->opt.nu_post);
+    const bool fold = fold_prolong(c, L);
+    if (!fold) HIPCHK(launch_prolong<T>(L.n, L.agg_pos, (const T *)C.x, (T *)L.x, c->stream));
+    smooth<T>(c, L, false, false, c->opt.nu_post, false, fold ? (const T *)C.x : nullptr, nat);
 }
 
 // The R stage in place on y: block ILU(0) triangular solves, or block Jacobi.
@@ -1370,10 +1457,15 @@ void bilu_solve(msp_ctx *c, T *y)
     } else {
         Lv = (const T *)D.L64; Uv = (const T *)D.U64; Dv = (const T *)D.D64;
     }
-    for (int s = 0; s < D.L.nseg(); ++s)
-        if (D.fwd_live[s])
-            HIPCHK(launch_bilu_fwd<T>(c->b, D.L.view(s), D.fwd_vpos_d, Lv, y, c->stream));
-    for (int s = 0; s < D.U.nseg(); ++s)
+    const int nf = D.L.nseg();
+    for (int s = 0; s < nf; ++s)
+        if (D.fwd_live[s]) {
+            const bool turn = D.turn && s == nf - 1;
+            HIPCHK(launch_bilu_fwd<T>(c->b, D.L.view(s), D.fwd_vpos_d, Lv, y, D.fwd_ptr[s],
+                                      D.fwd_ptr[s + 1] - D.fwd_ptr[s], turn ? Dv : nullptr,
+                                      c->stream));
+        }
+    for (int s = D.turn ? 1 : 0; s < D.U.nseg(); ++s)
         HIPCHK(launch_bilu_bwd<T>(c->b, D.U.view(s), D.bwd_vpos_d, Uv, Dv, y, c->stream));
 }
 
@@ -1408,10 +1500,18 @@ void apply_T(msp_ctx *c, const double *v_in, double *z, const ApplyIo *io = null
         HIPCHK(launch_spmv(c->b, c->SA.all(), c->valA, S.w1, v_in, S.r1, c->stream));
         v = S.r1;
     }
-    HIPCHK(launch_decouple_restrict<T>(c->b, c->n, L0.iperm_d, c->omega, v, io, (T *)L0.f,
-                                       c->stream));
-    vcycle<T>(c, 0);
-    HIPCHK(launch_unpermute<T>(c->n, L0.perm_d, (const T *)L0.x, (T *)c->e_nat, c->stream));
+    // a smoothed level 0 gets its first Gauss-Seidel color from zero here
+    const bool fuse = c->lev.size() > 1 && c->opt.smoother == 0 && c->opt.nu_pre > 0;
+    HIPCHK(launch_decouple_restrict<T>(
+        c->b, c->n, L0.iperm_d, c->omega, v, io, (T *)L0.f, fuse ? L0.seg_row[0] : 0,
+        fuse ? L0.seg_row[1] : 0, fuse ? lev_diag<T>(L0) : nullptr, fuse ? (T *)L0.x : nullptr,
+        c->stream));
+    if (natural_out(c)) {
+        vcycle<T>(c, 0, fuse, (T *)c->e_nat);
+    } else {
+        vcycle<T>(c, 0, fuse);
+        HIPCHK(launch_unpermute<T>(c->n, L0.perm_d, (const T *)L0.x, (T *)c->e_nat, c->stream));
+    }
     HIPCHK(launch_pcol_residual<T>(c->b, c->p, c->SA.all(), c->valA, c->pcol32, v, io,
                                    (const T *)c->e_nat, r_order(c), (T *)c->ybuf, c->stream));
     bilu_solve<T>(c, (T *)c->ybuf);

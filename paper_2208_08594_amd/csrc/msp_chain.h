@@ -56,6 +56,13 @@ using HipFail = void (*)(hipError_t);
 // filled from it.  A stalled level (the two passes keep more than 90% of its
 // rows) is finished on the host with absorb_singletons and galerkin, and its
 // coarse matrix uploaded.
+// Exclusive scan of in[0..n) in tiles of kScanTile entries: entry i's scan is
+// out[i] + tiles[i / kScanTile], *total the sum (tiles: scan_tiles(n) ints).
+constexpr int kScanTile = 1024;
+int scan_tiles(int n);
+hipError_t launch_tile_scan(const int *in, int *out, int *tiles, int *total, int n,
+                            hipStream_t st);
+
 // Bytes of the one device allocation the chain makes for a level 0 of n0
 // rows and nnz0 entries (freed with the setup's other temporaries).
 size_t device_chain_bytes(int n0, long long nnz0);

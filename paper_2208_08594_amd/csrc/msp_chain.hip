@@ -19,7 +19,7 @@ namespace msp {
 namespace {
 
 constexpr int kThreads = 256;
-constexpr int kScanTile = 1024;  // elements per block of the scan (4 per thread)
+static_assert(kScanTile == 4 * kThreads, "four elements per thread of a scan tile");
 // state word of a row in the matching: undecided, alone, taken by a lower
 // row, or ~j: it has taken row j
 constexpr int kFree = 0, kSingle = 1, kHigh = 2;
@@ -584,6 +584,18 @@ size_t place(Chain &X, char *base, int n0, long long nnz0)
 }
 
 }  // namespace
+
+int scan_tiles(int n)
+{
+    return (int)std::max<long long>(1, ((long long)n + kScanTile - 1) / kScanTile);
+}
+
+hipError_t launch_tile_scan(const int *in, int *out, int *tiles, int *total, int n, hipStream_t st)
+{
+    k_scan_tile<false><<<scan_tiles(n), kThreads, 0, st>>>(in, out, tiles, n);
+    k_scan_sums<<<1, kThreads, 0, st>>>(tiles, scan_tiles(n), total);
+    return hipGetLastError();
+}
 
 size_t device_chain_bytes(int n0, long long nnz0)
 {

@@ -98,13 +98,24 @@ struct ApplyIo {
 hipError_t launch_set_io(ApplyIo *io, const double *v, double *z, hipStream_t st);
 template <typename T>
 hipError_t launch_decouple_restrict(int b, int n, const int *iperm0, const double *omega,
-                                    const double *v, const ApplyIo *io, T *g, hipStream_t st);
+                                    const double *v, const ApplyIo *io, T *g, int p0, int p1,
+                                    const T *diag, T *x, hipStream_t st);
 template <typename T>
 hipError_t launch_gs_first(const SellView &seg0, int npos, const T *diag, const T *f, T *x,
                            int seg0_begin, int seg0_end, hipStream_t st);
+// What else a color's launch may do on a level of one lane per row: read the
+// other colors prolongated, x[j] + xc[agg[j]] (agg != nullptr), and write its
+// new x in natural order too (nat != nullptr, iperm: position -> row).
+template <typename T>
+struct GsColorExtra {
+    const int *agg = nullptr;
+    const T *xc = nullptr;
+    const int *iperm = nullptr;
+    T *nat = nullptr;
+};
 template <typename T>
 hipError_t launch_gs_color(const SellView &seg, const T *val, const T *diag, const T *f, T *x,
-                           hipStream_t st);
+                           hipStream_t st, const GsColorExtra<T> &ex = GsColorExtra<T>());
 template <typename T>
 hipError_t launch_residual(const SellView &all, const T *val, const T *diag, const T *f,
                            const T *x, T *r, hipStream_t st);
@@ -116,6 +127,23 @@ hipError_t launch_restrict(int nc, const int *mem_ptr, const int *mem, const T *
 template <typename T>
 hipError_t launch_restrict_first(int nc, const int *mem_ptr, const int *mem, const T *r, T *fc,
                                  int p0, int p1, const T *diag_c, T *xc, hipStream_t st);
+// fc = R (f - A x) after one forward Gauss-Seidel sweep from x = 0 (in exact
+// arithmetic), from the entries of higher colors in coarse-row order: ptr over
+// the nc coarse rows, col (fine positions), val.  lanes: 8 or 64 per row.
+// xc != nullptr: then the coarse level's first color as launch_restrict_first.
+template <typename T>
+hipError_t launch_restrict_upper(int nc, int lanes, const int *ptr, const int *col, const T *val,
+                                 const T *x, T *fc, int p0, int p1, const T *diag_c, T *xc,
+                                 hipStream_t st);
+// The entries themselves: counts per member slot, then (off, tile, total: the
+// tile scan of the counts) ptr, col and the values.
+hipError_t launch_ru_count(int n, const int *mem, const int *perm, const int *iperm, const int *rp,
+                           const int *ci, int *cnt, hipStream_t st);
+template <typename T>
+hipError_t launch_ru_fill(int n, int nc, const int *mem_ptr, const int *mem, const int *perm,
+                          const int *iperm, const int *rp, const int *ci, const double *val,
+                          const int *off, const int *tile, int tile_size, const int *total,
+                          int *ptr, int *col, T *out, hipStream_t st);
 template <typename T>
 hipError_t launch_prolong(int n, const int *agg_pos, const T *xc, T *x, hipStream_t st);
 // The restriction and prolongation maps of a level (n fine positions, nc
@@ -160,9 +188,12 @@ hipError_t launch_pcol_residual(int b, int p, const SellView &A, const double *v
 // The block ILU(0) solves of one dependency level, in place on y (z), a
 // block vector in elimination order: rows[r] is the elimination position of
 // the r-th row of the level order, the layouts' columns are positions too.
+// Dval != nullptr: the last forward level, whose nrows rows (from row0 of the
+// level order on) are the first backward level's in reverse and have no upper
+// entries: also z = D^-1 y with that level's pivot inverses.
 template <typename T>
 hipError_t launch_bilu_fwd(int b, const SellView &L, const int *rows, const T *Lval, T *y,
-                           hipStream_t st);
+                           int row0, int nrows, const T *Dval, hipStream_t st);
 template <typename T>
 hipError_t launch_bilu_bwd(int b, const SellView &U, const int *rows, const T *Uval,
                            const T *Dval, T *z, hipStream_t st);

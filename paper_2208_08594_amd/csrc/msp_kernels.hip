@@ -564,7 +564,9 @@ __global__ __launch_bounds__(kThreads) void k_decouple_restrict(int n,
                                                                 const double *__restrict__ omega,
                                                                 const double *v,
                                                                 const ApplyIo *io,
-                                                                T *__restrict__ g)
+                                                                T *__restrict__ g, int p0, int p1,
+                                                                const T *__restrict__ diag,
+                                                                T *__restrict__ x)
 {
     int t = blockIdx.x * kThreads + threadIdx.x;
     if (t >= n) return;
@@ -573,7 +575,10 @@ __global__ __launch_bounds__(kThreads) void k_decouple_restrict(int n,
     double acc = 0.0;
 #pragma unroll
     for (int k = 0; k < B; ++k) acc += omega[c * B + k] * v[c * B + k];
-    g[t] = (T)acc;
+    const T gt = (T)acc;
+    g[t] = gt;
+    // with x: also the first color of a forward sweep from x = 0 (k_gs_first)
+    if (x) x[t] = (t >= p0 && t < p1) ? gt / diag[t] : T(0);
 }
 
 template <typename T>
@@ -592,9 +597,11 @@ __global__ __launch_bounds__(kThreads) void k_gs_first(int npos, int p0, int p1,
 // entries go in batches of 8: the column and value loads of a batch issue
 // together, then its gathers of x, so a row costs two memory round trips per
 // batch instead of two per entry.
-template <typename T>
+// PRO: x[j] + xc[agg[j]] takes the place of x[j] (the prolongated vector).
+template <typename T, bool PRO = false>
 __device__ inline T sell_row_dot(const int *__restrict__ cb, const T *__restrict__ vb, int width,
-                                 const T *x, T sum0 = 0)
+                                 const T *x, T sum0 = 0, const int *__restrict__ agg = nullptr,
+                                 const T *__restrict__ xc = nullptr)
 {
     T sum = sum0;
     for (int k0 = 0; k0 < width; k0 += 8) {
@@ -608,6 +615,14 @@ __device__ inline T sell_row_dot(const int *__restrict__ cb, const T *__restrict
         }
 #pragma unroll
         for (int u = 0; u < 8; ++u) xv[u] = c[u] >= 0 ? x[c[u]] : T(0);
+        if (PRO) {
+            int a[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) a[u] = c[u] >= 0 ? agg[c[u]] : 0;
+#pragma unroll
+            for (int u = 0; u < 8; ++u)
+                if (c[u] >= 0) xv[u] += xc[a[u]];
+        }
 #pragma unroll
         for (int u = 0; u < 8; ++u)
             if (c[u] >= 0) sum += v[u] * xv[u];
@@ -615,12 +630,18 @@ __device__ inline T sell_row_dot(const int *__restrict__ cb, const T *__restrict
     return sum;
 }
 
-template <typename T>
+// PRO: the other colors' x is prolongated while it is read.  nat != nullptr:
+// the new x is also written in natural order (iperm: position -> row).
+template <typename T, bool PRO>
 __global__ __launch_bounds__(kThreads) void k_gs_color(const int4 *__restrict__ slices,
                                                        const int *__restrict__ col, int s0,
                                                        int s1, const T *__restrict__ val,
                                                        const T *__restrict__ diag,
-                                                       const T *__restrict__ f, T *x)
+                                                       const T *__restrict__ f, T *x,
+                                                       const int *__restrict__ agg,
+                                                       const T *__restrict__ xc,
+                                                       const int *__restrict__ iperm,
+                                                       T *__restrict__ nat)
 {
     const int s = s0 + xcd_block(blockIdx.x, gridDim.x) * 4 + (threadIdx.x >> 6);
     if (s >= s1) return;
@@ -629,8 +650,12 @@ __global__ __launch_bounds__(kThreads) void k_gs_color(const int4 *__restrict__ 
     if (lane >= d.y) return;
     const int row = d.x + lane;
     const T fr = f[row], dr = diag[row];
-    const T sum = sell_row_dot<T>(col + d.w + lane, val + d.w + lane, d.z, x);
-    x[row] = (fr - sum) / dr;
+    const int i = nat ? iperm[row] : 0;
+    const T sum =
+        sell_row_dot<T, PRO>(col + d.w + lane, val + d.w + lane, d.z, x, T(0), agg, xc);
+    const T xr = (fr - sum) / dr;
+    x[row] = xr;
+    if (nat) nat[i] = xr;
 }
 
 template <typename T>
@@ -789,6 +814,96 @@ __global__ __launch_bounds__(kThreads) void k_restrict_first(int nc, const int *
     xc[J] = (J >= p0 && J < p1) ? s / diag_c[J] : T(0);
 }
 
+// Restricted residual after one forward Gauss-Seidel sweep from x = 0: the
+// sweep solves every row against its lower colors, so the residual of row i is
+// -sum over its entries of higher colors of a_ij x_j, and f cancels.  One
+// product with those entries in the order of the coarse rows (ptr, col, val)
+// takes the place of the residual (all entries, f and the diagonal) and of the
+// restriction that reads it back: 60x220x85 cells layered, five levels, 70 + 66
+// us -> 48 us of kernel time per cycle.  L lanes per coarse row, entries j, j + L,
+// ... on lane j, summed across the lanes with a fixed butterfly.
+// xc != nullptr: also the first color [p0, p1) of the coarse level's sweep
+// from zero (as in k_restrict_first).
+template <typename T, int L>
+__global__ __launch_bounds__(kThreads) void k_restrict_upper(
+    int nc, const int *__restrict__ ptr, const int *__restrict__ col, const T *__restrict__ val,
+    const T *__restrict__ x, T *__restrict__ fc, int p0, int p1, const T *__restrict__ diag_c,
+    T *__restrict__ xc)
+{
+    const int J = (xcd_block(blockIdx.x, gridDim.x) * kThreads + threadIdx.x) / L;
+    const int j = threadIdx.x % L;
+    T s = 0;
+    if (J < nc) {
+        const int e = ptr[J + 1];
+        for (int k0 = ptr[J] + j; k0 < e; k0 += 4 * L) {
+            int c[4];
+            T v[4], xv[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const bool in = k0 + u * L < e;
+                c[u] = in ? __builtin_nontemporal_load(col + k0 + u * L) : -1;
+                v[u] = in ? __builtin_nontemporal_load(val + k0 + u * L) : T(0);
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u) xv[u] = c[u] >= 0 ? x[c[u]] : T(0);
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+                if (c[u] >= 0) s -= v[u] * xv[u];
+        }
+    }
+#pragma unroll
+    for (int o = 1; o < L; o <<= 1) s += __shfl_xor(s, o, 64);
+    if (J < nc && j == 0) {
+        fc[J] = s;
+        if (xc) xc[J] = (J >= p0 && J < p1) ? s / diag_c[J] : T(0);
+    }
+}
+
+// The entries of k_restrict_upper.  Member slot q (mem: fine positions, the
+// members of each coarse row in order) holds the row's entries of higher
+// positions, which are the higher colors: counted, then (off, tile: their
+// scan over the slots) written.  ptr[J] for the coarse rows.
+__global__ __launch_bounds__(kThreads) void k_ru_count(int n, const int *__restrict__ mem,
+                                                       const int *__restrict__ perm,
+                                                       const int *__restrict__ iperm,
+                                                       const int *__restrict__ rp,
+                                                       const int *__restrict__ ci,
+                                                       int *__restrict__ cnt)
+{
+    const int q = blockIdx.x * kThreads + threadIdx.x;
+    if (q >= n) return;
+    const int t = mem[q], i = iperm[t];
+    int m = 0;
+    for (int k = rp[i]; k < rp[i + 1]; ++k) m += perm[ci[k]] > t;
+    cnt[q] = m;
+}
+
+template <typename T>
+__global__ __launch_bounds__(kThreads) void k_ru_fill(
+    int n, int nc, const int *__restrict__ mem_ptr, const int *__restrict__ mem,
+    const int *__restrict__ perm, const int *__restrict__ iperm, const int *__restrict__ rp,
+    const int *__restrict__ ci, const double *__restrict__ val, const int *__restrict__ off,
+    const int *__restrict__ tile, int tile_size, const int *__restrict__ total,
+    int *__restrict__ ptr, int *__restrict__ col, T *__restrict__ out)
+{
+    const int q = blockIdx.x * kThreads + threadIdx.x;
+    if (q <= nc) {
+        const int a = mem_ptr[q];
+        ptr[q] = a < n ? off[a] + tile[a / tile_size] : *total;
+    }
+    if (q >= n) return;
+    const int t = mem[q], i = iperm[t];
+    int o = off[q] + tile[q / tile_size];
+    for (int k = rp[i]; k < rp[i + 1]; ++k) {
+        const int pj = perm[ci[k]];
+        if (pj > t) {
+            col[o] = pj;
+            out[o] = (T)val[k];
+            ++o;
+        }
+    }
+}
+
 template <typename T>
 __global__ __launch_bounds__(kThreads) void k_prolong(int n, const int *__restrict__ agg_pos,
                                                       const T *__restrict__ xc,
@@ -914,11 +1029,16 @@ __global__ __launch_bounds__(kThreads) void k_pcol_residual(
 // and column indices are read once per solve (non-temporal loads), padding
 // slots read the row's own block and add nothing, and slices are assigned to
 // XCDs in contiguous ranges.
-template <int B, typename T>
+// LAST: the last forward level, whose rows are the first backward level's (in
+// reverse) and have no upper entries: z_i = D_i^-1 y_i at once (Dval: the
+// backward level's blocks, nrows its rows), saving that level's launch and a
+// pass over its vector.
+template <int B, typename T, bool LAST>
 __global__ __launch_bounds__(kThreads) void k_bilu_fwd(const int4 *__restrict__ slices,
                                                        const int *__restrict__ col, int s0,
                                                        int s1, const int *__restrict__ rows,
-                                                       const T *__restrict__ Lval, T *y)
+                                                       const T *__restrict__ Lval, T *y, int row0,
+                                                       int nrows, const T *__restrict__ Dval)
 {
     constexpr int E = B * B;
     const int s = s0 + xcd_block(blockIdx.x, gridDim.x) * 4 + (threadIdx.x >> 6);
@@ -948,8 +1068,23 @@ __global__ __launch_bounds__(kThreads) void k_bilu_fwd(const int4 *__restrict__ 
             for (int u = 0; u < B; ++u)
                 acc[r] += __builtin_nontemporal_load(v + (r * B + u) * 64) * yk[u];
     }
+    if (!LAST) {
 #pragma unroll
-    for (int r = 0; r < B; ++r) y[i * B + r] = y[i * B + r] - acc[r];
+        for (int r = 0; r < B; ++r) y[i * B + r] = y[i * B + r] - acc[r];
+        return;
+    }
+    T t[B];
+#pragma unroll
+    for (int r = 0; r < B; ++r) t[r] = y[i * B + r] - acc[r];
+    const int q = nrows - 1 - (d.x + lane - row0);  // the row's place in the backward level
+    const T *D = Dval + (long long)(q >> 6) * 64 * E + (q & 63);
+#pragma unroll
+    for (int r = 0; r < B; ++r) {
+        T a = 0;
+#pragma unroll
+        for (int u = 0; u < B; ++u) a += __builtin_nontemporal_load(D + (r * B + u) * 64) * t[u];
+        y[i * B + r] = a;
+    }
 }
 
 template <int B, typename T>
@@ -1976,10 +2111,11 @@ hipError_t launch_set_io(ApplyIo *io, const double *v, double *z, hipStream_t st
 
 template <typename T>
 hipError_t launch_decouple_restrict(int b, int n, const int *iperm0, const double *omega,
-                                    const double *v, const ApplyIo *io, T *g, hipStream_t st)
+                                    const double *v, const ApplyIo *io, T *g, int p0, int p1,
+                                    const T *diag, T *x, hipStream_t st)
 {
     MSP_SWITCH_B(b, (k_decouple_restrict<B, T><<<blocks_for(n), kThreads, 0, st>>>(
-                        n, iperm0, omega, v, io, g)));
+                        n, iperm0, omega, v, io, g, p0, p1, diag, x)));
     return hipGetLastError();
 }
 
@@ -1993,7 +2129,7 @@ hipError_t launch_gs_first(const SellView &, int npos, const T *diag, const T *f
 
 template <typename T>
 hipError_t launch_gs_color(const SellView &seg, const T *val, const T *diag, const T *f, T *x,
-                           hipStream_t st)
+                           hipStream_t st, const GsColorExtra<T> &ex)
 {
     unsigned nb = slice_blocks(seg);
     if (!nb) return hipSuccess;
@@ -2002,8 +2138,14 @@ hipError_t launch_gs_color(const SellView &seg, const T *val, const T *diag, con
         k_gs_color_lanes<T, kRowLanes><<<(ns * kRowLanes + 3) / 4, kThreads, 0, st>>>(
             seg.slices, seg.col, seg.slice_begin, seg.slice_end, val, diag, f, x);
     } else {
-        k_gs_color<T><<<nb, kThreads, 0, st>>>(seg.slices, seg.col, seg.slice_begin,
-                                               seg.slice_end, val, diag, f, x);
+        if (ex.agg)
+            k_gs_color<T, true><<<nb, kThreads, 0, st>>>(seg.slices, seg.col, seg.slice_begin,
+                                                         seg.slice_end, val, diag, f, x, ex.agg,
+                                                         ex.xc, ex.iperm, ex.nat);
+        else
+            k_gs_color<T, false><<<nb, kThreads, 0, st>>>(seg.slices, seg.col, seg.slice_begin,
+                                                          seg.slice_end, val, diag, f, x, nullptr,
+                                                          nullptr, ex.iperm, ex.nat);
     }
     return hipGetLastError();
 }
@@ -2039,6 +2181,41 @@ hipError_t launch_restrict_first(int nc, const int *mem_ptr, const int *mem, con
 {
     k_restrict_first<T><<<blocks_for(nc), kThreads, 0, st>>>(nc, mem_ptr, mem, r, fc, p0, p1,
                                                               diag_c, xc);
+    return hipGetLastError();
+}
+
+template <typename T>
+hipError_t launch_restrict_upper(int nc, int lanes, const int *ptr, const int *col, const T *val,
+                                 const T *x, T *fc, int p0, int p1, const T *diag_c, T *xc,
+                                 hipStream_t st)
+{
+    if (nc <= 0) return hipSuccess;
+    const unsigned nb = blocks_for((long long)nc * lanes);
+    if (lanes == 64)
+        k_restrict_upper<T, 64><<<nb, kThreads, 0, st>>>(nc, ptr, col, val, x, fc, p0, p1, diag_c, xc);
+    else if (lanes == 8)
+        k_restrict_upper<T, 8><<<nb, kThreads, 0, st>>>(nc, ptr, col, val, x, fc, p0, p1, diag_c, xc);
+    else
+        return hipErrorInvalidValue;
+    return hipGetLastError();
+}
+
+hipError_t launch_ru_count(int n, const int *mem, const int *perm, const int *iperm, const int *rp,
+                           const int *ci, int *cnt, hipStream_t st)
+{
+    if (n <= 0) return hipSuccess;
+    k_ru_count<<<blocks_for(n), kThreads, 0, st>>>(n, mem, perm, iperm, rp, ci, cnt);
+    return hipGetLastError();
+}
+
+template <typename T>
+hipError_t launch_ru_fill(int n, int nc, const int *mem_ptr, const int *mem, const int *perm,
+                          const int *iperm, const int *rp, const int *ci, const double *val,
+                          const int *off, const int *tile, int tile_size, const int *total,
+                          int *ptr, int *col, T *out, hipStream_t st)
+{
+    k_ru_fill<T><<<blocks_for(std::max(n, nc + 1)), kThreads, 0, st>>>(
+        n, nc, mem_ptr, mem, perm, iperm, rp, ci, val, off, tile, tile_size, total, ptr, col, out);
     return hipGetLastError();
 }
 
@@ -2140,12 +2317,19 @@ hipError_t launch_pcol_residual(int b, int p, const SellView &A, const double *v
 
 template <typename T>
 hipError_t launch_bilu_fwd(int b, const SellView &L, const int *rows, const T *Lval, T *y,
-                           hipStream_t st)
+                           int row0, int nrows, const T *Dval, hipStream_t st)
 {
     unsigned nb = slice_blocks(L);
     if (!nb) return hipSuccess;
-    MSP_SWITCH_B(b, (k_bilu_fwd<B, T><<<nb, kThreads, 0, st>>>(L.slices, L.col, L.slice_begin,
-                                                               L.slice_end, rows, Lval, y)));
+    if (Dval) {
+        MSP_SWITCH_B(b, (k_bilu_fwd<B, T, true><<<nb, kThreads, 0, st>>>(
+                            L.slices, L.col, L.slice_begin, L.slice_end, rows, Lval, y, row0,
+                            nrows, Dval)));
+    } else {
+        MSP_SWITCH_B(b, (k_bilu_fwd<B, T, false><<<nb, kThreads, 0, st>>>(
+                            L.slices, L.col, L.slice_begin, L.slice_end, rows, Lval, y, 0, 0,
+                            nullptr)));
+    }
     return hipGetLastError();
 }
 
@@ -2252,12 +2436,19 @@ hipError_t launch_from_double(long long n, const double *x, T *y, hipStream_t st
 
 #define MSP_INSTANTIATE(T)                                                                     \
     template hipError_t launch_decouple_restrict<T>(int, int, const int *, const double *,     \
-                                                    const double *, const ApplyIo *, T *,      \
-                                                    hipStream_t);                              \
+                                                    const double *, const ApplyIo *, T *, int, \
+                                                    int, const T *, T *, hipStream_t);         \
     template hipError_t launch_gs_first<T>(const SellView &, int, const T *, const T *, T *,   \
                                            int, int, hipStream_t);                             \
     template hipError_t launch_gs_color<T>(const SellView &, const T *, const T *, const T *,  \
-                                           T *, hipStream_t);                                  \
+                                           T *, hipStream_t, const GsColorExtra<T> &);         \
+    template hipError_t launch_restrict_upper<T>(int, int, const int *, const int *, const T *, \
+                                                 const T *, T *, int, int, const T *, T *,     \
+                                                 hipStream_t);                                 \
+    template hipError_t launch_ru_fill<T>(int, int, const int *, const int *, const int *,     \
+                                          const int *, const int *, const int *,               \
+                                          const double *, const int *, const int *, int,       \
+                                          const int *, int *, int *, T *, hipStream_t);        \
     template hipError_t launch_residual<T>(const SellView &, const T *, const T *, const T *,  \
                                            const T *, T *, hipStream_t);                       \
     template hipError_t launch_restrict<T>(int, const int *, const int *, const T *, T *,      \
@@ -2277,7 +2468,7 @@ hipError_t launch_from_double(long long n, const double *x, T *y, hipStream_t st
                                                 const ApplyIo *, const T *, const int *, T *,  \
                                                 hipStream_t);                                  \
     template hipError_t launch_bilu_fwd<T>(int, const SellView &, const int *, const T *, T *, \
-                                           hipStream_t);                                       \
+                                           int, int, const T *, hipStream_t);                  \
     template hipError_t launch_bilu_bwd<T>(int, const SellView &, const int *, const T *,      \
                                            const T *, T *, hipStream_t);                       \
     template hipError_t launch_finish<T>(int, int, int, const T *, const int *, const T *,     \

@@ -456,7 +456,8 @@ __global__ __launch_bounds__(kThreads) void k_nd_upper(int n, const int4 *__rest
                                                        const int *__restrict__ cmap,
                                                        const double *__restrict__ W,
                                                        const double *__restrict__ t,
-                                                       T *__restrict__ x)
+                                                       T *__restrict__ x,
+                                                       const int *__restrict__ map)
 {
     const int row = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
     if (row >= n) return;
@@ -470,7 +471,7 @@ __global__ __launch_bounds__(kThreads) void k_nd_upper(int n, const int4 *__rest
         acc += v.x * t[cm[j]] + v.y * t[cm[j + 1]];
     }
     acc = nd_wave_sum(acc);
-    if (lane == 0) x[row] = (T)acc;
+    if (lane == 0) x[map ? map[row] : row] = (T)acc;
 }
 
 __global__ __launch_bounds__(kThreads) void k_nd_zero(long long n, double *__restrict__ x)
@@ -508,16 +509,17 @@ hipError_t launch_nd_factor(const NdPlan &P, const NdDev &d, hipStream_t st)
 }
 
 template <typename T>
-hipError_t launch_nd_solve(const NdSolve &s, const T *f, double *t, T *x, hipStream_t st)
+hipError_t launch_nd_solve(const NdSolve &s, const T *f, double *t, T *x, const int *map,
+                           hipStream_t st)
 {
     k_nd_lower<T><<<s.nlong + (s.n - s.nlong + 3) / 4, kThreads, 0, st>>>(s.n, s.nlong, s.yrow, s.Y,
                                                                          f, t);
-    k_nd_upper<T><<<(s.n + 3) / 4, kThreads, 0, st>>>(s.n, s.wrow, s.cmap, s.W, t, x);
+    k_nd_upper<T><<<(s.n + 3) / 4, kThreads, 0, st>>>(s.n, s.wrow, s.cmap, s.W, t, x, map);
     return hipGetLastError();
 }
 template hipError_t launch_nd_solve<float>(const NdSolve &, const float *, double *, float *,
-                                           hipStream_t);
+                                           const int *, hipStream_t);
 template hipError_t launch_nd_solve<double>(const NdSolve &, const double *, double *, double *,
-                                            hipStream_t);
+                                            const int *, hipStream_t);
 
 }  // namespace msp

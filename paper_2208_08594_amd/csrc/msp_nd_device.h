@@ -32,8 +32,10 @@ struct NdSolve {
     const int *cmap = nullptr;
     const double *W = nullptr, *Y = nullptr;
 };
-// x = A^-1 f = W (Y f), vectors in permuted order; t: FP64 work vector of n.
+// x = A^-1 f = W (Y f), vectors in permuted order (map != nullptr: entry r goes
+// to x[map[r]]); t: FP64 work vector of n.
 template <typename T>
-hipError_t launch_nd_solve(const NdSolve &s, const T *f, double *t, T *x, hipStream_t st);
+hipError_t launch_nd_solve(const NdSolve &s, const T *f, double *t, T *x, const int *map,
+                           hipStream_t st);
 
 }  // namespace msp
