@@ -633,9 +633,9 @@ void coarse_band(const Csr &A, std::vector<int> &rows_end, std::vector<int> &col
 // The nested-dissection solver of the coarsest level, queued on `stream`;
 // false (with nothing queued) if it does not serve this matrix: some row is
 // not strictly diagonally dominant (the natural-order solver pivots inside
-// its blocks), or its graph does not separate.  val_d: the matrix values on
-// the device if they are there already (level 0), else nullptr.
-bool launch_coarse_nd(msp_ctx *c, const Csr &A, bool level0, const double *val_d,
+// its blocks), or its graph does not separate.  dev: the matrix on the device
+// (null pointers: it is copied there).
+bool launch_coarse_nd(msp_ctx *c, const Csr &A, bool level0, LevelCsr dev,
                       std::vector<void *> &tmp)
 {
     const int m = A.n;
@@ -650,8 +650,8 @@ bool launch_coarse_nd(msp_ctx *c, const Csr &A, bool level0, const double *val_d
         }
         if (level0) c->nd_gen = c->pattern_gen;
     }
-    // one page-locked block [solve lists | factorisation lists | values], two
-    // device blocks: the first stays with the preconditioner
+    if (!dev.val) dev = LevelCsr{c->upload(A.rp, tmp), c->upload(A.ci, tmp), c->upload(A.val, tmp)};
+    // the plan's lists in one page-locked block and one copy
     struct Part {
         const void *src;
         size_t bytes, off;
@@ -663,14 +663,8 @@ bool launch_coarse_nd(msp_ctx *c, const Csr &A, bool level0, const double *val_d
         total += (part.back().bytes + 255) & ~(size_t)255;
         return part.back().off;
     };
-    const size_t o_yrow = add(P.yrow), o_wrow = add(P.wrow), o_cmap = add(P.cmap);
-    const size_t keep = total;
-    const size_t o_node = add(P.node), o_nodeof = add(P.nodeof), o_ep = add(P.ent_ptr),
-                 o_ent = add(P.ent), o_sp = add(P.self_ptr), o_self = add(P.self),
-                 o_rows = add(P.rows), o_first = add(P.first), o_prod = add(P.prod),
-                 o_inv = add(P.inv);
-    size_t o_val = 0;
-    if (!val_d) o_val = add(A.val);
+    const size_t o_iperm = add(P.iperm), o_node = add(P.node), o_rows = add(P.rows),
+                 o_first = add(P.first), o_prod = add(P.prod), o_inv = add(P.inv);
     if (c->nd_stage_bytes < total) {
         if (c->nd_stage) (void)hipHostFree(c->nd_stage);
         c->nd_stage = nullptr;
@@ -680,43 +674,63 @@ bool launch_coarse_nd(msp_ctx *c, const Csr &A, bool level0, const double *val_d
     }
     for (const Part &q : part)
         if (q.bytes) std::memcpy((char *)c->nd_stage + q.off, q.src, q.bytes);
-    char *kept = (char *)c->dalloc(keep, c->allocB);
-    char *work = (char *)c->dalloc(total - keep, tmp) - keep;
-    HIPCHK(hipMemcpyAsync(kept, c->nd_stage, keep, hipMemcpyHostToDevice, c->stream));
-    HIPCHK(hipMemcpyAsync(work + keep, (char *)c->nd_stage + keep, total - keep,
-                          hipMemcpyHostToDevice, c->stream));
-    auto dbl = [&](size_t k, std::vector<void *> &list) {
-        return (double *)c->dalloc(sizeof(double) * std::max<size_t>(k, 2), list);
+    char *lists = (char *)c->dalloc(total, c->allocB);
+    HIPCHK(hipMemcpyAsync(lists, c->nd_stage, total, hipMemcpyHostToDevice, c->stream));
+    // the arrays in two blocks: kept with the preconditioner, and for the setup
+    struct Want {
+        void **p;
+        size_t bytes;
+    };
+    std::vector<Want> keep, work;
+    auto arr = [&](auto *&p, size_t k, std::vector<Want> &list) {
+        list.push_back({(void **)&p, (sizeof(*p) * std::max<size_t>(k, 2) + 255) & ~(size_t)255});
+    };
+    auto place = [&](const std::vector<Want> &list, std::vector<void *> &owner) {
+        size_t all = 0;
+        for (const Want &w : list) all += w.bytes;
+        char *base = (char *)c->dalloc(all, owner);
+        for (const Want &w : list) {
+            *w.p = base;
+            base += w.bytes;
+        }
     };
     NdDev d;
-    d.node = (const NdNode *)(work + o_node);
-    d.nodeof = (const int *)(work + o_nodeof);
-    d.cmap = (const int *)(kept + o_cmap);
-    d.ent_ptr = (const int *)(work + o_ep);
-    d.ent = (const int4 *)(work + o_ent);
-    d.self_ptr = (const int *)(work + o_sp);
-    d.self = (const int2 *)(work + o_self);
-    d.rows = (const int *)(work + o_rows);
-    d.first = (const int *)(work + o_first);
-    d.prod = (const int4 *)(work + o_prod);
-    d.inv = (const int4 *)(work + o_inv);
-    d.val = val_d ? val_d : (const double *)(work + o_val);
-    d.W = dbl(P.wtot, c->allocB);
-    d.Y = dbl(P.qtot, c->allocB);
-    d.Yt = dbl(P.wtot, tmp);
-    d.L = dbl(P.qtot, tmp);
-    d.Ut = dbl(P.qtot, tmp);
-    d.X = dbl(P.xtot, tmp);
-    d.S0 = dbl(P.stot, tmp);
-    d.S1 = dbl(P.stot, tmp);
-    d.Dk = dbl(P.node.size() * 2 * kNdTile * kNdTile, tmp);
+    d.iperm = (const int *)(lists + o_iperm);
+    d.node = (const NdNode *)(lists + o_node);
+    d.rows = (const int *)(lists + o_rows);
+    d.first = (const int *)(lists + o_first);
+    d.prod = (const int4 *)(lists + o_prod);
+    d.inv = (const int4 *)(lists + o_inv);
+    d.rp = dev.rp;
+    d.ci = dev.ci;
+    d.val = dev.val;
+    const size_t nnz = (size_t)A.nnz();
+    arr(d.cmap, P.cmap_len, keep);
+    arr(d.yrow, m, keep);
+    arr(d.wrow, m, keep);
+    arr(d.W, P.wtot, keep);
+    arr(d.Y, P.qtot, keep);
+    arr(c->ct, m, keep);
+    place(keep, c->allocB);
+    arr(d.perm, m, work);
+    arr(d.nodeof, m, work);
+    arr(d.ent, nnz, work);
+    arr(d.self, nnz, work);
+    arr(d.ecnt, m, work);
+    arr(d.Yt, P.wtot, work);
+    arr(d.L, P.qtot, work);
+    arr(d.Ut, P.qtot, work);
+    arr(d.X, P.xtot, work);
+    arr(d.S0, P.stot, work);
+    arr(d.S1, P.stot, work);
+    arr(d.Dk, P.node.size() * 2 * kNdTile * kNdTile, work);
+    place(work, tmp);
     c->nL = m;
     c->ldL = (m + 15) & ~15;
-    c->ct = (double *)c->dalloc(sizeof(double) * (size_t)m, c->allocB);
     c->nd.n = m;
     c->nd.nlong = P.nlong;
-    c->nd.yrow = (const int4 *)(kept + o_yrow);
-    c->nd.wrow = (const int4 *)(kept + o_wrow);
+    c->nd.yrow = d.yrow;
+    c->nd.wrow = d.wrow;
     c->nd.cmap = d.cmap;
     c->nd.W = d.W;
     c->nd.Y = d.Y;
@@ -1165,15 +1179,18 @@ void rebuild_B(msp_ctx *c, const double *vals, bool nd_ok = true)
     };
     // the chain on the device (structurally symmetric patterns), else on the host
     int st = 1;
+    LevelCsr last;  // the coarsest level on the device, if the chain ran there
     if (c->opt.host_chain == 0) {
         device_levels = true;  // no level callback runs if the chain declines (st == 1)
         st = device_hierarchy(
             A0, c->rp_d, c->ci_d, ap, c->opt.max_coarse, MSP_MAX_LEVELS, 16384, H, start_level,
             [&a0_ready]() { a0_ready.get(); }, c->stream, c->chain_copy,
             [c, &tmp](size_t bytes) { return c->dalloc(bytes, tmp); }, fail_hip, c->chain_host,
-            [c](int l, size_t bytes) { return chain_staging(c, l, bytes); });
+            [c](int l, size_t bytes) { return chain_staging(c, l, bytes); }, &last.rp, &last.ci,
+            &last.val);
     }
     if (st == 1) {
+        last = LevelCsr();
         device_levels = false;
         a0_ready.get();
         st = build_hierarchy(std::move(A0), c->opt.max_coarse, MSP_MAX_LEVELS, 16384, H, false,
@@ -1183,7 +1200,8 @@ void rebuild_B(msp_ctx *c, const double *vals, bool nd_ok = true)
     if (st == -9) fail(MSP_ERR_COARSE);
     const int nlev = (int)H.A.size();
     std::future<void> coarse_queued;
-    if (!(nd_ok && launch_coarse_nd(c, H.A.back(), nlev == 1, nlev == 1 ? ap : nullptr, tmp)))
+    if (nlev == 1) last = LevelCsr{c->rp_d, c->ci_d, ap};
+    if (!(nd_ok && launch_coarse_nd(c, H.A.back(), nlev == 1, last, tmp)))
         coarse_queued = launch_coarse(c, H.A.back(), tmp);
     // zero diagonals on the smoothed levels (the device chain leaves this
     // test to here, behind the coarsest inverse already queued)

@@ -55,7 +55,8 @@ using HipFail = void (*)(hipError_t);
 // level's host work starts before the copy into H.A is done), and H.A is
 // filled from it.  A stalled level (the two passes keep more than 90% of its
 // rows) is finished on the host with absorb_singletons and galerkin, and its
-// coarse matrix uploaded.
+// coarse matrix uploaded.  last_rp, last_ci, last_val (if given) receive the
+// coarsest level on the device (in the chain's own memory, or level 0 itself).
 // Exclusive scan of in[0..n) in tiles of kScanTile entries: entry i's scan is
 // out[i] + tiles[i / kScanTile], *total the sum (tiles: scan_tiles(n) ints).
 constexpr int kScanTile = 1024;
@@ -72,6 +73,7 @@ int device_hierarchy(Csr &A0, const int *rp0, const int *ci0, const double *val0
                      const LevelCallback &on_smoothed, const std::function<void()> &level0_values,
                      hipStream_t st, hipStream_t copy_st,
                      const DeviceAlloc &alloc, HipFail hip_fail, int *pinned,
-                     const PinnedBuffer &staging = nullptr);
+                     const PinnedBuffer &staging = nullptr, const int **last_rp = nullptr,
+                     const int **last_ci = nullptr, const double **last_val = nullptr);
 
 }  // namespace msp

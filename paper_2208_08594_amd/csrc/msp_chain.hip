@@ -608,14 +608,21 @@ int device_hierarchy(Csr &A0, const int *rp0, const int *ci0, const double *val0
                      const LevelCallback &on_smoothed, const std::function<void()> &level0_values,
                      hipStream_t st, hipStream_t copy_st,
                      const DeviceAlloc &alloc, HipFail hip_fail, int *pinned,
-                     const PinnedBuffer &staging)
+                     const PinnedBuffer &staging, const int **last_rp, const int **last_ci,
+                     const double **last_val)
 {
+    const auto report = [&](const int *rp, const int *ci, const double *val) {
+        if (last_rp) *last_rp = rp;
+        if (last_ci) *last_ci = ci;
+        if (last_val) *last_val = val;
+    };
     const int n0 = A0.n;
     const long long nnz0 = A0.nnz();
     if (n0 <= max_coarse || max_levels <= 1) {
         H = Hierarchy();
         H.A.push_back(std::move(A0));
         level0_values();  // level 0 is the coarsest: the caller inverts it next
+        report(rp0, ci0, val0);
         return H.A.back().n > max_dense ? -9 : 0;
     }
     Chain X;
@@ -785,6 +792,7 @@ int device_hierarchy(Csr &A0, const int *rp0, const int *ci0, const double *val0
         next = 3 - next;
     }
     join();
+    report(cur.rp, cur.ci, cur.val);
     return H.A.back().n > max_dense ? -9 : 0;
 }
 

@@ -819,9 +819,9 @@ __global__ __launch_bounds__(kThreads) void k_restrict_first(int nc, const int *
 // -sum over its entries of higher colors of a_ij x_j, and f cancels.  One
 // product with those entries in the order of the coarse rows (ptr, col, val)
 // takes the place of the residual (all entries, f and the diagonal) and of the
-// restriction that reads it back: 60x220x85 cells layered, five levels, 70 + 66
-// us -> 48 us of kernel time per cycle.  L lanes per coarse row, entries j, j + L,
-// ... on lane j, summed across the lanes with a fixed butterfly.
+// restriction that reads it back: 60x220x85 cells layered, five levels, 80.7 +
+// 62.4 us -> 64.9 us of kernel time per cycle.  L lanes per coarse row, entries
+// j, j + L, ... on lane j, summed across the lanes with a fixed butterfly.
 // xc != nullptr: also the first color [p0, p1) of the coarse level's sweep
 // from zero (as in k_restrict_first).
 template <typename T, int L>

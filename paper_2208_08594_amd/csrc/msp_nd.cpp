@@ -20,7 +20,7 @@ struct Tree {
 using Forest = std::vector<std::unique_ptr<Tree>>;
 
 constexpr int kSep = -1;          // mark of a separator vertex (never part of a set again)
-constexpr int kParallelSet = 1500;  // halves of at least this many vertices get a thread
+constexpr int kParallelSet = 700;  // halves of at least this many vertices get a thread
 
 struct Cutter {
     const int *rp, *ci;
@@ -205,19 +205,15 @@ int place(const Tree &t, NdPlan &P, std::vector<int> &height)
 
 void NdPlan::clear()
 {
-    n = heights = nlong = 0;
+    n = heights = nlong = cmap_len = 0;
     wtot = qtot = xtot = stot = 0;
-    for (std::vector<int> *v : {&perm, &iperm, &nodeof, &cmap, &ent_ptr, &self_ptr, &rows, &rows_ptr,
-                                &prod_ptr, &inv_ptr, &first, &first_ptr, &mirror})
+    for (std::vector<int> *v :
+         {&perm, &iperm, &rows, &rows_ptr, &prod_ptr, &inv_ptr, &first, &first_ptr})
         v->clear();
     node.clear();
-    ent.clear();
-    self.clear();
     prod.clear();
     inv.clear();
     inv_n.clear();
-    yrow.clear();
-    wrow.clear();
 }
 
 bool nd_dominant(int n, const int *rp, const int *ci, const double *val)
@@ -240,22 +236,17 @@ bool nd_plan(int n, const int *rp, const int *ci, NdPlan &P)
     P.clear();
     P.n = n;
     if (n < 1 || n > 32767) return false;
-    // mirror entry of every entry: with sorted rows, the lower entries of row j
-    // come up in order as the rows above it are walked.  A pattern that is
-    // not symmetric, or lacks a diagonal, declines.
-    std::vector<int> &mirror = P.mirror;
-    mirror.resize((size_t)rp[n]);
+    // with sorted rows, the lower entries of row j come up in order as the rows
+    // above it are walked: a pattern that is not symmetric, or lacks a
+    // diagonal, declines
     {
         std::vector<int> cur(rp, rp + n);
         for (int i = 0; i < n; ++i) {
             int k = cur[i];
             if (k >= rp[i + 1] || ci[k] != i) return false;  // its lower entries all matched
-            mirror[k] = k;
             for (++k; k < rp[i + 1]; ++k) {
                 const int j = ci[k], m = cur[j]++;
                 if (m >= rp[j + 1] || ci[m] != i) return false;
-                mirror[k] = m;
-                mirror[m] = k;
             }
         }
     }
@@ -266,40 +257,20 @@ bool nd_plan(int n, const int *rp, const int *ci, NdPlan &P)
     P.iperm.reserve(n);
     for (const auto &t : forest) place(*t, P, height);
     P.perm.resize(n);
-    P.nodeof.resize(n);
     for (int t = 0; t < n; ++t) P.perm[P.iperm[t]] = t;
     const int nn = (int)P.node.size();
     for (int v = 0; v < nn; ++v) {
         NdNode &q = P.node[v];
         if (q.m > kNdMaxNode) return false;
-        for (int r = q.s; r < q.s + q.m; ++r) P.nodeof[r] = v;
         P.heights = std::max(P.heights, height[v] + 1);
     }
     // chains and offsets (ancestors first: they come later in postorder)
-    std::vector<int> depth(nn, 0);
-    std::vector<int> clen(nn, 0);
     for (int v = nn - 1; v >= 0; --v) {
         NdNode &q = P.node[v];
-        depth[v] = q.parent < 0 ? 0 : depth[q.parent] + 1;
-        clen[v] = q.m + (q.parent < 0 ? 0 : clen[q.parent]);
-        q.c = (clen[v] + 1) & ~1;
-    }
-    // (a parent's chain is written before its children's, which copy it)
-    {
-        size_t total = 0;
-        for (int v = nn - 1; v >= 0; --v) {
-            P.node[v].cbase = (int)total;
-            total += P.node[v].c;
-        }
-        P.cmap.resize(total);
-    }
-    for (int v = nn - 1; v >= 0; --v) {
-        const NdNode &q = P.node[v];
-        int *o = P.cmap.data() + q.cbase;
-        for (int r = 0; r < q.m; ++r) o[r] = q.s + r;
-        if (q.parent >= 0)
-            std::copy_n(P.cmap.data() + P.node[q.parent].cbase, clen[q.parent], o + q.m);
-        if (clen[v] & 1) o[clen[v]] = q.s;  // padding: its stored value is zero
+        q.len = q.m + (q.parent < 0 ? 0 : P.node[q.parent].len);
+        q.c = (q.len + 1) & ~1;
+        q.cbase = P.cmap_len;
+        P.cmap_len += q.c;
     }
     for (int v = 0; v < nn; ++v) {
         NdNode &q = P.node[v];
@@ -319,33 +290,6 @@ bool nd_plan(int n, const int *rp, const int *ci, NdPlan &P)
     const size_t need = 2 * P.wtot + 3 * P.qtot + P.xtot + 2 * P.stot;
     if (need > 2 * (size_t)n * n + ((size_t)1 << 16)) return false;
     if (P.wtot >= ((size_t)1 << 31) || P.qtot >= ((size_t)1 << 31)) return false;
-    // chain entries of node v below its ancestor a
-    auto below = [&](int v, int a) { return clen[v] - clen[a]; };
-    // entry lists
-    P.ent_ptr.resize(n + 1);
-    P.self_ptr.resize(n + 1);
-    P.ent.resize(rp[n] / 2 + 1);  // each pair of mirror entries is listed once at most
-    P.self.resize(rp[n]);
-    int ne = 0, ns = 0;
-    P.ent_ptr[0] = P.self_ptr[0] = 0;
-    for (int a = 0; a < nn; ++a) {
-        const NdNode &q = P.node[a];
-        for (int t = q.s; t < q.s + q.m; ++t) {
-            const int i = P.iperm[t];
-            for (int k = rp[i]; k < rp[i + 1]; ++k) {
-                const int r = P.perm[ci[k]];
-                if (r >= q.s + q.m) continue;  // an ancestor's row, which lists the pair
-                if (r >= q.s)
-                    P.self[ns++] = {r - q.s, k};
-                else
-                    P.ent[ne++] = {r, below(P.nodeof[r], a), k, mirror[k]};
-            }
-            P.ent_ptr[t + 1] = ne;
-            P.self_ptr[t + 1] = ns;
-        }
-    }
-    P.ent.resize(ne);
-    P.self.resize(ns);
     // tasks by height
     std::vector<std::vector<int>> at(P.heights);
     for (int v = 0; v < nn; ++v) at[height[v]].push_back(v);
@@ -371,7 +315,7 @@ bool nd_plan(int n, const int *rp, const int *ci, NdPlan &P)
             for (int v = firstnode[a]; v < a; ++v)
                 for (int i = 0; i < P.node[v].m; i += kNdTile)
                     for (int j = 0; j < q.m; j += kNdTile)
-                        P.prod.push_back({v, a, i << 16 | j, below(v, a)});
+                        P.prod.push_back({v, a, i << 16 | j, P.node[v].len - q.len});
             for (int i = 0; i < q.mp; i += kNdTile)
                 for (int j = 0; j < q.mp; j += kNdTile) P.inv.push_back({a, a, i << 16 | j, 0});
         }
@@ -388,9 +332,7 @@ bool nd_plan(int n, const int *rp, const int *ci, NdPlan &P)
         P.inv_ptr.push_back((int)P.inv.size());
         P.first_ptr.push_back((int)P.first.size());
     }
-    // solve lists
-    P.yrow.resize(n);
-    P.wrow.resize(n);
+    // the solve's order: rows by falling length of their part of Y
     std::vector<int> byl(nn);
     std::iota(byl.begin(), byl.end(), 0);
     std::stable_sort(byl.begin(), byl.end(), [&](int x, int y) {
@@ -398,11 +340,9 @@ bool nd_plan(int n, const int *rp, const int *ci, NdPlan &P)
     });
     int o = 0;
     for (int v : byl) {
-        const NdNode &q = P.node[v];
-        for (int r = 0; r < q.m; ++r) {
-            P.yrow[o++] = {q.s + r, q.f, q.s - q.f, (int)(q.qbase + (long long)r * q.qld)};
-            P.wrow[q.s + r] = {(int)(q.wbase + (long long)r * q.c), q.c, q.cbase, 0};
-        }
+        NdNode &q = P.node[v];
+        q.yord = o;
+        o += q.m;
         if (q.s - q.f >= kNdLongRow) P.nlong = o;
     }
     return true;

@@ -23,7 +23,12 @@
 // now): setup 19.8 -> 10.9 ms, FGMRES solve 4.5 -> 3.2 ms; eight 20^3 systems
 // (8,000 coarsest rows each) solved together 44.9 -> 8.4 ms (the natural
 // order's compute-unit masked streams, one hardware queue each, are no longer
-// created).
+// created).  Only the tree and the task lists are made on the host: the lists
+// per row and per entry (2.5 MB there) follow from them on the device, and the
+// matrix is taken where the aggregation chain left it.  With that, gathered
+// rows and a shorter pivot chain the Newton step on these cells went from 12.0
+// to 10.7 ms, and on 24x24x24 cells, b = 5 (3,662 coarsest rows) from 4.4 to
+// 3.9 ms.
 #pragma once
 
 #include <cstddef>
@@ -39,60 +44,40 @@ constexpr double kNdMargin = 1e-5;
 
 // Node of the tree as the kernels see it.  Rows [s, s + m) in permuted order;
 // its descendants are the rows [f, s).  chain = the node's own rows and all
-// its ancestors' rows, lowest first (c of them, rounded up to even); a row of
-// W (and of Y^T while Y is computed) is stored as its c chain entries at
-// wbase + (row - s) c, their columns at cmap + cbase.
+// its ancestors' rows, lowest first (len of them; c: len rounded up to even);
+// a row of W (and of Y^T while Y is computed) is stored as its c chain entries
+// at wbase + (row - s) c, their columns at cmap + cbase.  Chain entries of the
+// node below its ancestor a: len - a.len.
 struct NdNode {
     int s, m, f, c;
-    int cbase, qld, mp, parent;  // qld: s - f rounded up to even; mp: m rounded up to tiles
-    long long wbase;             // packed rows of W and of Y^T
-    long long qbase;             // m x qld: the node's rows of Y (and of L and U^T)
-    long long xbase;             // (s - f) x m: A_SS^-1 A(S, node), S the descendants
-    long long sbase;             // mp x mp: the node's Schur complement / its inverse
+    int len, cbase, qld, mp;  // qld: s - f rounded up to even; mp: m rounded up to tiles
+    int parent, yord;         // yord: place of the node's rows among the rows by length of Y
+    long long wbase;          // packed rows of W and of Y^T
+    long long qbase;          // m x qld: the node's rows of Y (and of L and U^T)
+    long long xbase;          // (s - f) x m: A_SS^-1 A(S, node), S the descendants
+    long long sbase;          // mp x mp: the node's Schur complement / its inverse
 };
 
-// Everything that depends on the pattern only (device arrays are copies of
-// these): order, tree, entry lists and the task lists of each height.
+// What depends on the pattern only (device arrays are copies of these): order,
+// tree and the task lists of each height.
 struct NdPlan {
     int n = 0, heights = 0;
     std::vector<int> perm, iperm;  // natural -> permuted, permuted -> natural
     std::vector<NdNode> node;      // postorder: descendants before their ancestors
-    std::vector<int> nodeof;       // node of a permuted row
-    std::vector<int> cmap;
-    // stored entries of a permuted row towards descendants of its node:
-    // {permuted column, chain entries of that row below this node, CSR index
-    // of (row, column), CSR index of (column, row)}
-    struct Ent {
-        int row, prefix, src, srcT;
-    };
-    std::vector<int> ent_ptr;
-    std::vector<Ent> ent;
-    // stored entries inside the node: {column relative to the node, CSR index}
-    struct Self {
-        int col, src;
-    };
-    std::vector<int> self_ptr;
-    std::vector<Self> self;
     // task lists; height h takes [ptr[h], ptr[h+1])
     struct Tile {
         int v, a, ij, k;  // nodes, tile origin (i << 16 | j), chain entries of v below a
     };
-    std::vector<int> rows, rows_ptr;      // rows of the nodes (heights >= 1)
+    std::vector<int> rows, rows_ptr;      // rows of the nodes
     std::vector<Tile> prod;               // tiles of the descendants' rows x node columns
     std::vector<int> prod_ptr;
     std::vector<Tile> inv;                // tiles of the node inverses, largest nodes first
     std::vector<int> inv_ptr;
     std::vector<int> first, first_ptr;    // nodes, largest first
     std::vector<std::vector<int>> inv_n;  // per height and block step: tiles that take part
-    // solve: rows by falling length of their Y part, {row, f, length, offset};
-    // per row of W {offset, c, cbase, 0}
-    struct Row {
-        int a, b, c, d;
-    };
-    std::vector<Row> yrow, wrow;
     int nlong = 0;                        // rows with at least kNdLongRow entries of Y
+    int cmap_len = 0;
     size_t wtot = 0, qtot = 0, xtot = 0, stot = 0;  // doubles
-    std::vector<int> mirror;              // scratch of nd_plan
     // Empties the lists and keeps their storage for the next plan.
     void clear();
 };

@@ -3,6 +3,8 @@
 // launch, FP64 matrix cores for the dense products and the node inverses.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+
 #include "msp_nd_device.h"
 
 namespace msp {
@@ -15,53 +17,149 @@ constexpr int kKC = 16;  // k-chunk of the node products
 typedef double dbl4 __attribute__((ext_vector_type(4)));
 
 // ---------------------------------------------------------------------------
-// rows of L(a, S) and U(S, a)^T of the nodes a of one height, S the
-// descendants of a: L(a, S) = A(a, S) W(S, S), U(S, a) = Y(S, S) A(S, a).
-// Each stored entry adds a multiple of one packed row of W (of Y^T), whose
-// columns below a are distinct.  One work-group per row and side.
+// lists that follow from the tree: per node, its rows' node numbers, the
+// columns of its chain and the solve's row descriptors (one work-group a node)
 // ---------------------------------------------------------------------------
+__global__ __launch_bounds__(kThreads) void k_nd_nodes(NdDev d)
+{
+    const int v = blockIdx.x;
+    const NdNode q = d.node[v];
+    for (int r = threadIdx.x; r < q.m; r += kThreads) {
+        const int row = q.s + r;
+        d.nodeof[row] = v;
+        d.perm[d.iperm[row]] = row;
+        d.yrow[q.yord + r] = make_int4(row, q.f, q.s - q.f, (int)(q.qbase + (long long)r * q.qld));
+        d.wrow[row] = make_int4((int)(q.wbase + (long long)r * q.c), q.c, q.cbase, 0);
+    }
+    int o = 0;
+    for (int a = v; a >= 0;) {
+        const NdNode p = d.node[a];
+        for (int r = threadIdx.x; r < p.m; r += kThreads) d.cmap[q.cbase + o + r] = p.s + r;
+        o += p.m;
+        a = p.parent;
+    }
+    if (threadIdx.x == 0 && q.c > q.len) d.cmap[q.cbase + q.len] = q.s;  // padding, value zero
+}
+
+// the entry lists of every row (one thread a row; rows are short and sorted)
+__global__ __launch_bounds__(kThreads) void k_nd_entries(int n, NdDev d)
+{
+    const int t = blockIdx.x * kThreads + threadIdx.x;
+    if (t >= n) return;
+    const int i = d.iperm[t], b0 = d.rp[i], b1 = d.rp[i + 1];
+    const NdNode q = d.node[d.nodeof[t]];
+    int ne = 0, ns = 0;
+    for (int k = b0; k < b1; ++k) {
+        const int j = d.ci[k], r = d.perm[j];
+        if (r >= q.s + q.m) continue;  // an ancestor's row, which lists the pair
+        if (r >= q.s) {
+            d.self[b1 - ++ns] = make_int2(r - q.s, k);
+            continue;
+        }
+        int lo = d.rp[j], hi = d.rp[j + 1];  // the mirror entry (the pattern is symmetric)
+        while (lo < hi) {
+            const int mid = (lo + hi) >> 1;
+            if (d.ci[mid] < i)
+                lo = mid + 1;
+            else
+                hi = mid;
+        }
+        d.ent[b0 + ne++] = make_int4(r, d.node[d.nodeof[r]].len - q.len, k, lo);
+    }
+    d.ecnt[t] = make_int2(ne, ns);
+}
+
+// ---------------------------------------------------------------------------
+// rows of L(a, S) and U(S, a)^T of the nodes a of one height, S the
+// descendants of a: L(a, S) = A(a, S) W(S, S), U(S, a) = Y(S, S) A(S, a).  A
+// stored entry towards row r adds a multiple of r's packed row of W (of Y^T),
+// which holds the columns of the nodes w on r's chain: those with r in w's
+// subtree.  One work-group per row, side and kRowCols columns; each thread
+// gathers its columns' terms over the row's entries.
+// ---------------------------------------------------------------------------
+constexpr int kRowCols = 4 * kThreads;
+constexpr int kRowEnts = 64;  // entries staged at a time
 __global__ __launch_bounds__(kThreads) void k_nd_rows(NdDev d, const int *__restrict__ rows)
 {
+    __shared__ int er[kRowEnts], el[kRowEnts];
+    __shared__ long long eo[kRowEnts];
+    __shared__ double ev[kRowEnts];
     const int c = rows[blockIdx.x];
-    const bool low = blockIdx.y == 0;
     const NdNode a = d.node[d.nodeof[c]];
-    const int len = a.s - a.f;
-    double *out = (low ? d.L : d.Ut) + a.qbase + (long long)(c - a.s) * a.qld;
+    const int len = a.s - a.f, j0 = (blockIdx.y >> 1) * kRowCols;
+    if (j0 >= len) return;
+    const bool low = (blockIdx.y & 1) == 0;
     const double *P = low ? d.W : d.Yt;
-    for (int j = threadIdx.x; j < len; j += kThreads) out[j] = 0.0;
-    for (int e = d.ent_ptr[c]; e < d.ent_ptr[c + 1]; ++e) {
-        __syncthreads();  // the writes of the previous entry are complete
-        const int4 t = d.ent[e];
-        const double v = d.val[low ? t.z : t.w];
-        const NdNode q = d.node[d.nodeof[t.x]];
-        const double *p = P + q.wbase + (long long)(t.x - q.s) * q.c;
-        const int *cm = d.cmap + q.cbase;
-        for (int k = threadIdx.x; k < t.y; k += kThreads) out[cm[k] - a.f] += v * p[k];
+    double *out = (low ? d.L : d.Ut) + a.qbase + (long long)(c - a.s) * a.qld;
+    const int e0 = d.rp[d.iperm[c]], ne = d.ecnt[c].x;
+    double acc[4];
+    int wf[4], we[4], wl[4], wo[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+        const int j = j0 + u * kThreads + threadIdx.x;
+        acc[u] = 0.0;
+        wf[u] = 0x7fffffff;  // no row is in this "subtree"
+        we[u] = wl[u] = wo[u] = 0;
+        if (j < len) {
+            const NdNode w = d.node[d.nodeof[a.f + j]];
+            wf[u] = w.f;
+            we[u] = w.s + w.m;
+            wl[u] = w.len;
+            wo[u] = a.f + j - w.s;
+        }
+    }
+    for (int k0 = 0; k0 < ne; k0 += kRowEnts) {
+        const int m = min(kRowEnts, ne - k0);
+        __syncthreads();
+        if ((int)threadIdx.x < m) {
+            const int4 t = d.ent[e0 + k0 + threadIdx.x];
+            const NdNode q = d.node[d.nodeof[t.x]];
+            er[threadIdx.x] = t.x;
+            el[threadIdx.x] = q.len;
+            eo[threadIdx.x] = q.wbase + (long long)(t.x - q.s) * q.c;
+            ev[threadIdx.x] = d.val[low ? t.z : t.w];
+        }
+        __syncthreads();
+        for (int k = 0; k < m; ++k) {
+            const int r = er[k];
+            const double *p = P + eo[k] + el[k];
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+                if (r >= wf[u] && r < we[u]) acc[u] += ev[k] * p[wo[u] - wl[u]];
+        }
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+        const int j = j0 + u * kThreads + threadIdx.x;
+        if (j < len) out[j] = acc[u];
     }
 }
 
 // 64 x 64 product tile C = sum_k A(i, k) B(j, k) on 4 waves (32 x 32 each),
 // both operands through LDS in k-chunks of 16, double buffered.  fa(i, k),
-// fb(j, k) return the operands (0 beyond K); KMAJ: fb is read with j along
-// the lanes instead of k.  Lane layout of the FP64 MFMA: A[i][k] in lane
-// i + 16k, B[k][j] in lane j + 16k, D[i][j] in lane j + 16(i%4), element i/4.
+// fb(j, k, x) return the operands (0 beyond K); KMAJ: fb is read with j along
+// the lanes instead of k.  x = ix(k) is fb's index of k, read a chunk ahead.
+// Lane layout of the FP64 MFMA: A[i][k] in lane i + 16k, B[k][j] in lane j + 16k, D[i][j] in lane j + 16(i%4), element i/4.
 struct NdLds {
     double A[2][kT][kKC + 1], B[2][kT][kKC + 1];
 };
-template <bool KMAJ, typename FA, typename FB>
-__device__ inline void nd_product(int K, const FA &fa, const FB &fb, dbl4 (&acc)[2][2], NdLds &s)
+template <bool KMAJ, typename FA, typename FB, typename IX>
+__device__ inline void nd_product(int K, const FA &fa, const FB &fb, const IX &ix,
+                                  dbl4 (&acc)[2][2], NdLds &s)
 {
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
     const int wr = (wave >> 1) * 32, wc = (wave & 1) * 32, li = lane & 15, lk = lane >> 4;
     const int ak = tid & 15, ai = tid >> 4;
     const int bk = KMAJ ? tid >> 6 : ak, bj = KMAJ ? tid & 63 : ai;
     double ra[4], rb[4];
+    int x = KMAJ ? 0 : ix(ak);
     auto fetch = [&](int k0) {
 #pragma unroll
         for (int u = 0; u < 4; ++u) ra[u] = fa(ai + 16 * u, k0 + ak);
 #pragma unroll
         for (int u = 0; u < 4; ++u)
-            rb[u] = KMAJ ? fb(bj, k0 + bk + 4 * u) : fb(bj + 16 * u, k0 + bk);
+            rb[u] = KMAJ ? fb(bj, k0 + bk + 4 * u, 0) : fb(bj + 16 * u, k0 + bk, x);
+        if (!KMAJ) x = ix(k0 + kKC + ak);
     };
     auto stash = [&](int buf) {
 #pragma unroll
@@ -122,11 +220,12 @@ __global__ __launch_bounds__(kThreads) void k_nd_prod(NdDev d, const int4 *__res
     const auto fa = [&](int i, int k) {
         return k < K && i0 + i < v.m ? P[(long long)(i0 + i) * v.c + k] : 0.0;
     };
-    const auto fb = [&](int j, int k) {
-        return k < K && j0 + j < a.m ? Q[(long long)(j0 + j) * a.qld + cm[k] - a.f] : 0.0;
+    const auto ix = [&](int k) { return k < K ? cm[k] - a.f : 0; };
+    const auto fb = [&](int j, int k, int x) {
+        return k < K && j0 + j < a.m ? Q[(long long)(j0 + j) * a.qld + x] : 0.0;
     };
     dbl4 acc[2][2];
-    nd_product<false>(K, fa, fb, acc, s);
+    nd_product<false>(K, fa, fb, ix, acc, s);
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int r0 = i0 + (wave >> 1) * 32 + (lane >> 4), c0 = j0 + (wave & 1) * 32 + (lane & 15);
 #pragma unroll
@@ -157,22 +256,29 @@ __global__ __launch_bounds__(kThreads) void k_nd_schur(NdDev d, const int *__res
     const NdNode a = d.node[nodes[blockIdx.x]];
     for (int r = blockIdx.y; r < a.mp; r += gridDim.y) {
         double *out = d.S0 + a.sbase + (long long)r * a.mp;
-        const int c = a.s + r;
+        int e0 = 0, e1 = 0, ne = 0, ns = 0;
+        if (r < a.m) {
+            const int i = d.iperm[a.s + r];
+            const int2 cnt = d.ecnt[a.s + r];
+            e0 = d.rp[i];
+            e1 = d.rp[i + 1];
+            ne = cnt.x;
+            ns = cnt.y;
+        }
         for (int j = threadIdx.x; j < a.mp; j += kThreads) {
             double acc = (r >= a.m && r == j) ? 1.0 : 0.0;
             if (r < a.m && j < a.m)
-                for (int e = d.ent_ptr[c]; e < d.ent_ptr[c + 1]; ++e) {
-                    const int4 t = d.ent[e];
+                for (int e = 0; e < ne; ++e) {
+                    const int4 t = d.ent[e0 + e];
                     acc -= d.val[t.z] * d.X[a.xbase + (long long)(t.x - a.f) * a.m + j];
                 }
             out[j] = acc;
         }
         __syncthreads();
-        if (r < a.m)
-            for (int e = d.self_ptr[c] + threadIdx.x; e < d.self_ptr[c + 1]; e += kThreads) {
-                const int2 t = d.self[e];
-                out[t.x] += d.val[t.y];
-            }
+        for (int e = threadIdx.x; e < ns; e += kThreads) {
+            const int2 t = d.self[e1 - 1 - e];
+            out[t.x] += d.val[t.y];
+        }
     }
 }
 
@@ -185,6 +291,52 @@ __global__ __launch_bounds__(kThreads) void k_nd_schur(NdDev d, const int *__res
 // ---------------------------------------------------------------------------
 constexpr int kLdA = 68, kLdB = 80;  // LDS leading dimensions: row-wise / column-wise reads
 
+// entry of lane t of every row of 16 lanes, to all lanes of that row
+template <int T>
+__device__ inline double row_bcast(double v)
+{
+    const long long b = __double_as_longlong(v);
+    const int lo = __builtin_amdgcn_update_dpp(0, (int)b, 0x150 + T, 0xf, 0xf, true);
+    const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), 0x150 + T, 0xf, 0xf, true);
+    return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
+}
+__device__ inline double lane_value(double v, int l)
+{
+    const long long b = __double_as_longlong(v);
+    const int lo = __builtin_amdgcn_readlane((int)b, l);
+    const int hi = __builtin_amdgcn_readlane((int)(b >> 32), l);
+    return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
+}
+
+// Steps T .. 15 of the in-place Gauss-Jordan inverse of a 16 x 16 block, row
+// li, columns 4 lk .. 4 lk + 3 in x.  A step's chain is the pivot's
+// reciprocal, one product and one multiply-add.
+template <int T>
+__device__ inline void nd_gj16(double (&x)[4], int li, int lk)
+{
+    if constexpr (T < 16) {
+        // the pivot's reciprocal by two Newton steps on the hardware's estimate
+        // (within an ulp, which the setup's check of the solve covers)
+        const double pv0 = lane_value(x[T & 3], ((T >> 2) << 4) | T);
+        double rp = __builtin_amdgcn_rcp(pv0);
+        rp = fma(fma(-pv0, rp, 1.0), rp, rp);
+        rp = fma(fma(-pv0, rp, 1.0), rp, rp);
+        const double f = __shfl(x[T & 3], ((T >> 2) << 4) | li, 64);  // column T, this row
+        double pr[4];  // row T, this lane's columns
+#pragma unroll
+        for (int q = 0; q < 4; ++q) pr[q] = row_bcast<T>(x[q]);
+        const double fr = f * rp;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const bool colt = lk == (T >> 2) && q == (T & 3);
+            const double up = colt ? -fr : x[q] - fr * pr[q];
+            const double pv = colt ? rp : pr[q] * rp;
+            x[q] = li == T ? pv : up;
+        }
+        nd_gj16<T + 1>(x, li, lk);
+    }
+}
+
 __device__ inline void nd_invert64(double (*__restrict__ M)[kLdA])
 {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -195,23 +347,7 @@ __device__ inline void nd_invert64(double (*__restrict__ M)[kLdA])
             double x[4];
 #pragma unroll
             for (int q = 0; q < 4; ++q) x[q] = M[P0 + li][P0 + 4 * lk + q];
-#pragma unroll
-            for (int t = 0; t < 16; ++t) {
-                // row t (this lane's columns), column t (this lane's row), pivot
-                double pr[4];
-#pragma unroll
-                for (int q = 0; q < 4; ++q) pr[q] = __shfl(x[q], (lane & 48) | t, 64);
-                const double f = __shfl(x[t & 3], ((t >> 2) << 4) | li, 64);
-                const double rp = 1.0 / __shfl(x[t & 3], ((t >> 2) << 4) | t, 64);
-                const double fr = f * rp;
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const bool colt = 4 * lk + q == t;
-                    const double up = colt ? -fr : x[q] - fr * pr[q];
-                    const double pv = colt ? rp : pr[q] * rp;
-                    x[q] = li == t ? pv : up;
-                }
-            }
+            nd_gj16<0>(x, li, lk);
 #pragma unroll
             for (int q = 0; q < 4; ++q) M[P0 + li][P0 + 4 * lk + q] = x[q];
         }
@@ -257,19 +393,42 @@ __device__ inline void nd_invert64(double (*__restrict__ M)[kLdA])
     }
 }
 
+// A 64 x 64 tile between global memory (leading dimension ld, 16-byte aligned
+// rows) and LDS: all loads of a thread go out before the first store.
+template <int LD>
+__device__ inline void nd_tile_in(const double *__restrict__ S, int ld, double (*__restrict__ M)[LD])
+{
+    double2 v[8];
+    const int r = threadIdx.x >> 5, c = 2 * (threadIdx.x & 31);
+#pragma unroll
+    for (int u = 0; u < 8; ++u)
+        v[u] = *reinterpret_cast<const double2 *>(S + (long long)(r + 8 * u) * ld + c);
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+        M[r + 8 * u][c] = v[u].x;
+        M[r + 8 * u][c + 1] = v[u].y;
+    }
+}
+template <int LD>
+__device__ inline void nd_tile_out(const double (*__restrict__ M)[LD], double *__restrict__ S, int ld)
+{
+    const int r = threadIdx.x >> 5, c = 2 * (threadIdx.x & 31);
+#pragma unroll
+    for (int u = 0; u < 8; ++u)
+        *reinterpret_cast<double2 *>(S + (long long)(r + 8 * u) * ld + c) =
+            make_double2(M[r + 8 * u][c], M[r + 8 * u][c + 1]);
+}
+
 // First pivot block of every node: D = S(0, 0)^-1 into the node's slot of Dk.
 __global__ __launch_bounds__(kThreads) void k_nd_first(NdDev d, const int *__restrict__ nodes)
 {
     __shared__ double M[kT][kLdA];
     const int id = nodes[blockIdx.x];
     const NdNode a = d.node[id];
-    const double *S = d.S0 + a.sbase;
-    for (int q = threadIdx.x; q < kT * kT; q += kThreads)
-        M[q >> 6][q & 63] = S[(long long)(q >> 6) * a.mp + (q & 63)];
+    nd_tile_in(d.S0 + a.sbase, a.mp, M);
     __syncthreads();
     nd_invert64(M);
-    double *D = d.Dk + (long long)id * 2 * kT * kT;
-    for (int q = threadIdx.x; q < kT * kT; q += kThreads) D[q] = M[q >> 6][q & 63];
+    nd_tile_out(M, d.Dk + (long long)id * 2 * kT * kT, kT);
 }
 
 // Block step k of the node inverses (blocked Gauss-Jordan without
@@ -288,19 +447,19 @@ __global__ __launch_bounds__(kThreads) void k_nd_step(NdDev d, const int4 *__res
     double *O = (k & 1 ? d.S0 : d.S1) + a.sbase;
     const double *D = d.Dk + ((long long)t.x * 2 + (k & 1)) * kT * kT;
     const bool rk = i0 == k0, ck = j0 == k0;
-    for (int q = tid; q < kT * kT; q += kThreads) {
-        const int r = q >> 6, c = q & 63;
-        const double dv = D[q];
-        Dm[r][c] = dv;
-        if (!rk) Am[r][c] = S[(long long)(i0 + r) * a.mp + k0 + c];
-        Bm[r][c] = ck ? dv : S[(long long)(k0 + r) * a.mp + j0 + c];
-    }
+    nd_tile_in(D, kT, Dm);
+    if (!rk) nd_tile_in(S + (long long)i0 * a.mp + k0, a.mp, Am);
+    if (ck)
+        nd_tile_in(D, kT, Bm);
+    else
+        nd_tile_in(S + (long long)k0 * a.mp + j0, a.mp, Bm);
     __syncthreads();
     const int wave = tid >> 6, lane = tid & 63, li = lane & 15, lk = lane >> 4;
     const int wr = (wave >> 1) * 32, wc = (wave & 1) * 32;
     dbl4 acc[2][2];
     // product of a row-wise with a column-wise operand, this wave's 32 x 32
     const auto mul = [&](const double (*X)[kLdA], double sgn) {
+#pragma unroll 4
         for (int kk = 0; kk < kT; kk += 4) {
             double av[2], bv[2];
 #pragma unroll
@@ -340,8 +499,7 @@ __global__ __launch_bounds__(kThreads) void k_nd_step(NdDev d, const int4 *__res
         __syncthreads();
     }
     if (rk) {
-        for (int q = tid; q < kT * kT; q += kThreads)
-            O[(long long)(i0 + (q >> 6)) * a.mp + j0 + (q & 63)] = Bm[q >> 6][q & 63];
+        nd_tile_out(Bm, O + (long long)i0 * a.mp + j0, a.mp);
         return;
     }
     load([&](int r, int c) { return ck ? 0.0 : S[(long long)(i0 + r) * a.mp + j0 + c]; });
@@ -352,17 +510,29 @@ __global__ __launch_bounds__(kThreads) void k_nd_step(NdDev d, const int4 *__res
         store([&](int r, int c, double v) { Am[r][c] = v; });
         __syncthreads();
         nd_invert64(Am);
-        double *N = d.Dk + ((long long)t.x * 2 + ((k + 1) & 1)) * kT * kT;
-        for (int q = tid; q < kT * kT; q += kThreads) N[q] = Am[q >> 6][q & 63];
+        nd_tile_out(Am, d.Dk + ((long long)t.x * 2 + ((k + 1) & 1)) * kT * kT, kT);
     }
 }
 
-// W(v, a) = -X(v, a) S_a^-1 for the descendants' rows; a tile with v == a
-// copies the inverse itself into the node's rows of W (and the identity into
-// those of Y^T).
-__global__ __launch_bounds__(kThreads) void k_nd_scale(NdDev d, const int4 *__restrict__ tiles)
+// W(v, a) = -X(v, a) S_a^-1 for the descendants' rows (ntile tiles); the
+// work-groups after them take one row each of the nodes themselves: S_a^-1
+// into its packed row of W, the identity into that of Y^T.
+__global__ __launch_bounds__(kThreads) void k_nd_scale(NdDev d, const int4 *__restrict__ tiles,
+                                                       int ntile, const int *__restrict__ rows)
 {
     __shared__ NdLds s;
+    if ((int)blockIdx.x >= ntile) {
+        const int c = rows[blockIdx.x - ntile];
+        const NdNode a = d.node[d.nodeof[c]];
+        const int r = c - a.s;
+        const double *Sv = ((a.mp / kT) & 1 ? d.S1 : d.S0) + a.sbase + (long long)r * a.mp;
+        double *w = d.W + a.wbase + (long long)r * a.c, *y = d.Yt + a.wbase + (long long)r * a.c;
+        for (int j = threadIdx.x; j < a.m; j += kThreads) {
+            w[j] = Sv[j];
+            y[j] = r == j ? 1.0 : 0.0;
+        }
+        return;
+    }
     const int4 t = tiles[blockIdx.x];
     const NdNode v = d.node[t.x], a = d.node[t.y];
     const int i0 = t.z >> 16, j0 = t.z & 0xffff;
@@ -371,11 +541,11 @@ __global__ __launch_bounds__(kThreads) void k_nd_scale(NdDev d, const int4 *__re
     const auto fa = [&](int i, int k) {
         return k < a.m && i0 + i < v.m ? X[(long long)(i0 + i) * a.m + k] : 0.0;
     };
-    const auto fb = [&](int j, int k) {
+    const auto fb = [&](int j, int k, int) {
         return k < a.m && j0 + j < a.m ? Sv[(long long)k * a.mp + j0 + j] : 0.0;
     };
     dbl4 acc[2][2];
-    nd_product<true>(a.m, fa, fb, acc, s);
+    nd_product<true>(a.m, fa, fb, [](int) { return 0; }, acc, s);
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int r0 = i0 + (wave >> 1) * 32 + (lane >> 4), c0 = j0 + (wave & 1) * 32 + (lane & 15);
 #pragma unroll
@@ -388,21 +558,6 @@ __global__ __launch_bounds__(kThreads) void k_nd_scale(NdDev d, const int4 *__re
                 if (r < v.m && c < a.m)
                     d.W[v.wbase + (long long)r * v.c + t.w + c] = -acc[x][y][q];
             }
-}
-
-// The nodes' own entries: S_a^-1 into the packed rows of W, the identity into
-// those of Y^T, zero into the padding entry of every row.
-__global__ __launch_bounds__(kThreads) void k_nd_own(NdDev d, const int *__restrict__ nodes)
-{
-    const NdNode a = d.node[nodes[blockIdx.x]];
-    const double *Sv = ((a.mp / kT) & 1 ? d.S1 : d.S0) + a.sbase;
-    for (int r = blockIdx.y; r < a.m; r += gridDim.y) {
-        double *w = d.W + a.wbase + (long long)r * a.c, *y = d.Yt + a.wbase + (long long)r * a.c;
-        for (int j = threadIdx.x; j < a.m; j += kThreads) {
-            w[j] = Sv[(long long)r * a.mp + j];
-            y[j] = r == j ? 1.0 : 0.0;
-        }
-    }
 }
 
 // ---------------------------------------------------------------------------
@@ -485,25 +640,30 @@ __global__ __launch_bounds__(kThreads) void k_nd_zero(long long n, double *__res
 
 hipError_t launch_nd_factor(const NdPlan &P, const NdDev &d, hipStream_t st)
 {
+    k_nd_nodes<<<(unsigned)P.node.size(), kThreads, 0, st>>>(d);
+    k_nd_entries<<<(P.n + kThreads - 1) / kThreads, kThreads, 0, st>>>(P.n, d);
     k_nd_zero<<<1024, kThreads, 0, st>>>((long long)P.wtot, d.W);  // the rows' padding entries
     for (int h = 0; h < P.heights; ++h) {
         const int nodes = P.first_ptr[h + 1] - P.first_ptr[h];
         const int nprod = P.prod_ptr[h + 1] - P.prod_ptr[h];
         const int nrows = P.rows_ptr[h + 1] - P.rows_ptr[h];
-        const int *first = d.first + P.first_ptr[h];
+        const int *first = d.first + P.first_ptr[h], *rows = d.rows + P.rows_ptr[h];
         const int4 *prod = d.prod + P.prod_ptr[h], *inv = d.inv + P.inv_ptr[h];
         if (nodes == 0) continue;
         const int mp = P.node[P.first[P.first_ptr[h]]].mp;  // the largest
         if (nprod > 0) {
-            k_nd_rows<<<dim3(nrows, 2), kThreads, 0, st>>>(d, d.rows + P.rows_ptr[h]);
+            int len = 0;
+            for (int q = P.first_ptr[h]; q < P.first_ptr[h + 1]; ++q)
+                len = std::max(len, P.node[P.first[q]].s - P.node[P.first[q]].f);
+            k_nd_rows<<<dim3(nrows, 2 * ((len + kRowCols - 1) / kRowCols)), kThreads, 0, st>>>(d,
+                                                                                            rows);
             k_nd_prod<<<dim3(nprod, 2), kThreads, 0, st>>>(d, prod);
         }
         k_nd_schur<<<dim3(nodes, mp), kThreads, 0, st>>>(d, first);
         k_nd_first<<<nodes, kThreads, 0, st>>>(d, first);
         for (size_t k = 0; k < P.inv_n[h].size(); ++k)
             k_nd_step<<<P.inv_n[h][k], kThreads, 0, st>>>(d, inv, (int)k);
-        k_nd_own<<<dim3(nodes, mp), kThreads, 0, st>>>(d, first);
-        if (nprod > 0) k_nd_scale<<<nprod, kThreads, 0, st>>>(d, prod);
+        k_nd_scale<<<nprod + nrows, kThreads, 0, st>>>(d, prod, nprod, rows);
     }
     return hipGetLastError();
 }

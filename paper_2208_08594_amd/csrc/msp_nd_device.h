@@ -9,13 +9,23 @@
 namespace msp {
 
 // Device pointers of a factorisation: copies of the plan's lists, the matrix
-// values (natural CSR order) and the work and result arrays.
+// in natural CSR order, lists built here, and the work and result arrays.
 struct NdDev {
     const NdNode *node;
-    const int *nodeof, *cmap, *ent_ptr, *self_ptr, *rows, *first;
-    const int4 *ent, *prod, *inv;
-    const int2 *self;
+    const int *rows, *first;
+    const int4 *prod, *inv;
+    const int *rp, *ci;
     const double *val;
+    const int *iperm;
+    int *perm, *nodeof, *cmap;  // built: n, n, cmap_len
+    int4 *yrow, *wrow;          // built: n each, see NdSolve
+    // built, nnz each: the stored entries of a permuted row t = perm[i] towards
+    // descendants of its node at ent[rp[i] ..): {permuted row, chain entries of
+    // that row below t's node, CSR index of (i, .), CSR index of (., i)}; those
+    // inside the node from the end of the row's slots backwards at self:
+    // {column relative to the node, CSR index}; ecnt[t]: {how many of each}
+    int4 *ent;
+    int2 *self, *ecnt;
     double *W, *Yt;      // packed rows (wtot each)
     double *Y, *L, *Ut;  // qtot each
     double *X;           // xtot
@@ -25,7 +35,9 @@ struct NdDev {
 // Computes W and Y (d.W and d.Y), queued on st.
 hipError_t launch_nd_factor(const NdPlan &P, const NdDev &d, hipStream_t st);
 
-// What the solve reads (kept with the preconditioner).
+// What the solve reads (kept with the preconditioner): the rows of Y by falling
+// length, {row, first column, length, offset}, and per row of W {offset,
+// entries, offset of their columns in cmap, 0}.
 struct NdSolve {
     int n = 0, nlong = 0;
     const int4 *yrow = nullptr, *wrow = nullptr;
