@@ -128,6 +128,8 @@ struct BiluData {
     std::vector<int> fwd_vpos, bwd_vpos;  // elimination position of each level-ordered row
     std::vector<char> fwd_live;           // forward level with at least one stored entry
     bool turn = false;  // the last forward level is the first backward level reversed
+    int sweep = 0;      // many short levels: launch_bilu_sweeps with that many work-groups
+    int *next = nullptr;  // its slice counters
     DevSell L, U;
     int *fwd_rows_d = nullptr, *bwd_rows_d = nullptr;
     int *pos_d = nullptr;  // elimination position of each block row: the solves' vector order
@@ -824,6 +826,26 @@ bool coarse_solve_accurate(msp_ctx *c, std::vector<void *> &tmp)
     return true;
 }
 
+// Triangular solves of more than kSweepLevels levels of at most kSweepWidth
+// slices each on average run as one launch per direction
+// (launch_bilu_sweeps), others as one launch per level.  A level's launch
+// costs 5 to 7 us however few rows it has, the sweep 1.5 to 3 us.  Whole apply,
+// launches -> sweep: natural order 10^3 cells, b = 4 (28 levels of 1 slice)
+// 260 -> 117 us; 64x64x32, b = 4 (158 of 13) 2240 -> 945 us; 128x128x64, b = 7
+// (318 of 52) 19.6 -> 3.8 ms; 200^3, b = 2 (598 of 209) 9.8 -> 6.3 ms;
+// multi-color order on 27-point boxes (8 levels) of 60^3 cells (422 slices)
+// 1090 -> 1058 us, but 80^3 (1000 slices) 1.41 -> 1.62 ms: such levels are bound
+// by bandwidth, which the launches use better.  Two levels (every 7-point
+// grid in the multi-color order) are as fast either way on small grids (20^3:
+// 68.5 and 67.4 us) and faster as launches on larger ones (64x64x32: 181 and
+// 266 us).
+// The work-groups at work: three levels' slices and a few more.  Fewer leave a
+// level's slices waiting for each other (64x64x32 with 16, 48, 256
+// work-groups: 1415, 932, 1287 us; 20^3: 255, 296, 365 us), more only poll.
+constexpr int kSweepLevels = 4;
+constexpr int kSweepWidth = 512;
+constexpr int kSweepMaxGroups = 256;
+
 // Host-only part of the block ILU(0) setup: elimination order, dependency
 // levels, factorisation tasks and the sliced layouts of L and U.  Touches no
 // device state, so it can run on a second host thread.
@@ -908,6 +930,9 @@ void bilu_plan(const msp_ctx *c, const std::vector<int> &color, int g, BiluData 
     const int f0 = D.fwd_ptr[D.fwd_ptr.size() - 2], nt = n - f0;
     D.turn = D.fwd_live.back() && D.bwd_ptr[1] == nt &&
              std::equal(D.bwd_rows.begin(), D.bwd_rows.begin() + nt, D.fwd_rows.rbegin());
+    const int levels = D.L.nseg(), slices = (int)D.L.lay.slice_row0.size();
+    if (levels > kSweepLevels && slices <= kSweepWidth * levels)
+        D.sweep = std::min(kSweepMaxGroups, 8 + 3 * (slices / levels));
 }
 
 // Device part: factorise level by level and lay the factors out, on the side
@@ -954,6 +979,7 @@ void bilu_device(msp_ctx *c, const double *vals, BiluPlan &P, std::vector<void *
     };
     layout(D.L, D.fwd_rows_d, true);
     layout(D.U, D.bwd_rows_d, false);
+    if (D.sweep) D.next = (int *)c->dalloc(2 * sizeof(int), c->allocB);
     D.dsrc = c->upload(P.dsrc, c->allocB);
     const long long dsl = (long long)P.dsrc.size();
     if (c->fp32()) {
@@ -1475,6 +1501,12 @@ void bilu_solve(msp_ctx *c, T *y)
     } else {
         Lv = (const T *)D.L64; Uv = (const T *)D.U64; Dv = (const T *)D.D64;
     }
+    if (D.sweep) {  // zout is written after this, by the apply's last kernel
+        HIPCHK(launch_bilu_sweeps<T>(c->b, c->n, D.L.all(), D.fwd_vpos_d, Lv, D.U.all(),
+                                     D.bwd_vpos_d, Uv, Dv, y, (T *)c->zout, D.next, D.sweep,
+                                     c->stream));
+        return;
+    }
     const int nf = D.L.nseg();
     for (int s = 0; s < nf; ++s)
         if (D.fwd_live[s]) {
@@ -1585,7 +1617,8 @@ int apply_launches(const msp_ctx *c)
 {
     int k = 6;
     for (const Level &L : c->lev) k += (c->opt.nu_pre + c->opt.nu_post) * L.g + 4;
-    if (c->opt.full_smoother == 0) k += c->bilu.L.nseg() + c->bilu.U.nseg();
+    if (c->opt.full_smoother == 0)
+        k += c->bilu.sweep ? 3 : c->bilu.L.nseg() + c->bilu.U.nseg();
     if (c->ns.on) k += (int)c->ns.grp_ptr.size() + 4;
     return k;
 }
@@ -1594,9 +1627,9 @@ int apply_launches(const msp_ctx *c)
 // ahead keeps the stream filled, and a graph launch costs 20 to 30 us of idle
 // device around it (eight 20^3 systems solved together, 11 launches each:
 // 7.4 ms with graphs, 4.3 without; 60x220x85 cells layered, 140 launches:
-// 111.3 and 110.4 ms).  Longer ones (the dependency levels of the natural
-// elimination order) would keep the host busy for as long as they run
-// (16x14x19 cells: 3.06 ms with graphs, 3.17 without).
+// 111.3 and 110.4 ms).  Longer ones (several sweeps per level of a hierarchy of
+// many colors) would keep the host busy for as long as they run (an apply of
+// 190 launches: 3.06 ms a solve with graphs, 3.17 without).
 constexpr int kEagerLaunches = 160;
 
 bool apply_by_graph(const msp_ctx *c, bool capture_ok)

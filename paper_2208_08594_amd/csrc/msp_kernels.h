@@ -197,6 +197,14 @@ hipError_t launch_bilu_fwd(int b, const SellView &L, const int *rows, const T *L
 template <typename T>
 hipError_t launch_bilu_bwd(int b, const SellView &U, const int *rows, const T *Uval,
                            const T *Dval, T *z, hipStream_t st);
+// Both solves in place on y, one launch each and one to prepare them, for
+// factors of many short levels (L, U: all slices).  w: another vector of n b
+// entries; next: two counters; groups: work-groups at work (those beyond the
+// few levels that are under way only poll).
+template <typename T>
+hipError_t launch_bilu_sweeps(int b, int n, const SellView &L, const int *fwd_rows, const T *Lval,
+                              const SellView &U, const int *bwd_rows, const T *Uval,
+                              const T *Dval, T *y, T *w, int *next, int groups, hipStream_t st);
 // z_c = zz[zperm[c]] (zperm may be nullptr: natural order) + e_c at the
 // pressure entry (+ w1_c if w1 != nullptr).
 template <typename T>

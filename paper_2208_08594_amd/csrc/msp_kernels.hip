@@ -1134,6 +1134,170 @@ __global__ __launch_bounds__(kThreads) void k_bilu_bwd(const int4 *__restrict__ 
     }
 }
 
+// ---------------------------------------------------------------------------
+// Block triangular solves with many short dependency levels, one launch each.
+// Work-groups of B waves draw the slices from a counter in level order, so a
+// slice's rows depend only on slices drawn before it by work-groups that run
+// or have ended, and the first unfinished slice never waits: every wait ends
+// (the bound on the polls only keeps an error from becoming a hang).  A value
+// is its own flag: `out` starts filled with a NaN pattern that no result has,
+// and a row's waves poll, past the caches of their own XCD, for the B values
+// of each block column until none holds it.  Factor blocks and pivot inverses
+// are loaded before that wait.  Lane = row of the slice, wave = component; the
+// polled values (and in the backward sweep t, before D^-1) cross the waves
+// through LDS.  Same operations in the same order as the level launches.
+// Bound by the chain of levels: a poll that sees the value, the products and
+// the store, 2.3 us a level on 64x64x32 cells, b = 4 (158 levels each way,
+// 0.75 ms; 2.0 ms with a launch per level).
+// ---------------------------------------------------------------------------
+template <typename T>
+struct SweepWord;
+template <>
+struct SweepWord<double> {
+    using type = unsigned long long;
+    static constexpr type pending = 0x7ff4a5a5a5a5a5a5ull;  // signalling: no operation returns it
+};
+template <>
+struct SweepWord<float> {
+    using type = unsigned;
+    static constexpr type pending = 0x7fa5a5a5u;
+};
+constexpr int kSweepCols = 4;        // block columns of a row per batch
+constexpr int kSweepPolls = 1 << 20;
+
+template <typename T>
+__device__ inline typename SweepWord<T>::type sweep_bits(T v)
+{
+    typename SweepWord<T>::type w;
+    __builtin_memcpy(&w, &v, sizeof(T));
+    return w;
+}
+template <typename T>
+__device__ inline typename SweepWord<T>::type sweep_load(const T *p)
+{
+    using W = typename SweepWord<T>::type;
+    return __hip_atomic_load(reinterpret_cast<const W *>(p), __ATOMIC_RELAXED,
+                             __HIP_MEMORY_SCOPE_AGENT);
+}
+template <typename T>
+__device__ inline void sweep_store(T *p, T v)
+{
+    using W = typename SweepWord<T>::type;
+    W w = sweep_bits(v);
+    if (w == SweepWord<T>::pending) w |= W(1) << (sizeof(T) == 8 ? 51 : 22);  // quiet
+    __hip_atomic_store(reinterpret_cast<W *>(p), w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// out = pending, and both sweeps' slice counters zero
+template <typename T>
+__global__ __launch_bounds__(kThreads) void k_sweep_begin(long long n, T *out, int *next)
+{
+    using W = typename SweepWord<T>::type;
+    const long long q = (long long)blockIdx.x * kThreads + threadIdx.x;
+    if (q < 2) next[q] = 0;
+    if (q < n) reinterpret_cast<W *>(out)[q] = SweepWord<T>::pending;
+}
+
+// Forward (BWD = false): out = in - L out, and `in`, once read, becomes pending
+// for the backward sweep into it.  Backward: out = D^-1 (in - U out).
+template <int B, typename T, bool BWD>
+__global__ __launch_bounds__(64 * B) void k_bilu_sweep(int nslices,
+                                                       const int4 *__restrict__ slices,
+                                                       const int *__restrict__ col,
+                                                       const int *__restrict__ rows,
+                                                       const T *__restrict__ val,
+                                                       const T *__restrict__ Dval, T *in, T *out,
+                                                       int *next)
+{
+    constexpr int E = B * B, K = kSweepCols;
+    using W = typename SweepWord<T>::type;
+    __shared__ W ys[K][B][64];
+    __shared__ T ts[B][64];
+    __shared__ int drawn;
+    const int lane = threadIdx.x & 63, r = threadIdx.x >> 6;
+    for (;;) {
+        __syncthreads();  // LDS of the slice before is no longer read
+        if (threadIdx.x == 0)
+            drawn = __hip_atomic_fetch_add(next, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __syncthreads();
+        const int s = drawn;
+        if (s >= nslices) return;
+        const int4 d = slices[s];
+        const bool on = lane < d.y;
+        const long long i = on ? rows[d.x + lane] : 0;
+        T t = on ? in[i * B + r] : T(0);
+        if (!BWD && on) reinterpret_cast<W *>(in)[i * B + r] = SweepWord<T>::pending;
+        T D[B];
+        if (BWD) {
+#pragma unroll
+            for (int u = 0; u < B; ++u)
+                D[u] = on ? Dval[(long long)s * 64 * E + (r * B + u) * 64 + lane] : T(0);
+        }
+        T acc = 0;
+        for (int k0 = 0; k0 < d.z; k0 += K) {
+            int c[K];
+            T v[K][B];
+#pragma unroll
+            for (int k = 0; k < K; ++k)
+                c[k] = on && k0 + k < d.z
+                           ? __builtin_nontemporal_load(col + d.w + (k0 + k) * 64 + lane)
+                           : -1;
+#pragma unroll
+            for (int k = 0; k < K; ++k)
+#pragma unroll
+                for (int u = 0; u < B; ++u)
+                    v[k][u] = c[k] >= 0 ? __builtin_nontemporal_load(
+                                              val + ((long long)(d.w >> 6) + k0 + k) * 64 * E +
+                                              (r * B + u) * 64 + lane)
+                                        : T(0);
+            W y[K];
+#pragma unroll
+            for (int k = 0; k < K; ++k)
+                y[k] = c[k] >= 0 ? sweep_load(out + (long long)c[k] * B + r) : 0;
+            for (int polls = 0; polls < kSweepPolls; ++polls) {
+                bool miss = false;
+#pragma unroll
+                for (int k = 0; k < K; ++k) miss |= y[k] == SweepWord<T>::pending;
+                if (!__any(miss)) break;
+#pragma unroll
+                for (int k = 0; k < K; ++k)
+                    if (y[k] == SweepWord<T>::pending)
+                        y[k] = sweep_load(out + (long long)c[k] * B + r);
+            }
+            if (k0) __syncthreads();
+#pragma unroll
+            for (int k = 0; k < K; ++k) ys[k][r][lane] = y[k];
+            __syncthreads();
+#pragma unroll
+            for (int k = 0; k < K; ++k) {
+                if (c[k] < 0) continue;
+                T a = 0;
+#pragma unroll
+                for (int u = 0; u < B; ++u) {
+                    T yk;
+                    const W w = ys[k][u][lane];
+                    __builtin_memcpy(&yk, &w, sizeof(T));
+                    if (BWD)
+                        a += v[k][u] * yk;
+                    else
+                        acc += v[k][u] * yk;
+                }
+                if (BWD) t -= a;
+            }
+        }
+        if (!BWD) {
+            if (on) sweep_store(out + i * B + r, t - acc);
+            continue;
+        }
+        ts[r][lane] = t;
+        __syncthreads();
+        T z = 0;
+#pragma unroll
+        for (int u = 0; u < B; ++u) z += D[u] * ts[u][lane];
+        if (on) sweep_store(out + i * B + r, z);
+    }
+}
+
 template <int B, typename T>
 __global__ __launch_bounds__(kThreads) void k_finish(int p, int n, const T *__restrict__ zz,
                                                      const int *__restrict__ zperm,
@@ -2345,6 +2509,23 @@ hipError_t launch_bilu_bwd(int b, const SellView &U, const int *rows, const T *U
     return hipGetLastError();
 }
 
+template <typename T>
+hipError_t launch_bilu_sweeps(int b, int n, const SellView &L, const int *fwd_rows, const T *Lval,
+                              const SellView &U, const int *bwd_rows, const T *Uval,
+                              const T *Dval, T *y, T *w, int *next, int groups, hipStream_t st)
+{
+    const long long N = (long long)n * b;
+    const int nl = L.slice_end - L.slice_begin, nu = U.slice_end - U.slice_begin;
+    k_sweep_begin<T><<<blocks_for(N), kThreads, 0, st>>>(N, w, next);
+    MSP_SWITCH_B(b, (k_bilu_sweep<B, T, false><<<std::min(nl, groups), 64 * B, 0, st>>>(
+                        nl, L.slices + L.slice_begin, L.col, fwd_rows, Lval, nullptr, y, w,
+                        next)));
+    MSP_SWITCH_B(b, (k_bilu_sweep<B, T, true><<<std::min(nu, groups), 64 * B, 0, st>>>(
+                        nu, U.slices + U.slice_begin, U.col, bwd_rows, Uval, Dval, w, y,
+                        next + 1)));
+    return hipGetLastError();
+}
+
 // dst_T[pos[c]*b + k] = (T)src[c*b + k] (src != nullptr), or
 // dst64[c*b + k] = (double)srcT[pos[c]*b + k]
 template <typename T>
@@ -2469,6 +2650,9 @@ hipError_t launch_from_double(long long n, const double *x, T *y, hipStream_t st
                                                 hipStream_t);                                  \
     template hipError_t launch_bilu_fwd<T>(int, const SellView &, const int *, const T *, T *, \
                                            int, int, const T *, hipStream_t);                  \
+    template hipError_t launch_bilu_sweeps<T>(int, int, const SellView &, const int *, const T *, \
+                                              const SellView &, const int *, const T *,       \
+                                              const T *, T *, T *, int *, int, hipStream_t);  \
     template hipError_t launch_bilu_bwd<T>(int, const SellView &, const int *, const T *,      \
                                            const T *, T *, hipStream_t);                       \
     template hipError_t launch_finish<T>(int, int, int, const T *, const int *, const T *,     \

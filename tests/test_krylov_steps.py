@@ -76,12 +76,14 @@ def test_initial_guess_and_exact_start():
 
 
 @pytest.mark.parametrize("fp32", [False, True])
-def test_captured_natural_order_apply(fp32):
+def test_captured_apply(fp32):
     """An apply of many launches is replayed from a graph: every replay equals
     the eager launches, with eager work between the replays."""
     s = synth.lognormal_grid(40, 33, 22, 3, 12, 1.5, 0.1, "lateral4")
-    a = msp.Solver(max_coarse=3000, bilu_order=0, precond_fp32=fp32, use_graphs=False)
-    b = msp.Solver(max_coarse=3000, bilu_order=0, precond_fp32=fp32, use_graphs=True)
+    a = msp.Solver(max_coarse=300, nu_pre=8, nu_post=8, precond_fp32=fp32,
+                   use_graphs=False)
+    b = msp.Solver(max_coarse=300, nu_pre=8, nu_post=8, precond_fp32=fp32,
+                   use_graphs=True)
     a.setup(s)
     b.setup(s)
     rng = np.random.default_rng(1)
