@@ -107,6 +107,10 @@ struct Level {
     int *ru_ptr = nullptr, *ru_col = nullptr;
     void *ru_val = nullptr;
     int ru_lanes = 8;
+    // the sweeps of the cycle in one launch each with that many work-groups, if
+    // not 0; their slice counters
+    int sweep = 0;
+    int *next = nullptr;
 };
 
 // N stage (concentration block, block Gauss-Seidel in the groups of the
@@ -431,6 +435,25 @@ int row_lanes(const SellLayout &lay)
     return w > 8 ? kRowLanes : 1;
 }
 
+// Work-groups of a sweep in one launch: the slices of three dependent groups of
+// rows and a few more, at most kSweepMaxGroups.  Fewer leave a group's slices
+// waiting for each other, more only poll (block ILU(0) in the natural order,
+// 64x64x32 cells with 13 slices a level: 16, 48 and 256 work-groups 1415, 932
+// and 1287 us an apply; Gauss-Seidel, 60x220x85 cells with at most 64, 128,
+// 256, 512: 862, 783, 769, 780 us).
+constexpr int kSweepMaxGroups = 256;
+
+// Both Gauss-Seidel sweeps of a smoothed coarse level run as one launch each
+// (launch_gs_sweep) if it has kGsSweepColors colors of at most kGsSweepWidth
+// slices on average: a color's launch costs 4.5 us however few rows it has, in
+// the sweep a color costs about 2.5 us.  Whole apply, launches -> sweeps:
+// 60x220x85 cells layered (five such levels of 9 to 12 colors; the largest, 530
+// slices a color, keeps its launches) 880 -> 769 us, 128x128x64 in FP32 778 ->
+// 671 us, 64x64x32 188 -> 150 us.  The widest levels are as fast as launches,
+// which use the bandwidth better: with sweeps on them too 801 and 703 us.
+constexpr int kGsSweepColors = 4;
+constexpr int kGsSweepWidth = 256;
+
 // Device arrays of level l (its layout computed by level_layout unless it is
 // the coarsest level, whose positions are the natural order).
 void build_level_device(msp_ctx *c, int l, bool last, LevelLayout *lay, const LevelCsr &csr)
@@ -479,6 +502,14 @@ void build_level_device(msp_ctx *c, int l, bool last, LevelLayout *lay, const Le
     }
     L.perm_d = c->upload(L.perm, c->allocB);
     L.iperm_d = c->upload(L.iperm, c->allocB);
+    if (l > 0 && S.lanes == kRowLanes && c->opt.smoother == 0 && c->opt.nu_pre == 1 &&
+        c->opt.nu_post == 1) {
+        const int g = (int)L.seg_row.size() - 1, slices = (int)S.slices_h.size();
+        if (g >= kGsSweepColors && slices <= kGsSweepWidth * g) {
+            L.sweep = std::min(kSweepMaxGroups, 8 + 3 * (slices / g));
+            L.next = (int *)c->dalloc(2 * sizeof(int), c->allocB);
+        }
+    }
     HIPCHK(launch_level_fill(c->fp32(), (int)S.slices_h.size(), S.slices, csr.rp, csr.ci, csr.val,
                              L.perm_d, L.iperm_d, S.col, S.src, vals, diag,
                              c->copy_stream ? c->copy_stream : c->stream));
@@ -839,12 +870,8 @@ bool coarse_solve_accurate(msp_ctx *c, std::vector<void *> &tmp)
 // grid in the multi-color order) are as fast either way on small grids (20^3:
 // 68.5 and 67.4 us) and faster as launches on larger ones (64x64x32: 181 and
 // 266 us).
-// The work-groups at work: three levels' slices and a few more.  Fewer leave a
-// level's slices waiting for each other (64x64x32 with 16, 48, 256
-// work-groups: 1415, 932, 1287 us; 20^3: 255, 296, 365 us), more only poll.
 constexpr int kSweepLevels = 4;
 constexpr int kSweepWidth = 512;
-constexpr int kSweepMaxGroups = 256;
 
 // Host-only part of the block ILU(0) setup: elimination order, dependency
 // levels, factorisation tasks and the sliced layouts of L and U.  Touches no
@@ -1459,7 +1486,12 @@ void vcycle(msp_ctx *c, int l, bool first_done = false, T *nat = nullptr)
         return;
     }
     Level &C = c->lev[l + 1];
-    smooth<T>(c, L, true, true, c->opt.nu_pre, first_done);
+    if (L.sweep)
+        HIPCHK(launch_gs_sweep<T>(L.S.all(), L.S.lay.seg_slice[1], true, lev_val<T>(L),
+                                  lev_diag<T>(L), (const T *)L.f, nullptr, (T *)L.x, L.next,
+                                  L.sweep, c->stream));
+    else
+        smooth<T>(c, L, true, true, c->opt.nu_pre, first_done);
     // a smoothed coarse level whose pre-smoothing starts with a Gauss-Seidel
     // color from zero gets that color from the restriction itself
     const bool fuse = l + 1 < (int)c->lev.size() - 1 && c->opt.smoother == 0 &&
@@ -1469,7 +1501,7 @@ void vcycle(msp_ctx *c, int l, bool first_done = false, T *nat = nullptr)
     T *xc = fuse ? (T *)C.x : nullptr;
     if (L.ru_ptr) {
         HIPCHK(launch_restrict_upper<T>(C.n, L.ru_lanes, L.ru_ptr, L.ru_col, (const T *)L.ru_val,
-                                        (const T *)L.x, (T *)C.f, p0, p1, dc, xc, c->stream));
+                                        (const T *)L.x, (T *)C.f, p0, p1, dc, xc, C.next, c->stream));
     } else {
         HIPCHK(launch_residual<T>(L.S.all(), lev_val<T>(L), lev_diag<T>(L), (const T *)L.f,
                                   (const T *)L.x, (T *)L.r, c->stream));
@@ -1480,6 +1512,14 @@ void vcycle(msp_ctx *c, int l, bool first_done = false, T *nat = nullptr)
             HIPCHK(launch_restrict<T>(C.n, L.mem_ptr, L.mem, (const T *)L.r, (T *)C.f, c->stream));
     }
     vcycle<T>(c, l + 1, fuse);
+    if (L.sweep) {
+        HIPCHK(launch_prolong_sweep<T>(L.n, L.agg_pos, (const T *)C.x, (T *)L.x, (T *)L.r,
+                                       c->stream));
+        HIPCHK(launch_gs_sweep<T>(L.S.all(), 0, false, lev_val<T>(L), lev_diag<T>(L),
+                                  (const T *)L.f, (const T *)L.r, (T *)L.x, L.next + 1, L.sweep,
+                                  c->stream));
+        return;
+    }
     const bool fold = fold_prolong(c, L);
     if (!fold) HIPCHK(launch_prolong<T>(L.n, L.agg_pos, (const T *)C.x, (T *)L.x, c->stream));
     smooth<T>(c, L, false, false, c->opt.nu_post, false, fold ? (const T *)C.x : nullptr, nat);
@@ -1616,7 +1656,8 @@ void capture_apply(msp_ctx *c)
 int apply_launches(const msp_ctx *c)
 {
     int k = 6;
-    for (const Level &L : c->lev) k += (c->opt.nu_pre + c->opt.nu_post) * L.g + 4;
+    for (const Level &L : c->lev)
+        k += (L.sweep ? 2 : (c->opt.nu_pre + c->opt.nu_post) * L.g) + 4;
     if (c->opt.full_smoother == 0)
         k += c->bilu.sweep ? 3 : c->bilu.L.nseg() + c->bilu.U.nseg();
     if (c->ns.on) k += (int)c->ns.grp_ptr.size() + 4;

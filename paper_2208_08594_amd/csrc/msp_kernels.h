@@ -130,11 +130,22 @@ hipError_t launch_restrict_first(int nc, const int *mem_ptr, const int *mem, con
 // fc = R (f - A x) after one forward Gauss-Seidel sweep from x = 0 (in exact
 // arithmetic), from the entries of higher colors in coarse-row order: ptr over
 // the nc coarse rows, col (fine positions), val.  lanes: 8 or 64 per row.
-// xc != nullptr: then the coarse level's first color as launch_restrict_first.
+// xc != nullptr: then the coarse level's first color as launch_restrict_first,
+// and with next != nullptr all else that a launch_gs_sweep into xc expects.
 template <typename T>
 hipError_t launch_restrict_upper(int nc, int lanes, const int *ptr, const int *col, const T *val,
                                  const T *x, T *fc, int p0, int p1, const T *diag_c, T *xc,
-                                 hipStream_t st);
+                                 int *next, hipStream_t st);
+// The other colors of a forward sweep from zero (after launch_restrict_upper;
+// s0: first slice of the second color), or a backward sweep of all colors (s0
+// = 0, after launch_prolong_sweep), in one launch of at most `groups`
+// work-groups.  A level of kRowLanes lanes; next: a counter, zero.
+template <typename T>
+hipError_t launch_gs_sweep(const SellView &all, int s0, bool forward, const T *val, const T *diag,
+                           const T *f, const T *old, T *x, int *next, int groups, hipStream_t st);
+template <typename T>
+hipError_t launch_prolong_sweep(int n, const int *agg_pos, const T *xc, T *x, T *old,
+                                hipStream_t st);
 // The entries themselves: counts per member slot, then (off, tile, total: the
 // tile scan of the counts) ptr, col and the values.
 hipError_t launch_ru_count(int n, const int *mem, const int *perm, const int *iperm, const int *rp,

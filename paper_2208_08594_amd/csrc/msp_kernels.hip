@@ -752,6 +752,151 @@ __global__ __launch_bounds__(kThreads) void k_residual_lanes(
     sweep_row_lanes<T, L, true>(slices, col, s0, s1, val, diag, f, const_cast<T *>(x), r);
 }
 
+// ---------------------------------------------------------------------------
+// Sweeps that run many dependent groups of rows in one launch (k_gs_sweep,
+// k_bilu_sweep).  Work-groups draw the slices from a counter in the order of
+// the dependencies, so a slice's rows depend only on slices drawn before it by
+// work-groups that run or have ended, and the first unfinished slice never
+// waits: every wait ends (the bound on the polls only keeps an error from
+// becoming a hang).  A value is its own flag: the output starts filled with a
+// NaN pattern that no result has, and a row polls, past the caches of its own
+// XCD, the values it needs until none holds it.
+// ---------------------------------------------------------------------------
+template <typename T>
+struct SweepWord;
+template <>
+struct SweepWord<double> {
+    using type = unsigned long long;
+    static constexpr type pending = 0x7ff4a5a5a5a5a5a5ull;  // signalling: no operation returns it
+};
+template <>
+struct SweepWord<float> {
+    using type = unsigned;
+    static constexpr type pending = 0x7fa5a5a5u;
+};
+constexpr int kSweepCols = 4;  // entries of a row (and lane) per batch
+constexpr int kSweepPolls = 1 << 20;
+
+template <typename T>
+__device__ inline typename SweepWord<T>::type sweep_bits(T v)
+{
+    typename SweepWord<T>::type w;
+    __builtin_memcpy(&w, &v, sizeof(T));
+    return w;
+}
+template <typename T>
+__device__ inline typename SweepWord<T>::type sweep_load(const T *p)
+{
+    using W = typename SweepWord<T>::type;
+    return __hip_atomic_load(reinterpret_cast<const W *>(p), __ATOMIC_RELAXED,
+                             __HIP_MEMORY_SCOPE_AGENT);
+}
+template <typename T>
+__device__ inline void sweep_store(T *p, T v)
+{
+    using W = typename SweepWord<T>::type;
+    W w = sweep_bits(v);
+    if (w == SweepWord<T>::pending) w |= W(1) << (sizeof(T) == 8 ? 51 : 22);  // quiet
+    __hip_atomic_store(reinterpret_cast<W *>(p), w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// Gauss-Seidel sweep over the slices [s0, s1), colors ascending (forward, from
+// x = 0: entries of higher colors are skipped, the first color is in x
+// already) or descending (backward: entries of lower colors take `old`).  x
+// holds the pending pattern where the sweep writes.  Rows, lanes and the order
+// of the sums as in k_gs_color_lanes; one slice per work-group of L waves, the
+// next slice drawn while one is worked on.  Bound by the chain of colors (poll,
+// sum over the lanes, division, store): about 2.5 us a color against 4.5 us for
+// a launch (77,000 rows, 10 colors).
+template <typename T, int L, bool BWD>
+__global__ __launch_bounds__(64 * L) void k_gs_sweep(const int4 *__restrict__ slices,
+                                                     const int *__restrict__ col, int s0, int s1,
+                                                     const T *__restrict__ val,
+                                                     const T *__restrict__ diag,
+                                                     const T *__restrict__ f,
+                                                     const T *__restrict__ old, T *x, int *next)
+{
+    constexpr int RPW = 64 / L, K = kSweepCols;
+    using W = typename SweepWord<T>::type;
+    __shared__ int drawn[2];
+    const int lane = threadIdx.x & 63, t = lane % RPW, j = lane / RPW;
+    const int local = (threadIdx.x >> 6) * RPW + t;
+    const auto draw = [next]() {
+        return __hip_atomic_fetch_add(next, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    };
+    if (threadIdx.x == 0) drawn[0] = draw();
+    for (int turn = 0;; turn ^= 1) {
+        __syncthreads();
+        const int q = drawn[turn];
+        if (q >= s1 - s0) return;
+        int ahead = 0;
+        if (threadIdx.x == 0) ahead = draw();
+        const int4 d = slices[BWD ? s1 - 1 - q : s0 + q];
+        const bool live = local < d.y;
+        const int row = d.x + local;
+        T fr = 0, dr = 1;
+        if (live && j == 0) {
+            fr = f[row];
+            dr = diag[row];
+        }
+        T sum = 0;
+        for (int k0 = 0; k0 < d.z; k0 += K * L) {
+            int c[K];
+            T v[K];
+            W y[K];
+#pragma unroll
+            for (int u = 0; u < K; ++u) {
+                const int k = k0 + u * L + j;
+                const bool in = live && k < d.z;
+                c[u] = in ? __builtin_nontemporal_load(col + d.w + k * 64 + local) : -1;
+                v[u] = in ? __builtin_nontemporal_load(val + d.w + k * 64 + local) : T(0);
+            }
+#pragma unroll
+            for (int u = 0; u < K; ++u) {
+                y[u] = 0;
+                if (c[u] < 0) continue;
+                if (BWD ? c[u] > row : c[u] < row)
+                    y[u] = sweep_load(x + c[u]);
+                else if (BWD)
+                    y[u] = sweep_bits(old[c[u]]);
+            }
+            for (int polls = 0; polls < kSweepPolls; ++polls) {
+                bool miss = false;
+#pragma unroll
+                for (int u = 0; u < K; ++u) miss |= y[u] == SweepWord<T>::pending;
+                if (!__any(miss)) break;
+#pragma unroll
+                for (int u = 0; u < K; ++u)
+                    if (y[u] == SweepWord<T>::pending) y[u] = sweep_load(x + c[u]);
+            }
+#pragma unroll
+            for (int u = 0; u < K; ++u) {
+                T xv;
+                __builtin_memcpy(&xv, &y[u], sizeof(T));
+                if (c[u] >= 0) sum += v[u] * xv;
+            }
+        }
+#pragma unroll
+        for (int o = RPW; o < 64; o <<= 1) sum += __shfl_xor(sum, o, 64);
+        if (live && j == 0) sweep_store(x + row, (fr - sum) / dr);
+        if (threadIdx.x == 0) drawn[turn ^ 1] = ahead;
+    }
+}
+
+// Prolongation ahead of a backward sweep: old = x + xc of the row's aggregate,
+// and x pending.
+template <typename T>
+__global__ __launch_bounds__(kThreads) void k_prolong_sweep(int n, const int *__restrict__ agg_pos,
+                                                            const T *__restrict__ xc,
+                                                            T *__restrict__ x,
+                                                            T *__restrict__ old)
+{
+    const int t = blockIdx.x * kThreads + threadIdx.x;
+    if (t >= n) return;
+    old[t] = x[t] + xc[agg_pos[t]];
+    reinterpret_cast<typename SweepWord<T>::type *>(x)[t] = SweepWord<T>::pending;
+}
+
 // Weighted point-Jacobi smoothing (the PJAC ablation of Sec. 6): the first
 // sweep from x = 0 is x = w D^-1 f; a later sweep is x += w D^-1 r with
 // r = f - A x from k_residual (all rows read the old x).
@@ -823,13 +968,15 @@ __global__ __launch_bounds__(kThreads) void k_restrict_first(int nc, const int *
 // 62.4 us -> 64.9 us of kernel time per cycle.  L lanes per coarse row, entries
 // j, j + L, ... on lane j, summed across the lanes with a fixed butterfly.
 // xc != nullptr: also the first color [p0, p1) of the coarse level's sweep
-// from zero (as in k_restrict_first).
+// from zero (as in k_restrict_first); next != nullptr: the others pending, and
+// that level's sweep counters zero.
 template <typename T, int L>
 __global__ __launch_bounds__(kThreads) void k_restrict_upper(
     int nc, const int *__restrict__ ptr, const int *__restrict__ col, const T *__restrict__ val,
     const T *__restrict__ x, T *__restrict__ fc, int p0, int p1, const T *__restrict__ diag_c,
-    T *__restrict__ xc)
+    T *__restrict__ xc, int *next)
 {
+    if (next && blockIdx.x == 0 && threadIdx.x < 2) next[threadIdx.x] = 0;
     const int J = (xcd_block(blockIdx.x, gridDim.x) * kThreads + threadIdx.x) / L;
     const int j = threadIdx.x % L;
     T s = 0;
@@ -855,7 +1002,12 @@ __global__ __launch_bounds__(kThreads) void k_restrict_upper(
     for (int o = 1; o < L; o <<= 1) s += __shfl_xor(s, o, 64);
     if (J < nc && j == 0) {
         fc[J] = s;
-        if (xc) xc[J] = (J >= p0 && J < p1) ? s / diag_c[J] : T(0);
+        if (xc && J >= p0 && J < p1)
+            xc[J] = s / diag_c[J];
+        else if (next)
+            reinterpret_cast<typename SweepWord<T>::type *>(xc)[J] = SweepWord<T>::pending;
+        else if (xc)
+            xc[J] = T(0);
     }
 }
 
@@ -1135,59 +1287,15 @@ __global__ __launch_bounds__(kThreads) void k_bilu_bwd(const int4 *__restrict__ 
 }
 
 // ---------------------------------------------------------------------------
-// Block triangular solves with many short dependency levels, one launch each.
-// Work-groups of B waves draw the slices from a counter in level order, so a
-// slice's rows depend only on slices drawn before it by work-groups that run
-// or have ended, and the first unfinished slice never waits: every wait ends
-// (the bound on the polls only keeps an error from becoming a hang).  A value
-// is its own flag: `out` starts filled with a NaN pattern that no result has,
-// and a row's waves poll, past the caches of their own XCD, for the B values
-// of each block column until none holds it.  Factor blocks and pivot inverses
-// are loaded before that wait.  Lane = row of the slice, wave = component; the
-// polled values (and in the backward sweep t, before D^-1) cross the waves
-// through LDS.  Same operations in the same order as the level launches.
+// Block triangular solves with many short dependency levels, one launch each:
+// a work-group of B waves per slice, lane = row, wave = component.  Factor
+// blocks and pivot inverses are loaded before the wait for the B values of
+// each block column; those (and in the backward sweep t, before D^-1) cross the
+// waves through LDS.  Same operations in the same order as the level launches.
 // Bound by the chain of levels: a poll that sees the value, the products and
 // the store, 2.3 us a level on 64x64x32 cells, b = 4 (158 levels each way,
 // 0.75 ms; 2.0 ms with a launch per level).
 // ---------------------------------------------------------------------------
-template <typename T>
-struct SweepWord;
-template <>
-struct SweepWord<double> {
-    using type = unsigned long long;
-    static constexpr type pending = 0x7ff4a5a5a5a5a5a5ull;  // signalling: no operation returns it
-};
-template <>
-struct SweepWord<float> {
-    using type = unsigned;
-    static constexpr type pending = 0x7fa5a5a5u;
-};
-constexpr int kSweepCols = 4;        // block columns of a row per batch
-constexpr int kSweepPolls = 1 << 20;
-
-template <typename T>
-__device__ inline typename SweepWord<T>::type sweep_bits(T v)
-{
-    typename SweepWord<T>::type w;
-    __builtin_memcpy(&w, &v, sizeof(T));
-    return w;
-}
-template <typename T>
-__device__ inline typename SweepWord<T>::type sweep_load(const T *p)
-{
-    using W = typename SweepWord<T>::type;
-    return __hip_atomic_load(reinterpret_cast<const W *>(p), __ATOMIC_RELAXED,
-                             __HIP_MEMORY_SCOPE_AGENT);
-}
-template <typename T>
-__device__ inline void sweep_store(T *p, T v)
-{
-    using W = typename SweepWord<T>::type;
-    W w = sweep_bits(v);
-    if (w == SweepWord<T>::pending) w |= W(1) << (sizeof(T) == 8 ? 51 : 22);  // quiet
-    __hip_atomic_store(reinterpret_cast<W *>(p), w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
 // out = pending, and both sweeps' slice counters zero
 template <typename T>
 __global__ __launch_bounds__(kThreads) void k_sweep_begin(long long n, T *out, int *next)
@@ -2351,14 +2459,16 @@ hipError_t launch_restrict_first(int nc, const int *mem_ptr, const int *mem, con
 template <typename T>
 hipError_t launch_restrict_upper(int nc, int lanes, const int *ptr, const int *col, const T *val,
                                  const T *x, T *fc, int p0, int p1, const T *diag_c, T *xc,
-                                 hipStream_t st)
+                                 int *next, hipStream_t st)
 {
     if (nc <= 0) return hipSuccess;
     const unsigned nb = blocks_for((long long)nc * lanes);
     if (lanes == 64)
-        k_restrict_upper<T, 64><<<nb, kThreads, 0, st>>>(nc, ptr, col, val, x, fc, p0, p1, diag_c, xc);
+        k_restrict_upper<T, 64><<<nb, kThreads, 0, st>>>(nc, ptr, col, val, x, fc, p0, p1, diag_c, xc,
+                                                       next);
     else if (lanes == 8)
-        k_restrict_upper<T, 8><<<nb, kThreads, 0, st>>>(nc, ptr, col, val, x, fc, p0, p1, diag_c, xc);
+        k_restrict_upper<T, 8><<<nb, kThreads, 0, st>>>(nc, ptr, col, val, x, fc, p0, p1, diag_c, xc,
+                                                       next);
     else
         return hipErrorInvalidValue;
     return hipGetLastError();
@@ -2380,6 +2490,29 @@ hipError_t launch_ru_fill(int n, int nc, const int *mem_ptr, const int *mem, con
 {
     k_ru_fill<T><<<blocks_for(std::max(n, nc + 1)), kThreads, 0, st>>>(
         n, nc, mem_ptr, mem, perm, iperm, rp, ci, val, off, tile, tile_size, total, ptr, col, out);
+    return hipGetLastError();
+}
+
+template <typename T>
+hipError_t launch_gs_sweep(const SellView &all, int s0, bool forward, const T *val, const T *diag,
+                           const T *f, const T *old, T *x, int *next, int groups, hipStream_t st)
+{
+    const int s1 = all.slice_end, nb = std::min(s1 - s0, groups);
+    if (nb <= 0) return hipSuccess;
+    if (forward)
+        k_gs_sweep<T, kRowLanes, false><<<nb, 64 * kRowLanes, 0, st>>>(
+            all.slices, all.col, s0, s1, val, diag, f, nullptr, x, next);
+    else
+        k_gs_sweep<T, kRowLanes, true><<<nb, 64 * kRowLanes, 0, st>>>(
+            all.slices, all.col, s0, s1, val, diag, f, old, x, next);
+    return hipGetLastError();
+}
+
+template <typename T>
+hipError_t launch_prolong_sweep(int n, const int *agg_pos, const T *xc, T *x, T *old,
+                                hipStream_t st)
+{
+    k_prolong_sweep<T><<<blocks_for(n), kThreads, 0, st>>>(n, agg_pos, xc, x, old);
     return hipGetLastError();
 }
 
@@ -2625,7 +2758,7 @@ hipError_t launch_from_double(long long n, const double *x, T *y, hipStream_t st
                                            T *, hipStream_t, const GsColorExtra<T> &);         \
     template hipError_t launch_restrict_upper<T>(int, int, const int *, const int *, const T *, \
                                                  const T *, T *, int, int, const T *, T *,     \
-                                                 hipStream_t);                                 \
+                                                 int *, hipStream_t);                          \
     template hipError_t launch_ru_fill<T>(int, int, const int *, const int *, const int *,     \
                                           const int *, const int *, const int *,               \
                                           const double *, const int *, const int *, int,       \
@@ -2637,6 +2770,10 @@ hipError_t launch_from_double(long long n, const double *x, T *y, hipStream_t st
     template hipError_t launch_restrict_first<T>(int, const int *, const int *, const T *, T *, \
                                                  int, int, const T *, T *, hipStream_t);       \
     template hipError_t launch_prolong<T>(int, const int *, const T *, T *, hipStream_t);      \
+    template hipError_t launch_prolong_sweep<T>(int, const int *, const T *, T *, T *,         \
+                                                hipStream_t);                                  \
+    template hipError_t launch_gs_sweep<T>(const SellView &, int, bool, const T *, const T *,  \
+                                           const T *, const T *, T *, int *, int, hipStream_t); \
     template hipError_t launch_jacobi_first<T>(int, T, const T *, const T *, T *, hipStream_t); \
     template hipError_t launch_jacobi_update<T>(int, T, const T *, const T *, T *, hipStream_t); \
     template hipError_t launch_zero<T>(int, T *, hipStream_t);                                 \
