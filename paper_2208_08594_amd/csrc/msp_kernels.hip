@@ -45,6 +45,23 @@ inline unsigned blocks_for(long long work, int per_block = kThreads)
     return (unsigned)(b < 1 ? 1 : b);
 }
 
+// Block products and triangular levels of up to this many slices take a
+// work-group of B waves per slice, a wave per component (k_spmv_rows,
+// k_pcol_residual_rows, k_bilu_rows), larger ones a wave per slice.  With a wave
+// per slice the chip has less than two waves per SIMD at 2000 slices, and each
+// works through B B loads per entry in turn.  7-point grids, wave per slice ->
+// per component, the product and both triangular solves: 1000 rows, b = 4
+// 9.2 -> 4.8 and 19.0 -> 10.1 us, b = 7 82.7 -> 8.1 and 66.2 -> 16.5; 13,824
+// rows, b = 5 17.0 -> 6.7 and 41.4 -> 13.1; 133,263 rows (2082 slices), b = 3
+// 15.8 -> 14.2 and 24.5 -> 19.5, b = 7 114 -> 70 and 101 -> 78.  160,000 rows are
+// about even (b = 6: 60.2 -> 62.4 and 97.7 -> 69.9), and on 1,048,576 rows, bound
+// by bandwidth, the wave per slice is faster (b = 7: 492 and 560 us; 515 and
+// 573): it reads an x block once, not once per component.
+constexpr int kSplitSlices = 2500;
+inline bool rows_split(const SellView &v)
+{
+    return v.slice_end - v.slice_begin <= kSplitSlices;
+}
 inline unsigned slice_blocks(const SellView &v)
 {
     int ns = v.slice_end - v.slice_begin;
@@ -553,6 +570,61 @@ __global__ __launch_bounds__(kThreads) void k_spmv(const int4 *__restrict__ slic
 #pragma unroll
     for (int r = 0; r < B; ++r)
         y[row * B + r] = sub ? sub[row * B + r] - acc[r] : acc[r];
+}
+
+// The same product with a wave per component: a slice takes a work-group of B
+// waves, wave r loads component r of the x blocks (shared through LDS) and row r
+// of the values, kRowsBatch entries at a time.  B times the waves of k_spmv,
+// with a B-th of the loads in each one's chain; the same sums.  Bound by its
+// two or three dependent loads on small matrices (4.8 us at 1000 rows, b = 4),
+// by bandwidth on larger ones (133,263 rows, b = 3: 14.2 us, 5.0 TB/s).
+template <int B>
+constexpr int kRowsBatch = B <= 4 ? 8 : 4;
+
+template <int B>
+__global__ __launch_bounds__(64 * B) void k_spmv_rows(const int4 *__restrict__ slices,
+                                                      const int *__restrict__ col, int s0,
+                                                      const double *__restrict__ val,
+                                                      const double *__restrict__ x,
+                                                      const double *__restrict__ sub,
+                                                      double *__restrict__ y)
+{
+    constexpr int E = B * B, K = kRowsBatch<B>;
+    __shared__ double xs[K][B][64];
+    const int4 d = slices[s0 + xcd_block(blockIdx.x, gridDim.x)];
+    const int lane = threadIdx.x & 63, r = threadIdx.x >> 6;
+    const bool on = lane < d.y;
+    const int *cb = col + d.w + lane;
+    const double *vb = val + (long long)(d.w >> 6) * 64 * E + r * B * 64 + lane;
+    double acc = 0.0;
+    for (int k0 = 0; k0 < d.z; k0 += K) {
+        int c[K];
+        double v[K][B], xv[K];
+#pragma unroll
+        for (int k = 0; k < K; ++k)
+            c[k] = on && k0 + k < d.z ? __builtin_nontemporal_load(cb + (k0 + k) * 64) : -1;
+#pragma unroll
+        for (int k = 0; k < K; ++k)
+#pragma unroll
+            for (int u = 0; u < B; ++u)
+                v[k][u] = on && k0 + k < d.z ? __builtin_nontemporal_load(
+                                                   vb + (long long)(k0 + k) * 64 * E + u * 64)
+                                             : 0.0;
+#pragma unroll
+        for (int k = 0; k < K; ++k) xv[k] = c[k] >= 0 ? x[(long long)c[k] * B + r] : 0.0;
+        if (k0) __syncthreads();
+#pragma unroll
+        for (int k = 0; k < K; ++k) xs[k][r][lane] = xv[k];
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < K; ++k)
+            if (c[k] >= 0)
+#pragma unroll
+                for (int u = 0; u < B; ++u) acc += v[k][u] * xs[k][u][lane];
+    }
+    if (!on) return;
+    const long long o = (long long)(d.x + lane) * B + r;
+    y[o] = sub ? sub[o] - acc : acc;
 }
 
 // ---------------------------------------------------------------------------
@@ -1176,6 +1248,49 @@ __global__ __launch_bounds__(kThreads) void k_pcol_residual(
     for (int q = 0; q < B; ++q) r[ro * B + q] = (T)v[row * B + q] - acc[q];
 }
 
+// k_pcol_residual with a wave per component.
+template <int B, typename T, bool F32>
+__global__ __launch_bounds__(64 * B) void k_pcol_residual_rows(
+    int p, const int4 *__restrict__ slices, const int *__restrict__ col, int s0,
+    const double *__restrict__ val64, const float *__restrict__ pcol32, const double *v,
+    const ApplyIo *io, const T *__restrict__ e, const int *__restrict__ rperm,
+    T *__restrict__ r)
+{
+    constexpr int E = B * B;
+    if (io) v = io->v;
+    const int4 d = slices[s0 + xcd_block(blockIdx.x, gridDim.x)];
+    const int lane = threadIdx.x & 63, q = threadIdx.x >> 6;
+    if (lane >= d.y) return;
+    const long long row = d.x + lane;
+    const long long ro = rperm ? rperm[row] : row;
+    const T vq = (T)v[row * B + q];
+    const int *cb = col + d.w + lane;
+    T acc = 0;
+    for (int k0 = 0; k0 < d.z; k0 += 8) {
+        int c[8];
+        T a[8], ev[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+            c[u] = k0 + u < d.z ? __builtin_nontemporal_load(cb + (k0 + u) * 64) : -1;
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            const long long sb = (long long)(d.w >> 6) + k0 + u;
+            a[u] = 0;
+            if (k0 + u >= d.z) continue;
+            if (F32)
+                a[u] = (T)__builtin_nontemporal_load(pcol32 + sb * 64 * B + q * 64 + lane);
+            else
+                a[u] = (T)__builtin_nontemporal_load(val64 + sb * 64 * E + (q * B + p) * 64 + lane);
+        }
+#pragma unroll
+        for (int u = 0; u < 8; ++u) ev[u] = c[u] >= 0 ? e[c[u]] : T(0);
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+            if (c[u] >= 0) acc += a[u] * ev[u];
+    }
+    r[ro * B + q] = vq - acc;
+}
+
 // Block ILU(0) triangular solves, one dependency level per launch, one
 // thread per block row of a 64-row slice.  As in k_spmv: the factor values
 // and column indices are read once per solve (non-temporal loads), padding
@@ -1404,6 +1519,80 @@ __global__ __launch_bounds__(64 * B) void k_bilu_sweep(int nslices,
         for (int u = 0; u < B; ++u) z += D[u] * ts[u][lane];
         if (on) sweep_store(out + i * B + r, z);
     }
+}
+
+// k_bilu_fwd, k_bilu_fwd with LAST and k_bilu_bwd (MODE 0, 1, 2) with a wave per
+// component, as in k_spmv_rows.
+template <int B, typename T, int MODE>
+__global__ __launch_bounds__(64 * B) void k_bilu_rows(const int4 *__restrict__ slices,
+                                                      const int *__restrict__ col, int s0,
+                                                      const int *__restrict__ rows,
+                                                      const T *__restrict__ val,
+                                                      const T *__restrict__ Dval, T *y, int row0,
+                                                      int nrows)
+{
+    constexpr int E = B * B, K = kRowsBatch<B>;
+    __shared__ T ys[K][B][64];
+    __shared__ T ts[B][64];
+    const int s = s0 + xcd_block(blockIdx.x, gridDim.x);
+    const int4 d = slices[s];
+    const int lane = threadIdx.x & 63, r = threadIdx.x >> 6;
+    const bool on = lane < d.y;
+    const long long i = on ? rows[d.x + lane] : 0;
+    T t = on ? y[i * B + r] : T(0);
+    T D[B];
+    if (MODE) {  // MODE 1: the row's place in the backward level
+        const int q = MODE == 2 ? 64 * s + lane : nrows - 1 - (d.x + lane - row0);
+        const T *Db = Dval + (long long)(q >> 6) * 64 * E + (q & 63) + r * B * 64;
+#pragma unroll
+        for (int u = 0; u < B; ++u)
+            D[u] = on ? __builtin_nontemporal_load(Db + u * 64) : T(0);
+    }
+    const int *cb = col + d.w + lane;
+    const T *vb = val + (long long)(d.w >> 6) * 64 * E + r * B * 64 + lane;
+    T acc = 0;
+    for (int k0 = 0; k0 < d.z; k0 += K) {
+        int c[K];
+        T v[K][B], yv[K];
+#pragma unroll
+        for (int k = 0; k < K; ++k)
+            c[k] = on && k0 + k < d.z ? __builtin_nontemporal_load(cb + (k0 + k) * 64) : -1;
+#pragma unroll
+        for (int k = 0; k < K; ++k)
+#pragma unroll
+            for (int u = 0; u < B; ++u)
+                v[k][u] = on && k0 + k < d.z ? __builtin_nontemporal_load(
+                                                   vb + (long long)(k0 + k) * 64 * E + u * 64)
+                                             : T(0);
+#pragma unroll
+        for (int k = 0; k < K; ++k) yv[k] = c[k] >= 0 ? y[(long long)c[k] * B + r] : T(0);
+        if (k0) __syncthreads();
+#pragma unroll
+        for (int k = 0; k < K; ++k) ys[k][r][lane] = yv[k];
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            if (c[k] < 0) continue;
+            T a = 0;
+#pragma unroll
+            for (int u = 0; u < B; ++u) {
+                if (MODE == 2)
+                    a += v[k][u] * ys[k][u][lane];
+                else
+                    acc += v[k][u] * ys[k][u][lane];
+            }
+            if (MODE == 2) t -= a;
+        }
+    }
+    if (MODE != 2) t = t - acc;
+    if (MODE) {
+        ts[r][lane] = t;
+        __syncthreads();
+        t = 0;
+#pragma unroll
+        for (int u = 0; u < B; ++u) t += D[u] * ts[u][lane];
+    }
+    if (on) y[i * B + r] = t;
 }
 
 template <int B, typename T>
@@ -2364,6 +2553,11 @@ hipError_t launch_spmv(int b, const SellView &A, const double *val, const double
 {
     unsigned nb = slice_blocks(A);
     if (!nb) return hipSuccess;
+    if (rows_split(A)) {
+        MSP_SWITCH_B(b, (k_spmv_rows<B><<<A.slice_end - A.slice_begin, 64 * B, 0, st>>>(
+                            A.slices, A.col, A.slice_begin, val, x, sub, y)));
+        return hipGetLastError();
+    }
     MSP_SWITCH_B(b, (k_spmv<B><<<nb, kThreads, 0, st>>>(A.slices, A.col, A.slice_begin,
                                                         A.slice_end, val, x, sub, y)));
     return hipGetLastError();
@@ -2600,6 +2794,19 @@ hipError_t launch_pcol_residual(int b, int p, const SellView &A, const double *v
 {
     unsigned nb = slice_blocks(A);
     if (!nb) return hipSuccess;
+    if (rows_split(A)) {
+        const int ns = A.slice_end - A.slice_begin;
+        if (pcol32) {
+            MSP_SWITCH_B(b, (k_pcol_residual_rows<B, T, true><<<ns, 64 * B, 0, st>>>(
+                                p, A.slices, A.col, A.slice_begin, val64, pcol32, v, io, e,
+                                rperm, r)));
+        } else {
+            MSP_SWITCH_B(b, (k_pcol_residual_rows<B, T, false><<<ns, 64 * B, 0, st>>>(
+                                p, A.slices, A.col, A.slice_begin, val64, pcol32, v, io, e,
+                                rperm, r)));
+        }
+        return hipGetLastError();
+    }
     if (pcol32) {
         MSP_SWITCH_B(b, (k_pcol_residual<B, T, true><<<nb, kThreads, 0, st>>>(
                             p, A.slices, A.col, A.slice_begin, A.slice_end, val64, pcol32, v, io,
@@ -2618,6 +2825,18 @@ hipError_t launch_bilu_fwd(int b, const SellView &L, const int *rows, const T *L
 {
     unsigned nb = slice_blocks(L);
     if (!nb) return hipSuccess;
+    if (rows_split(L)) {
+        const int ns = L.slice_end - L.slice_begin;
+        if (Dval) {
+            MSP_SWITCH_B(b, (k_bilu_rows<B, T, 1><<<ns, 64 * B, 0, st>>>(
+                                L.slices, L.col, L.slice_begin, rows, Lval, Dval, y, row0,
+                                nrows)));
+        } else {
+            MSP_SWITCH_B(b, (k_bilu_rows<B, T, 0><<<ns, 64 * B, 0, st>>>(
+                                L.slices, L.col, L.slice_begin, rows, Lval, nullptr, y, 0, 0)));
+        }
+        return hipGetLastError();
+    }
     if (Dval) {
         MSP_SWITCH_B(b, (k_bilu_fwd<B, T, true><<<nb, kThreads, 0, st>>>(
                             L.slices, L.col, L.slice_begin, L.slice_end, rows, Lval, y, row0,
@@ -2636,6 +2855,11 @@ hipError_t launch_bilu_bwd(int b, const SellView &U, const int *rows, const T *U
 {
     unsigned nb = slice_blocks(U);
     if (!nb) return hipSuccess;
+    if (rows_split(U)) {
+        MSP_SWITCH_B(b, (k_bilu_rows<B, T, 2><<<U.slice_end - U.slice_begin, 64 * B, 0, st>>>(
+                            U.slices, U.col, U.slice_begin, rows, Uval, Dval, z, 0, 0)));
+        return hipGetLastError();
+    }
     MSP_SWITCH_B(b, (k_bilu_bwd<B, T><<<nb, kThreads, 0, st>>>(U.slices, U.col, U.slice_begin,
                                                                U.slice_end, rows, Uval, Dval,
                                                                z)));
