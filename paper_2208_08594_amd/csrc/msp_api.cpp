@@ -677,7 +677,8 @@ bool launch_coarse_nd(msp_ctx *c, const Csr &A, bool level0, LevelCsr dev,
     // level 0's pattern stays for the whole Newton sequence, and so does its plan
     if (!level0 || c->nd_gen != c->pattern_gen || P.n != m) {
         c->nd_gen = -1;
-        if (!nd_plan(m, A.rp.data(), A.ci.data(), P)) {
+        // (Galerkin products keep level 0's symmetry; dominance implies a diagonal)
+        if (!nd_plan(m, A.rp.data(), A.ci.data(), P, c->pattern_sym)) {
             P.clear();
             return false;
         }

@@ -719,7 +719,6 @@ int device_hierarchy(Csr &A0, const int *rp0, const int *ci0, const double *val0
                                                       dev_done]() {
                 bool signalled = false;
                 try {
-                    hagg.resize(nf);
                     hn.rp.resize(Cd.n + 1);
                     auto ck = [hip_fail](hipError_t e) {
                         if (e != hipSuccess) {
@@ -732,13 +731,16 @@ int device_hierarchy(Csr &A0, const int *rp0, const int *ci0, const double *val0
                                       hipMemcpyDeviceToHost, copy_st));
                     ck(hipStreamSynchronize(copy_st));
                     const long long nnzc = hn.rp[Cd.n];
-                    hn.ci.resize(nnzc);
-                    hn.val.resize(nnzc);
                     // page-locked staging: [ci | val | agg], one DMA each
                     char *sb = stg ? (char *)(*stg)(lnext, sizeof(int) * (size_t)nnzc +
                                                                sizeof(double) * (size_t)nnzc +
                                                                sizeof(int) * (size_t)nf)
                                    : nullptr;
+                    if (!sb) {
+                        hagg.resize(nf);
+                        hn.ci.resize(nnzc);
+                        hn.val.resize(nnzc);
+                    }
                     int *sci = sb ? (int *)sb : hn.ci.data();
                     double *sval =
                         sb ? (double *)(sb + sizeof(int) * (size_t)nnzc) : hn.val.data();
@@ -756,9 +758,16 @@ int device_hierarchy(Csr &A0, const int *rp0, const int *ci0, const double *val0
                                           hipMemcpyDeviceToHost, copy_st));
                     ck(hipMemcpyAsync(sagg, aggf, sizeof(int) * nf, hipMemcpyDeviceToHost,
                                       copy_st));
-                    // H grows on the main thread once the device reads are done:
-                    // the destinations are taken here (moving a vector keeps its
-                    // storage)
+                    // the host arrays are sized (their pages cleared) behind the
+                    // copies, after the level's host work has started: 43 MB on
+                    // 306,000 rows, 4 ms.  H grows on the main thread once the
+                    // device reads are done: the destinations are taken here
+                    // (moving a vector keeps its storage)
+                    if (sb) {
+                        hn.ci.resize(nnzc);
+                        hn.val.resize(nnzc);
+                        hagg.resize(nf);
+                    }
                     int *dci = hn.ci.data(), *dagg = hagg.data();
                     double *dval = hn.val.data();
                     if (sb) std::memcpy(dci, sci, sizeof(int) * (size_t)nnzc);

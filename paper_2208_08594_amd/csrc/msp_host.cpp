@@ -209,128 +209,121 @@ static bool bipartite_groups(const Adjacency &G, std::vector<int> &color, int &g
     return true;
 }
 
-// The greedy of Alg. 4.2 over the neighbour lists nb[ptr[u] .. ptr[u+1]):
-// with REL each entry holds w - u (16 bits: the arrays the greedy reads at
-// random then take about half the cache, which keeps it fast while other
-// host threads stream through memory), else w.  Cnt holds the counts of
-// uncoloured neighbours (at least the largest degree).
-template <bool REL, typename Off, typename Cnt>
-static int greedy_groups(int n, const int *ptr, const Off *nb, int dmax, std::vector<int> &color)
+// The greedy of Alg. 4.2.  degree(i) is the number of neighbours of vertex i,
+// each(i, f) calls f with every one of them.
+//
+// Static priority: larger |S_i| first, smaller index on ties (Alg. 4.1 picks
+// any vertex of maximal |S_i|; the lowest index makes the choice unique).
+// Vertices are renamed to their place in that order, so that a set of vertices
+// is a bit set whose lowest member is the best, small enough (37 KB at 300,000
+// vertices) for the first-level cache, and the neighbour lists hold places.
+// Bound by the dependent reads of the lists, one random list after another:
+// 293,000 vertices with 10 neighbours each take 35 ms (42 ms with byte flags and
+// 16-bit lists in the natural order and a queue of places beside them).
+template <class Degree, class Each>
+static int greedy_groups(int n, int dmax, Degree degree, Each each, std::vector<int> &color)
 {
-    auto degree = [ptr](int i) { return ptr[i + 1] - ptr[i]; };
-    color.assign(n, 0);
-    // Static priority: larger |S_i| first, smaller index on ties (Alg. 4.1 picks
-    // any vertex of maximal |S_i|; the lowest index makes the choice unique).
-    // (a counting sort by degree: buckets from the largest degree down,
-    // ascending indices inside a bucket)
-    std::vector<int> order(n);
+    using Word = unsigned long long;
+    std::unique_ptr<int[]> order(new int[(size_t)n]), place(new int[(size_t)n]);
+    std::unique_ptr<int[]> ptr(new int[(size_t)n + 1]);
     {
+        // a counting sort by degree: buckets from the largest degree down,
+        // ascending indices inside a bucket
         std::vector<int> start(dmax + 2, 0);
         for (int i = 0; i < n; ++i) ++start[dmax - degree(i) + 1];
         for (int d = 0; d <= dmax; ++d) start[d + 1] += start[d];
-        for (int i = 0; i < n; ++i) order[start[dmax - degree(i)]++] = i;
-    }
-    // Candidates W^ are taken in the same priority, i.e. smallest position in
-    // `order` first: a two-level bit set over positions (words of 64
-    // positions and a summary bit per word) gives that position quickly.
-    std::vector<int> pos(n);
-    for (int q = 0; q < n; ++q) pos[order[q]] = q;
-    const int nw = (n + 63) / 64, ns = (nw + 63) / 64;
-    std::vector<unsigned long long> bits(nw, 0ull), summ(ns, 0ull);
-    int nqueued = 0;
-    int s_lo = ns;  // no summary word below s_lo is set
-    auto hat_push = [&](int v) {
-        const int q = pos[v];
-        bits[q >> 6] |= 1ull << (q & 63);
-        summ[q >> 12] |= 1ull << ((q >> 6) & 63);
-        s_lo = std::min(s_lo, q >> 12);
-        ++nqueued;
-    };
-    auto hat_pop = [&]() -> int {  // requires nqueued > 0
-        int s = s_lo;
-        while (summ[s] == 0ull) ++s;
-        s_lo = s;
-        const int w = (s << 6) + __builtin_ctzll(summ[s]);
-        const int b = __builtin_ctzll(bits[w]);
-        bits[w] &= bits[w] - 1;
-        if (bits[w] == 0ull) summ[s] &= ~(1ull << (w & 63));
-        --nqueued;
-        return order[(w << 6) + b];
-    };
-    // per vertex: kOpen (in V), kQueued (already a second-ring candidate of this
-    // group), kScanned (neighbourhood already enumerated for this group), in
-    // one byte so that each visit touches one cache line.  A vertex never
-    // re-enters V inside a group, so enumerating a neighbourhood a second time
-    // cannot add a candidate: each neighbourhood is scanned at most once per
-    // group.
-    constexpr unsigned char kOpen = 1, kQueued = 2, kScanned = 4;
-    std::vector<unsigned char> fl(n);
-    // unc[u]: neighbours of u not yet in any group; a vertex with none has
-    // nothing left to add to a second ring, so its neighbourhood is skipped
-    std::vector<Cnt> unc(n);
-    for (int u = 0; u < n; ++u) unc[u] = (Cnt)degree(u);
-    // second-ring vertices newly queued for one chosen vertex (each vertex is
-    // queued at most once per group)
-    std::vector<int> fresh((size_t)std::min<long long>((long long)dmax * dmax, n) + 1);
-    unsigned char *F = fl.data();
-    auto at = [nb](int u, int q) { return REL ? u + (int)nb[q] : (int)nb[q]; };
-    int left = n, g = 0;
-    while (left > 0) {
-        ++g;  // one call of VerticesSplitting builds group g
-        int avail = 0;
         for (int i = 0; i < n; ++i) {
-            F[i] = color[i] == 0 ? kOpen : 0;  // V: undetermined vertices
-            avail += F[i];
+            const int q = start[dmax - degree(i)]++;
+            order[q] = i;
+            place[i] = q;
         }
-        std::fill(bits.begin(), bits.end(), 0ull);
-        std::fill(summ.begin(), summ.end(), 0ull);
-        nqueued = 0;
-        s_lo = ns;
-        size_t cursor = 0;
-        while (avail > 0) {
+    }
+    ptr[0] = 0;
+    for (int q = 0; q < n; ++q) ptr[q + 1] = ptr[q] + degree(order[q]);
+    std::unique_ptr<int[]> nb(new int[(size_t)std::max(ptr[n], 1)]);
+    for_chunks(n, host_parts(n), [&](int lo, int hi, int) {
+        for (int q = lo; q < hi; ++q) {
+            int o = ptr[q];
+            each(order[q], [&](int w) { nb[o++] = place[w]; });
+        }
+    });
+    // left: not in any group.  Of the group being built: open, the set V;
+    // fresh, open and not yet a second-ring candidate; hat, the candidates W^
+    // (closed ones among them are masked out when a word is read) with a
+    // summary bit per word; seen, vertices whose neighbourhood has been
+    // enumerated.  A vertex never re-enters V inside a group, so enumerating a
+    // neighbourhood a second time cannot add a candidate.  spent: vertices
+    // with no neighbour left (unc counts those), whose neighbourhoods add
+    // nothing in any later group.
+    const int nw = (n + 63) / 64, ns = (nw + 63) / 64;
+    std::vector<Word> left(nw, ~0ull), open(nw), fresh(nw), seen(nw), spent(nw, 0ull);
+    std::vector<Word> hat(nw, 0ull), summ(ns, 0ull);
+    if (n & 63) left[nw - 1] = (1ull << (n & 63)) - 1;
+    std::vector<int> unc(n), ring(dmax + 1), group(n);
+    for (int u = 0; u < n; ++u) {
+        unc[u] = ptr[u + 1] - ptr[u];
+        if (unc[u] == 0) spent[u >> 6] |= 1ull << (u & 63);
+    }
+    int todo = n, g = 0;
+    while (todo > 0) {
+        ++g;  // one call of VerticesSplitting builds group g
+        open = left;
+        fresh = left;
+        seen = spent;
+        int cursor = 0, low = ns;  // no summary word below low is set
+        for (;;) {
             int v = -1;
-            while (nqueued > 0) {  // second-ring candidates W^ that are still in V
-                int t = hat_pop();
-                if (F[t] & kOpen) { v = t; break; }
-            }
+            for (; low < ns && v < 0; low += v < 0)  // second-ring candidates that are still in V
+                while (summ[low] != 0ull) {
+                    const int w = (low << 6) + __builtin_ctzll(summ[low]);
+                    hat[w] &= open[w];
+                    if (hat[w] != 0ull) {
+                        v = (w << 6) + __builtin_ctzll(hat[w]);
+                        break;
+                    }
+                    summ[low] &= summ[low] - 1;
+                }
             if (v < 0) {
-                while (!(F[order[cursor]] & kOpen)) ++cursor;
-                v = order[cursor];
+                while (cursor < nw && open[cursor] == 0ull) ++cursor;
+                if (cursor == nw) break;  // V is empty
+                v = (cursor << 6) + __builtin_ctzll(open[cursor]);
             }
-            color[v] = g;  // v joins W
-            F[v] &= (unsigned char)~kOpen;
-            --avail;
-            --left;
-            const int p0 = ptr[v], p1 = ptr[v + 1];
-            for (int q = p0; q < p1; ++q) {  // S_v leaves V (W-bar)
-                const int u = at(v, q);
-                __builtin_prefetch(&nb[ptr[u]]);  // read by the second ring below
-                --unc[u];
-                const unsigned char f = F[u];
-                avail -= f & kOpen;
-                F[u] = f & (unsigned char)~kOpen;
-            }
-            // second ring enters W^.  Whether a vertex is open is close to
-            // random here: the flags are updated without a branch and the
-            // newly queued vertices collected, then pushed together.
+            group[v] = g;  // v joins W
+            --todo;
+            const Word bv = 1ull << (v & 63);
+            open[v >> 6] &= ~bv;
+            fresh[v >> 6] &= ~bv;
+            left[v >> 6] &= ~bv;
             int k = 0;
-            for (int q = p0; q < p1; ++q) {
-                const int u = at(v, q);
-                if ((F[u] & kScanned) || unc[u] == 0) continue;
-                F[u] |= kScanned;
-                const int e = ptr[u + 1];
-                for (int t = ptr[u]; t < e; ++t) {
-                    const int w = at(u, t);
-                    const unsigned char f = F[w];
-                    const int take = (f & (kOpen | kQueued)) == kOpen;
-                    F[w] = (unsigned char)(f | take * kQueued);
-                    fresh[k] = w;
-                    k += take;
+            for (int q = ptr[v]; q < ptr[v + 1]; ++q) {  // S_v leaves V (W-bar)
+                const int u = nb[q], i = u >> 6;
+                __builtin_prefetch(&nb[ptr[u]]);  // read by the second ring below
+                const Word b = 1ull << (u & 63);
+                open[i] &= ~b;
+                fresh[i] &= ~b;
+                const int c = --unc[u];
+                if (c == 0) spent[i] |= b;
+                ring[k] = u;
+                k += (seen[i] & b) == 0ull && c != 0;
+                seen[i] |= b;
+            }
+            for (int r = 0; r < k; ++r) {  // second ring enters W^
+                const int e = ptr[ring[r] + 1];
+                for (int t = ptr[ring[r]]; t < e; ++t) {
+                    const int w = nb[t], i = w >> 6;
+                    const Word b = 1ull << (w & 63);
+                    if (__builtin_expect((fresh[i] & b) != 0ull, 0)) {
+                        fresh[i] &= ~b;
+                        hat[i] |= b;
+                        summ[i >> 6] |= 1ull << (i & 63);
+                        low = std::min(low, i >> 6);
+                    }
                 }
             }
-            for (int i = 0; i < k; ++i) hat_push(fresh[i]);
         }
     }
+    color.resize(n);
+    for (int i = 0; i < n; ++i) color[i] = group[place[i]];
     return g;
 }
 
@@ -341,40 +334,23 @@ int vertices_grouping(const Adjacency &G, std::vector<int> &color)
     if (bipartite_groups(G, color, g_bip)) return g_bip;
     int dmax = 0;
     for (int i = 0; i < n; ++i) dmax = std::max(dmax, G.degree(i));
-    // 16-bit neighbour offsets where every one fits (levels built from a mesh
-    // numbering: neighbours lie within a few planes)
-    const long long nnz = (long long)G.nbr.size();
-    std::unique_ptr<short[]> nb16(new short[std::max<long long>(nnz, 1)]);
-    const int parts = host_parts(n);
-    std::vector<unsigned char> fits(parts, 1);
-    for_chunks(n, parts, [&](int lo, int hi, int t) {
-        for (int u = lo; u < hi && fits[t]; ++u)
-            for (int q = G.ptr[u]; q < G.ptr[u + 1]; ++q) {
-                const int d = G.nbr[q] - u;
-                if (d < -32768 || d > 32767) {
-                    fits[t] = 0;
-                    break;
-                }
-                nb16[q] = (short)d;
-            }
-    });
-    const bool rel = dmax <= 65535 &&
-                     std::all_of(fits.begin(), fits.end(), [](unsigned char f) { return f != 0; });
-    if (rel)
-        return greedy_groups<true, short, unsigned short>(n, G.ptr.data(), nb16.get(), dmax, color);
-    nb16.reset();
-    return greedy_groups<false, int, int>(n, G.ptr.data(), G.nbr.data(), dmax, color);
+    return greedy_groups(
+        n, dmax, [&G](int i) { return G.degree(i); },
+        [&G](int i, auto f) {
+            for (int q = G.ptr[i]; q < G.ptr[i + 1]; ++q) f(G.nbr[q]);
+        },
+        color);
 }
 
 int vertices_grouping_symmetric(int n, const int *rp, const int *ci, std::vector<int> &color,
                                 bool *diag_once)
 {
     if (diag_once) *diag_once = false;
-    // Off-diagonal lists straight from the pattern: when every row stores its
-    // diagonal exactly once, row u's neighbours go to [rp[u] - u,
-    // rp[u+1] - u - 1), ranges that are disjoint and cover [0, nnz - n).
-    // The groups of a bipartite graph come out of the greedy itself here (the
-    // closed form gives the same groups, only faster).
+    // Off-diagonal lists straight from the pattern when every row stores its
+    // diagonal exactly once and couples over less than 32,768 rows (a mesh
+    // numbering: larger graphs with longer couplings have an adjacency built,
+    // whose bipartite case has the closed form).  The groups of a bipartite graph come out of the
+    // greedy itself here (the closed form gives the same groups, only faster).
     if (n <= 0) return vertices_grouping(build_adjacency(n, rp, ci, true), color);
     const int parts = host_parts(n);
     std::vector<unsigned char> ok(parts, 1);
@@ -393,24 +369,17 @@ int vertices_grouping_symmetric(int n, const int *rp, const int *ci, std::vector
         }
         dpart[t] = dm;
     });
-    const int dmax = *std::max_element(dpart.begin(), dpart.end());
-    if (!std::all_of(ok.begin(), ok.end(), [](unsigned char f) { return f != 0; }) ||
-        dmax > 65535)
+    if (!std::all_of(ok.begin(), ok.end(), [](unsigned char f) { return f != 0; }))
         return vertices_grouping(build_adjacency(n, rp, ci, true), color);
     if (diag_once) *diag_once = true;
-    const long long nadj = (long long)rp[n] - n;
-    std::unique_ptr<int[]> aptr(new int[(size_t)n + 1]);
-    std::unique_ptr<short[]> nb16(new short[(size_t)std::max<long long>(nadj, 1)]);
-    for_chunks(n, parts, [&](int lo, int hi, int) {
-        for (int u = lo; u < hi; ++u) {
-            int q = rp[u] - u;
-            aptr[u] = q;
-            for (int e = rp[u]; e < rp[u + 1]; ++e)
-                if (ci[e] != u) nb16[q++] = (short)(ci[e] - u);
-        }
-    });
-    aptr[n] = (int)nadj;
-    return greedy_groups<true, short, unsigned short>(n, aptr.get(), nb16.get(), dmax, color);
+    return greedy_groups(
+        n, *std::max_element(dpart.begin(), dpart.end()),
+        [rp](int i) { return rp[i + 1] - rp[i] - 1; },
+        [rp, ci](int i, auto f) {
+            for (int e = rp[i]; e < rp[i + 1]; ++e)
+                if (ci[e] != i) f(ci[e]);
+        },
+        color);
 }
 
 static inline double entry(const Csr &A, int i, int j)

@@ -231,7 +231,7 @@ bool nd_dominant(int n, const int *rp, const int *ci, const double *val)
     return true;
 }
 
-bool nd_plan(int n, const int *rp, const int *ci, NdPlan &P)
+bool nd_plan(int n, const int *rp, const int *ci, NdPlan &P, bool known_symmetric)
 {
     P.clear();
     P.n = n;
@@ -239,7 +239,7 @@ bool nd_plan(int n, const int *rp, const int *ci, NdPlan &P)
     // with sorted rows, the lower entries of row j come up in order as the rows
     // above it are walked: a pattern that is not symmetric, or lacks a
     // diagonal, declines
-    {
+    if (!known_symmetric) {
         std::vector<int> cur(rp, rp + n);
         for (int i = 0; i < n; ++i) {
             int k = cur[i];

@@ -86,8 +86,9 @@ constexpr int kNdLongRow = 1024;
 // Builds the plan of a pattern (rp, ci: sorted rows).  False if the pattern
 // is not structurally symmetric with a full diagonal, or its graph does not
 // separate well enough: the natural-order solver then reads less or needs
-// less memory.
-bool nd_plan(int n, const int *rp, const int *ci, NdPlan &P);
+// less memory.  known_symmetric: the pattern is known to be structurally
+// symmetric and its diagonal full (it is not looked at again).
+bool nd_plan(int n, const int *rp, const int *ci, NdPlan &P, bool known_symmetric = false);
 // True if every row is strictly diagonally dominant by kNdMargin.
 bool nd_dominant(int n, const int *rp, const int *ci, const double *val);
 
