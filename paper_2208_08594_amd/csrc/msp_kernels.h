@@ -258,13 +258,16 @@ hipError_t launch_reduce_partials(int nv, int nblk, const double *partial, doubl
 // w -= sum_i h[i] V_i
 hipError_t launch_axpy_multi(long long N, int nv, const double *V, long long ldv,
                              const double *h, double *w, hipStream_t st);
-// Work-groups of the Gram-Schmidt and norm passes over N entries: four entries
-// per thread while that gives at most kDotBlocksFused work-groups (262,144
-// entries), whose last one then adds up the partials itself (one launch less
-// per pass), else kDotBlocks and a reduction launch.  Stretching the 256
-// work-groups over more entries costs more than the launch: 553,000 unknowns,
-// one FGMRES solve of 10 iterations 2.94 -> 3.20 ms.
-constexpr int kDotBlocksFused = 256;
+// Work-groups of the Gram-Schmidt and norm passes over N entries.  Up to
+// kGsFused entries: one per 1024, at most kGsBlocks, the last of which adds up
+// the partials itself (one launch less per pass); with fewer entries each that
+// sum only gets longer (32,000 unknowns, 256 instead of 1024: 72 -> 76 us an
+// iteration).  Beyond: kDotBlocks and a reduction launch, as a pass over up to 30
+// long vectors needs more waves in flight.  FGMRES iterations with 256
+// work-groups, and with 1024 and the launch: 552,960 unknowns 238 and 248 us,
+// 1,055,652 unknowns 381 and 374 us, 4,488,000 unknowns 1633 and 1425 us.
+constexpr int kGsBlocks = 256;
+constexpr long long kGsFused = 786432;
 int gs_blocks(long long N);
 // Where a pass's sums go: out (device); with host != nullptr also, with the
 // nhost doubles at src (out among them), to page-locked host memory.  ctr: an

@@ -10,6 +10,7 @@
 #include <vector>
 
 #include "msp_kernels.h"
+#include "msp_lanes.h"
 
 namespace msp {
 
@@ -18,13 +19,6 @@ namespace {
 constexpr int kThreads = 256;
 
 __device__ __forceinline__ bool finite_d(double v) { return __builtin_isfinite(v); }
-
-__device__ __forceinline__ double wave_sum(double v)
-{
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-    return v;
-}
 
 // Work-groups are dispatched to the 8 XCDs round-robin (work-group b to XCD
 // b mod 8), and each XCD has its own L2.  xcd_block maps the dispatch order
@@ -797,8 +791,8 @@ __device__ inline void sweep_row_lanes(const int4 *__restrict__ slices,
                 if (c[u] >= 0) sum += v[u] * xv[u];
         }
     }
-#pragma unroll
-    for (int o = RPW; o < 64; o <<= 1) sum += __shfl_xor(sum, o, 64);
+    static_assert(RPW == 8, "lanes of a row are 8 apart");
+    sum = sum_of_rows8(sum);
     if (live && j == 0) {
         if (RESIDUAL)
             r[row] = fr - (dr * xr + sum);
@@ -948,8 +942,8 @@ __global__ __launch_bounds__(64 * L) void k_gs_sweep(const int4 *__restrict__ sl
                 if (c[u] >= 0) sum += v[u] * xv;
             }
         }
-#pragma unroll
-        for (int o = RPW; o < 64; o <<= 1) sum += __shfl_xor(sum, o, 64);
+        static_assert(RPW == 8, "lanes of a row are 8 apart");
+        sum = sum_of_rows8(sum);
         if (live && j == 0) sweep_store(x + row, (fr - sum) / dr);
         if (threadIdx.x == 0) drawn[turn ^ 1] = ahead;
     }
@@ -1070,8 +1064,7 @@ __global__ __launch_bounds__(kThreads) void k_restrict_upper(
                 if (c[u] >= 0) s -= v[u] * xv[u];
         }
     }
-#pragma unroll
-    for (int o = 1; o < L; o <<= 1) s += __shfl_xor(s, o, 64);
+    s = group_sum<L>(s);
     if (J < nc && j == 0) {
         fc[J] = s;
         if (xc && J >= p0 && J < p1)
@@ -1785,13 +1778,18 @@ __global__ __launch_bounds__(kThreads) void k_dot_multi(long long N, int nv,
 // out[i] = sum over the nblk blocks of partial[b * nv + i]: one wave per
 // vector i (lane l adds blocks l, l + 64, ... in order, then a fixed
 // butterfly across the wave), so every sum has a fixed order.
+// COHERENT: the partials come from other work-groups of the same launch.
+template <bool COHERENT>
 __device__ __forceinline__ void sum_partials(int nv, int nblk, const double *partial, double *out,
                                              int nwaves)
 {
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     for (int i = wave; i < nv; i += nwaves) {
         double s = 0.0;
-        for (int b = lane; b < nblk; b += 64) s += partial[(long long)b * nv + i];
+        for (int b = lane; b < nblk; b += 64) {
+            const double *p = partial + (long long)b * nv + i;
+            s += COHERENT ? __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : *p;
+        }
         s = wave_sum(s);
         if (lane == 0) out[i] = s;
     }
@@ -1804,7 +1802,7 @@ __global__ __launch_bounds__(kReduceThreads) void k_reduce_partials(
     int nv, int nblk, const double *__restrict__ partial, double *out, const double *src,
     int nhost, double *host)
 {
-    sum_partials(nv, nblk, partial, out, kReduceThreads / 64);
+    sum_partials<false>(nv, nblk, partial, out, kReduceThreads / 64);
     if (host) {
         __syncthreads();
         for (int q = threadIdx.x; q < nhost; q += kReduceThreads) host[q] = src[q];
@@ -1813,19 +1811,26 @@ __global__ __launch_bounds__(kReduceThreads) void k_reduce_partials(
 
 // The reduction of a pass's partial sums by the last of its work-groups to
 // finish (ctr: zero before the pass, and again after it), instead of a launch
-// of its own: for grids of at most kDotBlocksFused work-groups, whose partials
-// one work-group reads in a few microseconds.
+// of its own.  The partials go past the XCD's L2 (store_partial) and are
+// complete before the work-group counts itself: a fence over all of its writes
+// would flush and empty that L2 once per work-group (FGMRES iteration with
+// fences, without: 69,120 unknowns 103 -> 88 us, 245,760 186 -> 145 us).
+__device__ __forceinline__ void store_partial(double *p, double v)
+{
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
 __device__ __forceinline__ void reduce_in_last_block(int nv, const double *partial,
                                                      const GsTail &t)
 {
     __shared__ int last;
-    __threadfence();  // this work-group's partials, before it counts itself
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this wave's partials have arrived
     __syncthreads();
-    if (threadIdx.x == 0) last = atomicAdd(t.ctr, 1) == (int)gridDim.x - 1;
+    if (threadIdx.x == 0)
+        last = __hip_atomic_fetch_add(t.ctr, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ==
+               (int)gridDim.x - 1;
     __syncthreads();
     if (!last) return;
-    __threadfence();  // the others' partials
-    sum_partials(nv, gridDim.x, partial, t.out, kThreads / 64);
+    sum_partials<true>(nv, gridDim.x, partial, t.out, kThreads / 64);
     if (threadIdx.x == 0) *t.ctr = 0;
     if (t.host) {
         __syncthreads();
@@ -1906,8 +1911,9 @@ __global__ __launch_bounds__(kThreads) void k_gs_pass(long long N, const double 
     }
     __syncthreads();
     if (threadIdx.x < NOUT)
-        partial[(long long)blockIdx.x * NOUT + threadIdx.x] =
-            (red[0][threadIdx.x] + red[1][threadIdx.x]) + (red[2][threadIdx.x] + red[3][threadIdx.x]);
+        store_partial(partial + (long long)blockIdx.x * NOUT + threadIdx.x,
+                      (red[0][threadIdx.x] + red[1][threadIdx.x]) +
+                          (red[2][threadIdx.x] + red[3][threadIdx.x]));
     if (tail.ctr) reduce_in_last_block(NOUT, partial, tail);
 }
 
@@ -1939,8 +1945,9 @@ __global__ __launch_bounds__(kThreads) void k_norm2(long long N, const double *_
     }
     __syncthreads();
     if ((int)threadIdx.x < nv)
-        partial[(long long)blockIdx.x * nv + threadIdx.x] =
-            (red[0][threadIdx.x] + red[1][threadIdx.x]) + (red[2][threadIdx.x] + red[3][threadIdx.x]);
+        store_partial(partial + (long long)blockIdx.x * nv + threadIdx.x,
+                      (red[0][threadIdx.x] + red[1][threadIdx.x]) +
+                          (red[2][threadIdx.x] + red[3][threadIdx.x]));
     if (tail.ctr) reduce_in_last_block(nv, partial, tail);
 }
 
@@ -3047,8 +3054,8 @@ hipError_t launch_reduce_partials(int nv, int nblk, const double *partial, doubl
 
 int gs_blocks(long long N)
 {
-    const long long b = (N + 1023) / 1024;
-    return b <= kDotBlocksFused ? (int)std::max<long long>(b, 1) : kDotBlocks;
+    if (N > kGsFused) return kDotBlocks;
+    return (int)std::max<long long>(1, std::min<long long>((N + 1023) / 1024, kGsBlocks));
 }
 
 static unsigned stream_blocks(long long N)
@@ -3095,7 +3102,7 @@ hipError_t launch_gs_pass(int mode, long long N, int nv, const double *V, long l
                           hipStream_t st)
 {
     if (nv < 1 || nv > kFusedGsMax) return hipErrorInvalidValue;
-    const bool fused = gs_blocks(N) <= kDotBlocksFused;
+    const bool fused = N <= kGsFused;
     GsTail t = tail;
     if (!fused) t.ctr = nullptr;
     hipError_t e = hipErrorInvalidValue;
@@ -3110,15 +3117,14 @@ hipError_t launch_gs_pass(int mode, long long N, int nv, const double *V, long l
 hipError_t launch_norm2(long long N, const double *x, const double *first, double *partial,
                         const GsTail &tail, hipStream_t st)
 {
-    const int nb = gs_blocks(N);
-    const bool fused = nb <= kDotBlocksFused;
+    const bool fused = N <= kGsFused;
     GsTail t = tail;
     if (!fused) t.ctr = nullptr;
-    k_norm2<<<nb, kThreads, 0, st>>>(N, x, first, partial, t);
+    k_norm2<<<gs_blocks(N), kThreads, 0, st>>>(N, x, first, partial, t);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess || fused) return e;
-    return launch_reduce_partials(first ? 2 : 1, nb, partial, tail.out, tail.src, tail.nhost,
-                                  tail.host, st);
+    return launch_reduce_partials(first ? 2 : 1, gs_blocks(N), partial, tail.out, tail.src,
+                                  tail.nhost, tail.host, st);
 }
 
 __global__ void k_clear_i32(int *x)

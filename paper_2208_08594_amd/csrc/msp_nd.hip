@@ -6,6 +6,7 @@
 #include <algorithm>
 #include <type_traits>
 
+#include "msp_lanes.h"
 #include "msp_nd_device.h"
 
 namespace msp {
@@ -578,13 +579,6 @@ __global__ __launch_bounds__(kThreads) void k_nd_scale(NdDev d, const int4 *__re
 // x = W t.  Rows of Y by falling length: the nlong longest take a work-group
 // each (four waves share the row), the rest a wavefront each.
 // ---------------------------------------------------------------------------
-__device__ __forceinline__ double nd_wave_sum(double v)
-{
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-    return v;
-}
-
 template <typename T>
 __global__ __launch_bounds__(kThreads) void k_nd_lower(int n, int nlong,
                                                        const int4 *__restrict__ rows,
@@ -608,7 +602,7 @@ __global__ __launch_bounds__(kThreads) void k_nd_lower(int n, int nlong,
         acc += v.x * (double)fv[j] + v.y * (double)fv[j + 1];
     }
     if ((d.z & 1) && lane == 0 && (!wide || wave == 0)) acc += y[d.z - 1] * (double)fv[d.z - 1];
-    acc = nd_wave_sum(acc);
+    acc = wave_sum(acc);
     if (wide) {
         if (lane == 0) red[wave] = acc;
         __syncthreads();
@@ -638,7 +632,7 @@ __global__ __launch_bounds__(kThreads) void k_nd_upper(int n, const int4 *__rest
         const double2 v = *reinterpret_cast<const double2 *>(w + j);
         acc += v.x * t[cm[j]] + v.y * t[cm[j + 1]];
     }
-    acc = nd_wave_sum(acc);
+    acc = wave_sum(acc);
     if (lane == 0) x[map ? map[row] : row] = (T)acc;
 }
 

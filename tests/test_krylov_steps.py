@@ -20,9 +20,11 @@ def true_residual(sys_, x):
     return np.linalg.norm(sys_.rhs - A @ x) / np.linalg.norm(sys_.rhs)
 
 
-# unknowns: 1, 257, 1,024 and 1,025, one below, at and above 256 work-groups of 1,024
+# unknowns: 1, 257, 1,024 and 1,025, near 256 work-groups of 1,024, and below, at
+# and above the largest vector whose passes add up their own partials
 SMALL = [((1, 1, 1), 1), ((257, 1, 1), 1), ((16, 8, 8), 1), ((41, 25, 1), 1)]
-LARGE = [((64, 64, 32), 2), ((61, 61, 35), 2), ((64, 64, 64), 1), ((65, 64, 64), 1)]
+LARGE = [((64, 64, 32), 2), ((61, 61, 35), 2), ((64, 64, 64), 1), ((65, 64, 64), 1),
+         ((64, 64, 64), 3), ((64, 48, 51), 5), ((61, 73, 59), 3)]
 
 
 @pytest.mark.parametrize("dims,b,restart", [(d, b, m) for d, b in SMALL for m in (1, 5, 30, 40)] +
