@@ -96,10 +96,17 @@ struct ApplyIo {
     double *z;
 };
 hipError_t launch_set_io(ApplyIo *io, const double *v, double *z, hipStream_t st);
+// A new basis vector v = w / sqrt(*s2), formed by the first kernel of the apply
+// that reads it.
+struct UnitScale {
+    const double *w = nullptr, *s2 = nullptr;
+    double *v = nullptr;
+};
 template <typename T>
 hipError_t launch_decouple_restrict(int b, int n, const int *iperm0, const double *omega,
                                     const double *v, const ApplyIo *io, T *g, int p0, int p1,
-                                    const T *diag, T *x, hipStream_t st);
+                                    const T *diag, T *x, hipStream_t st,
+                                    const UnitScale *sc = nullptr);
 template <typename T>
 hipError_t launch_gs_first(const SellView &seg0, int npos, const T *diag, const T *f, T *x,
                            int seg0_begin, int seg0_end, hipStream_t st);

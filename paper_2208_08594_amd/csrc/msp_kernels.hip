@@ -624,23 +624,32 @@ __global__ __launch_bounds__(64 * B) void k_spmv_rows(const int4 *__restrict__ s
 // ---------------------------------------------------------------------------
 // preconditioner kernels
 // ---------------------------------------------------------------------------
-template <int B, typename T>
-__global__ __launch_bounds__(kThreads) void k_decouple_restrict(int n,
-                                                                const int *__restrict__ iperm0,
-                                                                const double *__restrict__ omega,
-                                                                const double *v,
-                                                                const ApplyIo *io,
-                                                                T *__restrict__ g, int p0, int p1,
-                                                                const T *__restrict__ diag,
-                                                                T *__restrict__ x)
+// SCALE: also k_scale ahead of it, v = w / sqrt(s2) formed and written here.
+template <int B, typename T, bool SCALE>
+__global__ __launch_bounds__(kThreads) void k_decouple_restrict(
+    int n, const int *__restrict__ iperm0, const double *__restrict__ omega, const double *v,
+    const ApplyIo *io, UnitScale sc, T *__restrict__ g, int p0, int p1,
+    const T *__restrict__ diag, T *__restrict__ x)
 {
     int t = blockIdx.x * kThreads + threadIdx.x;
     if (t >= n) return;
     if (io) v = io->v;
     const long long c = iperm0[t];
+    double vc[B];
+    if (SCALE) {
+        const double s = sqrt(*sc.s2);
+#pragma unroll
+        for (int k = 0; k < B; ++k) {
+            vc[k] = sc.w[c * B + k] / s;
+            sc.v[c * B + k] = vc[k];
+        }
+    } else {
+#pragma unroll
+        for (int k = 0; k < B; ++k) vc[k] = v[c * B + k];
+    }
     double acc = 0.0;
 #pragma unroll
-    for (int k = 0; k < B; ++k) acc += omega[c * B + k] * v[c * B + k];
+    for (int k = 0; k < B; ++k) acc += omega[c * B + k] * vc[k];
     const T gt = (T)acc;
     g[t] = gt;
     // with x: also the first color of a forward sweep from x = 0 (k_gs_first)
@@ -2585,10 +2594,15 @@ hipError_t launch_set_io(ApplyIo *io, const double *v, double *z, hipStream_t st
 template <typename T>
 hipError_t launch_decouple_restrict(int b, int n, const int *iperm0, const double *omega,
                                     const double *v, const ApplyIo *io, T *g, int p0, int p1,
-                                    const T *diag, T *x, hipStream_t st)
+                                    const T *diag, T *x, hipStream_t st, const UnitScale *sc)
 {
-    MSP_SWITCH_B(b, (k_decouple_restrict<B, T><<<blocks_for(n), kThreads, 0, st>>>(
-                        n, iperm0, omega, v, io, g, p0, p1, diag, x)));
+    if (sc) {
+        MSP_SWITCH_B(b, (k_decouple_restrict<B, T, true><<<blocks_for(n), kThreads, 0, st>>>(
+                            n, iperm0, omega, v, io, *sc, g, p0, p1, diag, x)));
+    } else {
+        MSP_SWITCH_B(b, (k_decouple_restrict<B, T, false><<<blocks_for(n), kThreads, 0, st>>>(
+                            n, iperm0, omega, v, io, UnitScale(), g, p0, p1, diag, x)));
+    }
     return hipGetLastError();
 }
 
@@ -2982,7 +2996,8 @@ hipError_t launch_from_double(long long n, const double *x, T *y, hipStream_t st
 #define MSP_INSTANTIATE(T)                                                                     \
     template hipError_t launch_decouple_restrict<T>(int, int, const int *, const double *,     \
                                                     const double *, const ApplyIo *, T *, int, \
-                                                    int, const T *, T *, hipStream_t);         \
+                                                    int, const T *, T *, hipStream_t,          \
+                                                    const UnitScale *);                        \
     template hipError_t launch_gs_first<T>(const SellView &, int, const T *, const T *, T *,   \
                                            int, int, hipStream_t);                             \
     template hipError_t launch_gs_color<T>(const SellView &, const T *, const T *, const T *,  \

@@ -77,6 +77,23 @@ def test_initial_guess_and_exact_start():
     g.close()
 
 
+@pytest.mark.parametrize("dims,b,opt", [
+    ((5, 4, 3), 1, {}), ((10, 10, 10), 4, {}), ((24, 20, 11), 7, {"precond_fp32": True}),
+    ((17, 13, 9), 3, {"bilu_order": 0}), ((17, 13, 9), 3, {"n_stage": 1}),
+    ((61, 73, 59), 3, {})])
+def test_scaled_basis_vector(dims, b, opt):
+    """A new basis vector scaled inside the apply, and (as with events recorded
+    around the parts) by a launch ahead of it: the same solve bit for bit."""
+    s = synth.lognormal_grid(*dims, b, 3, 1.0, 1.0, "none")
+    g = msp.Solver(**opt)
+    g.setup(s)
+    x, info = g.solve(s.rhs, rtol=1e-9)
+    g.set_timing(True)
+    y, info2 = g.solve(s.rhs, rtol=1e-9)
+    assert info["iterations"] == info2["iterations"] and torch.equal(x, y)
+    g.close()
+
+
 @pytest.mark.parametrize("fp32", [False, True])
 def test_captured_apply(fp32):
     """An apply of many launches is replayed from a graph: every replay equals
