@@ -3,7 +3,8 @@
  * of the hot path on the context's current matrix / preconditioner so that it
  * can be checked and timed on its own.  Same conventions as msp.h (device
  * pointers unless "host", synchronous on return, negative = error).
- * All of them return MSP_ERR_STATE before a successful msp_setup.
+ * All that need a preconditioner return MSP_ERR_STATE before a successful
+ * msp_setup.
  */
 #ifndef MSP_STAGES_H
 #define MSP_STAGES_H
@@ -118,6 +119,16 @@ int msp_stage_set_timing(msp_ctx *ctx, int on);
  * updates, norm); calls[i] the number of steps summed.  Zero when timing was
  * off.  Errors: MSP_ERR_ARG (a NULL pointer). */
 int msp_stage_get_timing(msp_ctx *ctx, double *ms, int *calls);
+
+/* Limits of a context's bounded waits, for tests of what follows when one runs
+ * out; value 0 restores the library's own.
+ * MSP_LIMIT_MATCH_LOOKS: looks of a row of the pairwise matching at undecided
+ * rows before the row is left to another run of the matching (the result is
+ * the same for every value). */
+#define MSP_LIMIT_MATCH_LOOKS 0
+/* Sets one limit for the later calls on the context.  Errors: MSP_ERR_ARG (ctx
+ * NULL, unknown limit, value < 0). */
+int msp_stage_set_limit(msp_ctx *ctx, int limit, int value);
 
 #ifdef __cplusplus
 }

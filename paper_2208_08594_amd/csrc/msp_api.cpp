@@ -228,6 +228,7 @@ struct msp_ctx {
     // optional HIP-event timing of the solve's parts (SpMV, preconditioner
     // apply, Gram-Schmidt step): summed ms and counts over the last solve
     bool timing = false;
+    int match_looks = kMatchLooks;  // msp_stage_set_limit
     hipEvent_t tev[4] = {nullptr, nullptr, nullptr, nullptr};
     hipEvent_t ev_step[2] = {nullptr, nullptr};  // ends of the solve's last two queued steps
     double t_ms[kTimedParts] = {0, 0, 0};
@@ -1241,7 +1242,7 @@ void rebuild_B(msp_ctx *c, const double *vals, bool nd_ok = true)
             [&a0_ready]() { a0_ready.get(); }, c->stream, c->chain_copy,
             [c, &tmp](size_t bytes) { return c->dalloc(bytes, tmp); }, fail_hip, c->chain_host,
             [c](int l, size_t bytes) { return chain_staging(c, l, bytes); }, &last.rp, &last.ci,
-            &last.val);
+            &last.val, c->match_looks);
     }
     if (st == 1) {
         last = LevelCsr();
@@ -2781,6 +2782,16 @@ int msp_stage_repeat(msp_ctx *c, int stage, int reps, const double *in, double *
         c->sync();
         return MSP_OK;
     });
+}
+
+int msp_stage_set_limit(msp_ctx *c, int limit, int value)
+{
+    if (!c || value < 0) return MSP_ERR_ARG;
+    switch (limit) {
+    case MSP_LIMIT_MATCH_LOOKS: c->match_looks = value ? value : kMatchLooks; break;
+    default: return MSP_ERR_ARG;
+    }
+    return MSP_OK;
 }
 
 }  // extern "C"

@@ -35,6 +35,10 @@ using PinnedBuffer = std::function<void *(int l, size_t bytes)>;
 // Called with every HIP error; must not return (it throws).
 using HipFail = void (*)(hipError_t);
 
+// Looks of a row at undecided rows before the matching kernel gives it up and is
+// run again (about 15 ms).
+constexpr int kMatchLooks = 32768;
+
 // Builds the hierarchy of A0 on `st`.  A0 is the host copy of level 0 and
 // rp0/ci0/val0 the same matrix in device memory.  Same contract as
 // build_hierarchy (with_colors = false): H.A holds every level on the host,
@@ -57,6 +61,7 @@ using HipFail = void (*)(hipError_t);
 // rows) is finished on the host with absorb_singletons and galerkin, and its
 // coarse matrix uploaded.  last_rp, last_ci, last_val (if given) receive the
 // coarsest level on the device (in the chain's own memory, or level 0 itself).
+// looks (>= 1): see kMatchLooks.
 // Exclusive scan of in[0..n) in tiles of kScanTile entries: entry i's scan is
 // out[i] + tiles[i / kScanTile], *total the sum (tiles: scan_tiles(n) ints).
 constexpr int kScanTile = 1024;
@@ -74,6 +79,7 @@ int device_hierarchy(Csr &A0, const int *rp0, const int *ci0, const double *val0
                      hipStream_t st, hipStream_t copy_st,
                      const DeviceAlloc &alloc, HipFail hip_fail, int *pinned,
                      const PinnedBuffer &staging = nullptr, const int **last_rp = nullptr,
-                     const int **last_ci = nullptr, const double **last_val = nullptr);
+                     const int **last_ci = nullptr, const double **last_val = nullptr,
+                     int looks = kMatchLooks);
 
 }  // namespace msp

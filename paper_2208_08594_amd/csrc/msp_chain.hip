@@ -1,7 +1,7 @@
 // Aggregation chain of the AMG setup on the device (Sec. 5 hierarchy, the
 // pairwise rule of the host builder): strength and candidate lists per row,
-// the pairwise pass as rounds of locally first edges, the numbering of the
-// aggregates in creation order and the Galerkin product per coarse row.  The
+// the pairwise pass with every row waiting for the decisions of lower rows that
+// its own needs, the numbering of the aggregates in creation order and the Galerkin product per coarse row.  The
 // results equal the host chain bit for bit; msp_chain.h gives the argument.
 #include "msp_chain.h"
 
@@ -12,6 +12,8 @@
 #include <memory>
 #include <vector>
 
+#include "msp_match.h"
+
 // every sum and comparison below is a single IEEE operation, as on the host
 #pragma clang fp contract(off)
 
@@ -20,9 +22,6 @@ namespace {
 
 constexpr int kThreads = 256;
 static_assert(kScanTile == 4 * kThreads, "four elements per thread of a scan tile");
-// state word of a row in the matching: undecided, alone, taken by a lower
-// row, or ~j: it has taken row j
-constexpr int kFree = 0, kSingle = 1, kHigh = 2;
 
 inline unsigned nblocks(long long n, int per = kThreads)
 {
@@ -85,8 +84,6 @@ __global__ void k_strength(int n, const int *__restrict__ rp, const int *__restr
 // of both lists are also held inline in two records, so that the matching
 // loads a whole list at once; kOver in a record's first slot: the list is
 // longer.  Unused slots are -1.  The row's state word is cleared.
-constexpr int kRec = 4;
-constexpr int kOver = -2;
 __global__ void k_lists(int n, const int *__restrict__ rp, const int *__restrict__ ci,
                         const double *__restrict__ s, const double *__restrict__ smax,
                         const unsigned char *__restrict__ elig, int *__restrict__ lst,
@@ -141,30 +138,21 @@ __global__ void k_lists(int n, const int *__restrict__ rp, const int *__restrict
 }
 
 // The pairwise pass: every row decides for itself, in any order, what the
-// ascending pass decides when it visits the row.  Row v
-//  - is taken (kHigh) if some in-row has taken it;
-//  - otherwise, once all its in-rows are decided, takes the first candidate
-//    that no lower row has taken: a candidate j is known to be taken when one
-//    of j's in-rows below v has taken it, and known to be free when all of
-//    them are decided and none has; while neither is known, v waits;
-//  - stays alone when every candidate is taken.
-// A decision reads only state words of lower rows, each written once, so
-// stale reads only delay it and the result does not depend on the schedule.
-// The words of the work-group's own rows are held in LDS, those of lower
-// work-groups read with device-scope loads.  The vote keeps the wavefront's
-// lanes together, so that none spins ahead of a lane it waits for.  A thread
-// looks at most `polls` times; rows still undecided then are counted in *left
-// and the kernel is run again.  (Work-groups start in order and the lowest
-// undecided row can always decide, so a second run is rare.)
+// ascending pass decides when it visits the row (MatchRow).  The words of the
+// work-group's own rows are held in LDS, those of lower work-groups read with
+// device-scope loads.  The vote keeps the wavefront's lanes together, so that
+// none spins ahead of a lane it waits for.  A row gives up after `looks` looks
+// that found an undecided row; rows still undecided then are counted in *left
+// and the kernel is run again from their first entries.  Looks that go on along
+// a list are not counted (lists end): the lowest undecided row finds every row
+// that it asks about decided, so it decides in any run, however long its lists.
+// (Work-groups start in order, so a second run is rare.)
 // Work-groups of 256 or 512 rows are no faster (128x128x64 cells, all ten
 // passes: 8.7 and 8.4 ms, 8.1 with 1024), several rows per thread are slower
 // (a lane that starts on its next row stalls the others).
 constexpr int kMatchThreads = 1024;
-constexpr int kMatchPolls = 32768;
 __global__ void __launch_bounds__(kMatchThreads)
-k_match(int n, int polls, const int *__restrict__ rp, const int *__restrict__ lst,
-        const int *__restrict__ ncand, const int *__restrict__ nin, const int4 *__restrict__ rin,
-        const int4 *__restrict__ rcand, int *word, int *__restrict__ partner,
+k_match(int n, int looks, MatchLists<int4> L, int *word, int *__restrict__ partner,
         int *__restrict__ left)
 {
     __shared__ int own[kMatchThreads];
@@ -172,84 +160,22 @@ k_match(int n, int polls, const int *__restrict__ rp, const int *__restrict__ ls
     own[threadIdx.x] = v < n ? word[v] : kSingle;
     __syncthreads();
     bool open = own[threadIdx.x] == kFree;
-    // what v waits for: the in-rows below v of `target` (v itself, then its
-    // candidates in order), up to four entries at a time
-    int target = v, pos = -1, cq = -1, nc = 0;
-    int4 a = make_int4(-1, -1, -1, -1), cand = a, rec0 = a;
-    // the next entries, from number pos on, of a list longer than a record
-    const auto next = [&]() {
-        int r[4] = {-1, -1, -1, -1};
-        const int e = rp[target + 1], m = nin[target];
-#pragma unroll
-        for (int u = 0; u < 4; ++u)
-            while (pos < m && r[u] < 0) {
-                const int k = lst[e - 1 - pos++];
-                if (k < v) r[u] = k;
-            }
-        a = make_int4(r[0], r[1], r[2], r[3]);
+    MatchRow<int4> R;
+    if (open) R.start(L, v);
+    const auto state = [&](int k) -> int {
+        if (k < 0) return kSingle;
+        const int o = k - b0;  // (no row above v is read)
+        if (o >= 0)
+            return __hip_atomic_load(&own[o], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        return __hip_atomic_load(word + k, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     };
-    const auto begin = [&](const int4 rec) {
-        pos = -1;
-        a = rec;
-        if (rec.x == kOver) {
-            pos = 0;
-            next();
-        } else {
-            if (a.x >= v) a.x = -1;
-            if (a.y >= v) a.y = -1;
-            if (a.z >= v) a.z = -1;
-            if (a.w >= v) a.w = -1;
-        }
-    };
-    if (open) {
-        cand = rcand[v];
-        nc = ncand[v];
-        begin(rin[v]);
-        if (cand.x >= 0) rec0 = rin[cand.x];  // (read ahead)
-    }
-    for (int it = 0; it < polls && __any(open); ++it) {
-        if (!open) continue;
-        const auto state = [&](int k) -> int {
-            if (k < 0) return kSingle;
-            const int o = k - b0;  // (no row above v is read)
-            if (o >= 0)
-                return __hip_atomic_load(&own[o], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-            return __hip_atomic_load(word + k, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        };
-        const int w0 = state(a.x), w1 = state(a.y), w2 = state(a.z), w3 = state(a.w);
-        int by = -1;  // the row that has taken the target
-        if (w0 == ~target) by = a.x;
-        if (w1 == ~target) by = a.y;
-        if (w2 == ~target) by = a.z;
-        if (w3 == ~target) by = a.w;
-        if (w0 != kFree) a.x = -1;
-        if (w1 != kFree) a.y = -1;
-        if (w2 != kFree) a.z = -1;
-        if (w3 != kFree) a.w = -1;
-        if (by < 0) {
-            if ((a.x & a.y & a.z & a.w) != -1) continue;
-            if (pos >= 0) {
-                next();
-                if ((a.x & a.y & a.z & a.w) != -1) continue;
-            }
-        }
-        int dec = kFree;
-        if (cq < 0 && by >= 0) {
-            partner[v] = by;
-            dec = kHigh;
-        } else if (cq >= 0 && by < 0) {
-            dec = ~target;  // no lower row took this candidate
-        } else if (++cq == nc) {
-            dec = kSingle;
-        } else {
-            target = cand.x == kOver ? lst[rp[v] + cq]
-                     : cq == 0       ? cand.x
-                     : cq == 1       ? cand.y
-                     : cq == 2       ? cand.z
-                                     : cand.w;
-            begin(cq == 0 && cand.x != kOver ? rec0 : rin[target]);
-        }
+    for (int waited = 0; __any(open && waited < looks);) {
+        if (!open || waited >= looks) continue;
+        bool waits;
+        const int dec = R.look(L, state, waits);
+        waited += waits;
         if (dec != kFree) {
+            if (dec == kHigh) partner[v] = R.by;
             __hip_atomic_store(&own[threadIdx.x], dec, __ATOMIC_RELAXED,
                                __HIP_MEMORY_SCOPE_WORKGROUP);
             __hip_atomic_store(word + v, dec, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -438,6 +364,7 @@ struct Chain {
     hipStream_t st = nullptr;
     HipFail hip_fail = nullptr;
     int *pinned = nullptr;
+    int looks = kMatchLooks;
     hipEvent_t ev_lvl = nullptr;  // a new level is on the device
     // work arrays, sized for level 0 (no later matrix is larger)
     double *s = nullptr, *cs = nullptr, *smax = nullptr;
@@ -498,7 +425,8 @@ struct Chain {
             if (run > (long long)n + 1) hip_fail(hipErrorUnknown);
             fill(ctr + 1, 0, 1);
             k_match<<<nblocks(n, kMatchThreads), kMatchThreads, 0, st>>>(
-                n, kMatchPolls, L.rp, lst, ncand, nin, rin, rcand, word, partner, ctr + 1);
+                n, looks, MatchLists<int4>{L.rp, lst, ncand, nin, rin, rcand}, word, partner,
+                ctr + 1);
             launched();
             scan<true>(word, pos, ctr, n);
             k_number<<<nblocks(n), kThreads, 0, st>>>(n, word, partner, pos, tiles, agg, mem0, mem1);
@@ -609,7 +537,7 @@ int device_hierarchy(Csr &A0, const int *rp0, const int *ci0, const double *val0
                      hipStream_t st, hipStream_t copy_st,
                      const DeviceAlloc &alloc, HipFail hip_fail, int *pinned,
                      const PinnedBuffer &staging, const int **last_rp, const int **last_ci,
-                     const double **last_val)
+                     const double **last_val, int looks)
 {
     const auto report = [&](const int *rp, const int *ci, const double *val) {
         if (last_rp) *last_rp = rp;
@@ -629,6 +557,7 @@ int device_hierarchy(Csr &A0, const int *rp0, const int *ci0, const double *val0
     X.st = st;
     X.hip_fail = hip_fail;
     X.pinned = pinned;
+    X.looks = looks;
     EventGuard guard{&X.ev_lvl};
     X.ck(hipEventCreateWithFlags(&X.ev_lvl, hipEventDisableTiming));
     // one allocation for every work array

@@ -87,9 +87,12 @@ SIGNATURES = {
     "msp_stage_get_nstage": ([_vp, _vp, _vp], _i),
     "msp_stage_set_timing": ([_vp, _i], _i),
     "msp_stage_get_timing": ([_vp, C.POINTER(_d), C.POINTER(_i)], _i),
+    "msp_stage_set_limit": ([_vp, _i, _i], _i),
 }
 STAGE_SPMV, STAGE_GS0, STAGE_PRECOND, STAGE_BILU, STAGE_VCYCLE, STAGE_COARSE, STAGE_TRI_SWEEP = \
     range(7)
+
+LIMIT_MATCH_LOOKS = 0
 
 _LIB = None
 _LOCK = threading.Lock()
@@ -318,6 +321,10 @@ class Solver:
         calls = (C.c_int * 3)()
         _check(self._lib.msp_stage_get_timing(self.h, ms, calls), "get_timing")
         return {k: (ms[i], calls[i]) for i, k in enumerate(("spmv", "apply", "gram_schmidt"))}
+
+    def set_limit(self, limit, value):
+        """msp_stage_set_limit: a bounded wait's limit (0: the library's own)."""
+        _check(self._lib.msp_stage_set_limit(self.h, int(limit), int(value)), "set_limit")
 
     @property
     def nlevels(self):
