@@ -50,6 +50,8 @@ extern "C" {
 #define MSP_ERR_COARSE (-9)    /* coarsening stalled above the dense coarsest-level limit */
 #define MSP_ERR_SCRATCH (-10)  /* msp_solve_noalloc: the FGMRES workspace of this system does
                                   not fit MSP_NOALLOC_SCRATCH_BYTES */
+#define MSP_ERR_STALL (-11)    /* a kernel's bounded wait for values of the same launch ran out;
+                                  the results of the call are not valid */
 #define MSP_NOT_CONVERGED 1    /* max_iter reached; x holds the last iterate, info is filled */
 
 #define MSP_MAX_LEVELS 25
@@ -179,7 +181,8 @@ int msp_setup(struct msp_ctx *ctx, int n_block_rows, int block_size, int pressur
  *   info may be NULL (host).
  * rhs = 0 gives x = 0 after 0 iterations.  Returns MSP_OK,
  * MSP_NOT_CONVERGED (x = last iterate), MSP_ERR_STATE (no setup),
- * MSP_ERR_NONFINITE (rhs), MSP_ERR_ARG, MSP_ERR_HIP. */
+ * MSP_ERR_NONFINITE (rhs), MSP_ERR_STALL (x = last iterate), MSP_ERR_ARG,
+ * MSP_ERR_HIP. */
 int msp_solve(struct msp_ctx *ctx, const double *rhs, double *x, double rtol, msp_info *info);
 
 /* k FGMRES solves of Sec. 5 (as msp_solve), one per context, advanced

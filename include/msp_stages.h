@@ -126,6 +126,9 @@ int msp_stage_get_timing(msp_ctx *ctx, double *ms, int *calls);
  * rows before the row is left to another run of the matching (the result is
  * the same for every value). */
 #define MSP_LIMIT_MATCH_LOOKS 0
+/* MSP_LIMIT_SWEEP_POLLS: looks at a pending value in the sweeps that run as one
+ * launch; a wait that needs more ends the call with MSP_ERR_STALL. */
+#define MSP_LIMIT_SWEEP_POLLS 1
 /* Sets one limit for the later calls on the context.  Errors: MSP_ERR_ARG (ctx
  * NULL, unknown limit, value < 0). */
 int msp_stage_set_limit(msp_ctx *ctx, int limit, int value);

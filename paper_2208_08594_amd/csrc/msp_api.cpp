@@ -228,7 +228,7 @@ struct msp_ctx {
     // optional HIP-event timing of the solve's parts (SpMV, preconditioner
     // apply, Gram-Schmidt step): summed ms and counts over the last solve
     bool timing = false;
-    int match_looks = kMatchLooks;  // msp_stage_set_limit
+    int match_looks = kMatchLooks, sweep_polls = kSweepPolls;  // msp_stage_set_limit
     hipEvent_t tev[4] = {nullptr, nullptr, nullptr, nullptr};
     hipEvent_t ev_step[2] = {nullptr, nullptr};  // ends of the solve's last two queued steps
     double t_ms[kTimedParts] = {0, 0, 0};
@@ -294,6 +294,17 @@ struct msp_ctx {
     void clear_flag(int i = 0)
     {
         HIPCHK(hipMemsetAsync(flag + i, 0, sizeof(int), i == 0 ? stream : side));
+    }
+    // flag_host[kRanOut] is set by a kernel whose wait ran out; cleared while no
+    // work of the context is under way, read after the work has been waited for
+    static constexpr int kRanOut = 4;
+    SweepWait sweep_wait() const { return SweepWait{sweep_polls, flag_host + kRanOut}; }
+    void waits_begin() { __atomic_store_n(flag_host + kRanOut, 0, __ATOMIC_RELAXED); }
+    bool wait_ran_out() const { return __atomic_load_n(flag_host + kRanOut, __ATOMIC_ACQUIRE) != 0; }
+    int waits_end()
+    {
+        sync();
+        return wait_ran_out() ? MSP_ERR_STALL : MSP_OK;
     }
     bool fp32() const { return opt.precond_fp32 != 0; }
 };
@@ -1491,7 +1502,7 @@ void vcycle(msp_ctx *c, int l, bool first_done = false, T *nat = nullptr)
     if (L.sweep)
         HIPCHK(launch_gs_sweep<T>(L.S.all(), L.S.lay.seg_slice[1], true, lev_val<T>(L),
                                   lev_diag<T>(L), (const T *)L.f, nullptr, (T *)L.x, L.next,
-                                  L.sweep, c->stream));
+                                  L.sweep, c->sweep_wait(), c->stream));
     else
         smooth<T>(c, L, true, true, c->opt.nu_pre, first_done);
     // a smoothed coarse level whose pre-smoothing starts with a Gauss-Seidel
@@ -1519,7 +1530,7 @@ void vcycle(msp_ctx *c, int l, bool first_done = false, T *nat = nullptr)
                                        c->stream));
         HIPCHK(launch_gs_sweep<T>(L.S.all(), 0, false, lev_val<T>(L), lev_diag<T>(L),
                                   (const T *)L.f, (const T *)L.r, (T *)L.x, L.next + 1, L.sweep,
-                                  c->stream));
+                                  c->sweep_wait(), c->stream));
         return;
     }
     const bool fold = fold_prolong(c, L);
@@ -1546,7 +1557,7 @@ void bilu_solve(msp_ctx *c, T *y)
     if (D.sweep) {  // zout is written after this, by the apply's last kernel
         HIPCHK(launch_bilu_sweeps<T>(c->b, c->n, D.L.all(), D.fwd_vpos_d, Lv, D.U.all(),
                                      D.bwd_vpos_d, Uv, Dv, y, (T *)c->zout, D.next, D.sweep,
-                                     c->stream));
+                                     c->sweep_wait(), c->stream));
         return;
     }
     const int nf = D.L.nseg();
@@ -1832,6 +1843,7 @@ struct Fgmres {
     void start()
     {
         t0 = now_ms();
+        c->waits_begin();
         N = (long long)c->n * c->b;
         m = c->opt.restart;
         H.assign((size_t)(m + 1) * m, 0.0);
@@ -1917,6 +1929,7 @@ struct Fgmres {
     // The step just waited for is complete: do the host part, queue the next.
     void advance()
     {
+        if (c->wait_ran_out()) return finish(MSP_ERR_STALL);
         if (stage == kStart) {
             const double bn2 = host_slot(0)[1];
             if (!std::isfinite(bn2)) return finish(MSP_ERR_NONFINITE);
@@ -2230,7 +2243,7 @@ int msp_create(msp_ctx **ctx, const msp_options *opt)
         c->stream = (hipStream_t)o.stream;
         for (auto &e : c->ev_step) HIPCHK(hipEventCreateWithFlags(&e, hipEventDisableTiming));
         HIPCHK(hipHostMalloc((void **)&c->hhost, sizeof(double) * 1024, hipHostMallocDefault));
-        HIPCHK(hipHostMalloc((void **)&c->flag_host, sizeof(int) * 4, hipHostMallocDefault));
+        HIPCHK(hipHostMalloc((void **)&c->flag_host, sizeof(int) * 5, hipHostMallocDefault));
         HIPCHK(hipHostMalloc((void **)&c->chain_host, sizeof(int) * 16, hipHostMallocDefault));
         c->flag = (int *)c->dalloc(sizeof(int) * 4, c->allocW);
         c->wsN = -1;
@@ -2499,6 +2512,7 @@ const char *msp_status_string(int s)
     case MSP_ERR_COARSE: return "coarsest level exceeds the dense limit";
     case MSP_ERR_SCRATCH:
         return "the solve needs more than the fixed scratch of msp_solve_noalloc";
+    case MSP_ERR_STALL: return "a bounded wait on the device ran out";
     case MSP_NOT_CONVERGED: return "not converged within max_iter";
     default: return "unknown status";
     }
@@ -2521,9 +2535,9 @@ int msp_stage_precond(msp_ctx *c, const double *v, double *z)
     if (!c || !v || !z) return MSP_ERR_ARG;
     if (!c->hasB || !c->haveA) return MSP_ERR_STATE;
     return guarded([&]() {
+        c->waits_begin();
         apply(c, v, z);
-        c->sync();
-        return MSP_OK;
+        return c->waits_end();
     });
 }
 
@@ -2533,12 +2547,12 @@ int msp_stage_vcycle(msp_ctx *c, const double *f, double *e)
     if (!c || !f || !e) return MSP_ERR_ARG;
     if (!c->hasB) return MSP_ERR_STATE;
     return guarded([&]() {
+        c->waits_begin();
         if (c->fp32())
             stage_vcycle_T<float>(c, f, e);
         else
             stage_vcycle_T<double>(c, f, e);
-        c->sync();
-        return MSP_OK;
+        return c->waits_end();
     });
 }
 
@@ -2564,12 +2578,12 @@ int msp_stage_bilu(msp_ctx *c, const double *r, double *z)
     if (!c || !r || !z) return MSP_ERR_ARG;
     if (!c->hasB) return MSP_ERR_STATE;
     return guarded([&]() {
+        c->waits_begin();
         if (c->fp32())
             stage_bilu_T<float>(c, r, z);
         else
             stage_bilu_T<double>(c, r, z);
-        c->sync();
-        return MSP_OK;
+        return c->waits_end();
     });
 }
 
@@ -2722,6 +2736,7 @@ int msp_stage_repeat(msp_ctx *c, int stage, int reps, const double *in, double *
     if (!c->haveA || (stage != MSP_STAGE_SPMV && !c->hasB)) return MSP_ERR_STATE;
     if (stage == MSP_STAGE_GS0 && c->lev.size() < 2) return MSP_ERR_STATE;
     return guarded([&]() {
+        c->waits_begin();
         const bool f32 = c->fp32();
         if (stage == MSP_STAGE_TRI_SWEEP) {
             // the largest step of the triangular-inverse sweeps of the
@@ -2779,8 +2794,7 @@ int msp_stage_repeat(msp_ctx *c, int stage, int reps, const double *in, double *
             }
             }
         }
-        c->sync();
-        return MSP_OK;
+        return c->waits_end();
     });
 }
 
@@ -2789,6 +2803,10 @@ int msp_stage_set_limit(msp_ctx *c, int limit, int value)
     if (!c || value < 0) return MSP_ERR_ARG;
     switch (limit) {
     case MSP_LIMIT_MATCH_LOOKS: c->match_looks = value ? value : kMatchLooks; break;
+    case MSP_LIMIT_SWEEP_POLLS:
+        drop_graph(c);  // (holds the limit)
+        c->sweep_polls = value ? value - 1 : kSweepPolls;
+        break;
     default: return MSP_ERR_ARG;
     }
     return MSP_OK;

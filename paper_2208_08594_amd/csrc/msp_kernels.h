@@ -143,13 +143,22 @@ template <typename T>
 hipError_t launch_restrict_upper(int nc, int lanes, const int *ptr, const int *col, const T *val,
                                  const T *x, T *fc, int p0, int p1, const T *diag_c, T *xc,
                                  int *next, hipStream_t st);
+// The waits of a sweep in one launch: looks at a pending value before a wait
+// gives up (the sweep then goes on with wrong values, so that it ends), and where
+// that is reported (1, in page-locked host memory).
+struct SweepWait {
+    int polls;
+    int *ran_out;
+};
+constexpr int kSweepPolls = 1 << 20;  // about a second
 // The other colors of a forward sweep from zero (after launch_restrict_upper;
 // s0: first slice of the second color), or a backward sweep of all colors (s0
 // = 0, after launch_prolong_sweep), in one launch of at most `groups`
 // work-groups.  A level of kRowLanes lanes; next: a counter, zero.
 template <typename T>
 hipError_t launch_gs_sweep(const SellView &all, int s0, bool forward, const T *val, const T *diag,
-                           const T *f, const T *old, T *x, int *next, int groups, hipStream_t st);
+                           const T *f, const T *old, T *x, int *next, int groups,
+                           const SweepWait &wait, hipStream_t st);
 template <typename T>
 hipError_t launch_prolong_sweep(int n, const int *agg_pos, const T *xc, T *x, T *old,
                                 hipStream_t st);
@@ -222,7 +231,8 @@ hipError_t launch_bilu_bwd(int b, const SellView &U, const int *rows, const T *U
 template <typename T>
 hipError_t launch_bilu_sweeps(int b, int n, const SellView &L, const int *fwd_rows, const T *Lval,
                               const SellView &U, const int *bwd_rows, const T *Uval,
-                              const T *Dval, T *y, T *w, int *next, int groups, hipStream_t st);
+                              const T *Dval, T *y, T *w, int *next, int groups,
+                              const SweepWait &wait, hipStream_t st);
 // z_c = zz[zperm[c]] (zperm may be nullptr: natural order) + e_c at the
 // pressure entry (+ w1_c if w1 != nullptr).
 template <typename T>

@@ -833,7 +833,7 @@ __global__ __launch_bounds__(kThreads) void k_residual_lanes(
 // the dependencies, so a slice's rows depend only on slices drawn before it by
 // work-groups that run or have ended, and the first unfinished slice never
 // waits: every wait ends (the bound on the polls only keeps an error from
-// becoming a hang).  A value is its own flag: the output starts filled with a
+// becoming a hang, and such an error is reported).  A value is its own flag: the output starts filled with a
 // NaN pattern that no result has, and a row polls, past the caches of its own
 // XCD, the values it needs until none holds it.
 // ---------------------------------------------------------------------------
@@ -850,7 +850,6 @@ struct SweepWord<float> {
     static constexpr type pending = 0x7fa5a5a5u;
 };
 constexpr int kSweepCols = 4;  // entries of a row (and lane) per batch
-constexpr int kSweepPolls = 1 << 20;
 
 template <typename T>
 __device__ inline typename SweepWord<T>::type sweep_bits(T v)
@@ -875,6 +874,30 @@ __device__ inline void sweep_store(T *p, T v)
     __hip_atomic_store(reinterpret_cast<W *>(p), w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+// Looks again at the values of y that are pending, load(k) for y[k], until none
+// of the wavefront's is, or the wait runs out: that is reported.  (The test of
+// the polls stands between the vote and the loads: 64x64x32 cells, b = 4, natural
+// order, 653 us both ways without a report, 661 here, 725 with the test behind
+// the loads or the report behind the loop.)
+template <typename T, int K, class Load>
+__device__ inline void sweep_wait(typename SweepWord<T>::type (&y)[K], const SweepWait &wait,
+                                  const Load &load)
+{
+    for (int polls = 0;; ++polls) {
+        bool miss = false;
+#pragma unroll
+        for (int k = 0; k < K; ++k) miss |= y[k] == SweepWord<T>::pending;
+        if (!__any(miss)) return;
+        if (polls >= wait.polls) {
+            __hip_atomic_store(wait.ran_out, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+            return;
+        }
+#pragma unroll
+        for (int k = 0; k < K; ++k)
+            if (y[k] == SweepWord<T>::pending) y[k] = load(k);
+    }
+}
+
 // Gauss-Seidel sweep over the slices [s0, s1), colors ascending (forward, from
 // x = 0: entries of higher colors are skipped, the first color is in x
 // already) or descending (backward: entries of lower colors take `old`).  x
@@ -889,7 +912,8 @@ __global__ __launch_bounds__(64 * L) void k_gs_sweep(const int4 *__restrict__ sl
                                                      const T *__restrict__ val,
                                                      const T *__restrict__ diag,
                                                      const T *__restrict__ f,
-                                                     const T *__restrict__ old, T *x, int *next)
+                                                     const T *__restrict__ old, T *x, int *next,
+                                                     SweepWait wait)
 {
     constexpr int RPW = 64 / L, K = kSweepCols;
     using W = typename SweepWord<T>::type;
@@ -935,15 +959,7 @@ __global__ __launch_bounds__(64 * L) void k_gs_sweep(const int4 *__restrict__ sl
                 else if (BWD)
                     y[u] = sweep_bits(old[c[u]]);
             }
-            for (int polls = 0; polls < kSweepPolls; ++polls) {
-                bool miss = false;
-#pragma unroll
-                for (int u = 0; u < K; ++u) miss |= y[u] == SweepWord<T>::pending;
-                if (!__any(miss)) break;
-#pragma unroll
-                for (int u = 0; u < K; ++u)
-                    if (y[u] == SweepWord<T>::pending) y[u] = sweep_load(x + c[u]);
-            }
+            sweep_wait<T>(y, wait, [&](int u) { return sweep_load(x + c[u]); });
 #pragma unroll
             for (int u = 0; u < K; ++u) {
                 T xv;
@@ -1432,7 +1448,7 @@ __global__ __launch_bounds__(64 * B) void k_bilu_sweep(int nslices,
                                                        const int *__restrict__ rows,
                                                        const T *__restrict__ val,
                                                        const T *__restrict__ Dval, T *in, T *out,
-                                                       int *next)
+                                                       int *next, SweepWait wait)
 {
     constexpr int E = B * B, K = kSweepCols;
     using W = typename SweepWord<T>::type;
@@ -1479,16 +1495,8 @@ __global__ __launch_bounds__(64 * B) void k_bilu_sweep(int nslices,
 #pragma unroll
             for (int k = 0; k < K; ++k)
                 y[k] = c[k] >= 0 ? sweep_load(out + (long long)c[k] * B + r) : 0;
-            for (int polls = 0; polls < kSweepPolls; ++polls) {
-                bool miss = false;
-#pragma unroll
-                for (int k = 0; k < K; ++k) miss |= y[k] == SweepWord<T>::pending;
-                if (!__any(miss)) break;
-#pragma unroll
-                for (int k = 0; k < K; ++k)
-                    if (y[k] == SweepWord<T>::pending)
-                        y[k] = sweep_load(out + (long long)c[k] * B + r);
-            }
+            sweep_wait<T>(y, wait,
+                          [&](int k) { return sweep_load(out + (long long)c[k] * B + r); });
             if (k0) __syncthreads();
 #pragma unroll
             for (int k = 0; k < K; ++k) ys[k][r][lane] = y[k];
@@ -2710,16 +2718,17 @@ hipError_t launch_ru_fill(int n, int nc, const int *mem_ptr, const int *mem, con
 
 template <typename T>
 hipError_t launch_gs_sweep(const SellView &all, int s0, bool forward, const T *val, const T *diag,
-                           const T *f, const T *old, T *x, int *next, int groups, hipStream_t st)
+                           const T *f, const T *old, T *x, int *next, int groups,
+                           const SweepWait &wait, hipStream_t st)
 {
     const int s1 = all.slice_end, nb = std::min(s1 - s0, groups);
     if (nb <= 0) return hipSuccess;
     if (forward)
         k_gs_sweep<T, kRowLanes, false><<<nb, 64 * kRowLanes, 0, st>>>(
-            all.slices, all.col, s0, s1, val, diag, f, nullptr, x, next);
+            all.slices, all.col, s0, s1, val, diag, f, nullptr, x, next, wait);
     else
         k_gs_sweep<T, kRowLanes, true><<<nb, 64 * kRowLanes, 0, st>>>(
-            all.slices, all.col, s0, s1, val, diag, f, old, x, next);
+            all.slices, all.col, s0, s1, val, diag, f, old, x, next, wait);
     return hipGetLastError();
 }
 
@@ -2890,17 +2899,18 @@ hipError_t launch_bilu_bwd(int b, const SellView &U, const int *rows, const T *U
 template <typename T>
 hipError_t launch_bilu_sweeps(int b, int n, const SellView &L, const int *fwd_rows, const T *Lval,
                               const SellView &U, const int *bwd_rows, const T *Uval,
-                              const T *Dval, T *y, T *w, int *next, int groups, hipStream_t st)
+                              const T *Dval, T *y, T *w, int *next, int groups,
+                              const SweepWait &wait, hipStream_t st)
 {
     const long long N = (long long)n * b;
     const int nl = L.slice_end - L.slice_begin, nu = U.slice_end - U.slice_begin;
     k_sweep_begin<T><<<blocks_for(N), kThreads, 0, st>>>(N, w, next);
     MSP_SWITCH_B(b, (k_bilu_sweep<B, T, false><<<std::min(nl, groups), 64 * B, 0, st>>>(
                         nl, L.slices + L.slice_begin, L.col, fwd_rows, Lval, nullptr, y, w,
-                        next)));
+                        next, wait)));
     MSP_SWITCH_B(b, (k_bilu_sweep<B, T, true><<<std::min(nu, groups), 64 * B, 0, st>>>(
                         nu, U.slices + U.slice_begin, U.col, bwd_rows, Uval, Dval, w, y,
-                        next + 1)));
+                        next + 1, wait)));
     return hipGetLastError();
 }
 
@@ -3019,7 +3029,8 @@ hipError_t launch_from_double(long long n, const double *x, T *y, hipStream_t st
     template hipError_t launch_prolong_sweep<T>(int, const int *, const T *, T *, T *,         \
                                                 hipStream_t);                                  \
     template hipError_t launch_gs_sweep<T>(const SellView &, int, bool, const T *, const T *,  \
-                                           const T *, const T *, T *, int *, int, hipStream_t); \
+                                           const T *, const T *, T *, int *, int,              \
+                                           const SweepWait &, hipStream_t);                    \
     template hipError_t launch_jacobi_first<T>(int, T, const T *, const T *, T *, hipStream_t); \
     template hipError_t launch_jacobi_update<T>(int, T, const T *, const T *, T *, hipStream_t); \
     template hipError_t launch_zero<T>(int, T *, hipStream_t);                                 \
@@ -3035,7 +3046,8 @@ hipError_t launch_from_double(long long n, const double *x, T *y, hipStream_t st
                                            int, int, const T *, hipStream_t);                  \
     template hipError_t launch_bilu_sweeps<T>(int, int, const SellView &, const int *, const T *, \
                                               const SellView &, const int *, const T *,       \
-                                              const T *, T *, T *, int *, int, hipStream_t);  \
+                                              const T *, T *, T *, int *, int,                \
+                                              const SweepWait &, hipStream_t);                \
     template hipError_t launch_bilu_bwd<T>(int, const SellView &, const int *, const T *,      \
                                            const T *, T *, hipStream_t);                       \
     template hipError_t launch_finish<T>(int, int, int, const T *, const int *, const T *,     \

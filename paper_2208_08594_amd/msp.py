@@ -20,7 +20,7 @@ MSP_OK = 0
 MSP_NOT_CONVERGED = 1
 STATUS = {0: "OK", -1: "ERR_ARG", -2: "ERR_PATTERN", -3: "ERR_SINGULAR", -4: "ERR_NONFINITE",
           -5: "ERR_NOMEM", -6: "ERR_HIP", -7: "ERR_NO_DEVICE", -8: "ERR_STATE",
-          -9: "ERR_COARSE", -10: "ERR_SCRATCH", 1: "NOT_CONVERGED"}
+          -9: "ERR_COARSE", -10: "ERR_SCRATCH", -11: "ERR_STALL", 1: "NOT_CONVERGED"}
 NOALLOC_SCRATCH_BYTES = 128 << 20
 MAX_LEVELS = 25
 
@@ -92,7 +92,7 @@ SIGNATURES = {
 STAGE_SPMV, STAGE_GS0, STAGE_PRECOND, STAGE_BILU, STAGE_VCYCLE, STAGE_COARSE, STAGE_TRI_SWEEP = \
     range(7)
 
-LIMIT_MATCH_LOOKS = 0
+LIMIT_MATCH_LOOKS, LIMIT_SWEEP_POLLS = range(2)
 
 _LIB = None
 _LOCK = threading.Lock()
