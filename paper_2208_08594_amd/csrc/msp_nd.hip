@@ -325,12 +325,10 @@ template <int T>
 __device__ inline void nd_gj16(double (&x)[4], int li, int lk)
 {
     if constexpr (T < 16) {
-        // the pivot's reciprocal by two Newton steps on the hardware's estimate
-        // (within an ulp, which the setup's check of the solve covers)
-        const double pv0 = lane_value(x[T & 3], ((T >> 2) << 4) | T);
-        double rp = __builtin_amdgcn_rcp(pv0);
-        rp = fma(fma(-pv0, rp, 1.0), rp, rp);
-        rp = fma(fma(-pv0, rp, 1.0), rp, rp);
+        // (two Newton steps on the hardware's estimate save 1 us of 15.5 a block of
+        // 64 rows, but are a unit in the last place off for a few mantissas just
+        // below a power of two, which decoupled diagonals of nearly 1 do take)
+        const double rp = 1.0 / lane_value(x[T & 3], ((T >> 2) << 4) | T);
         const double f = __shfl(x[T & 3], ((T >> 2) << 4) | li, 64);  // column T, this row
         double pr[4];  // row T, this lane's columns
 #pragma unroll
@@ -349,7 +347,7 @@ __device__ inline void nd_gj16(double (&x)[4], int li, int lk)
 
 // Inverse of a pivot block in LDS, its first `rows` rows in use: the padding is
 // the identity and couples to nothing, so blocks of 16 rows beyond them are left
-// out (13 us for 64 rows, about 3 us less for each block).
+// out (14 us for 64 rows, about 3 us less for each block).
 __device__ inline void nd_invert64(double (*__restrict__ M)[kLdA], int rows)
 {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
