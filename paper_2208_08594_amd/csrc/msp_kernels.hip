@@ -39,22 +39,49 @@ inline unsigned blocks_for(long long work, int per_block = kThreads)
     return (unsigned)(b < 1 ? 1 : b);
 }
 
-// Block products and triangular levels of up to this many slices take a
-// work-group of B waves per slice, a wave per component (k_spmv_rows,
-// k_pcol_residual_rows, k_bilu_rows), larger ones a wave per slice.  With a wave
-// per slice the chip has less than two waves per SIMD at 2000 slices, and each
-// works through B B loads per entry in turn.  7-point grids, wave per slice ->
-// per component, the product and both triangular solves: 1000 rows, b = 4
-// 9.2 -> 4.8 and 19.0 -> 10.1 us, b = 7 82.7 -> 8.1 and 66.2 -> 16.5; 13,824
-// rows, b = 5 17.0 -> 6.7 and 41.4 -> 13.1; 133,263 rows (2082 slices), b = 3
-// 15.8 -> 14.2 and 24.5 -> 19.5, b = 7 114 -> 70 and 101 -> 78.  160,000 rows are
-// about even (b = 6: 60.2 -> 62.4 and 97.7 -> 69.9), and on 1,048,576 rows, bound
-// by bandwidth, the wave per slice is faster (b = 7: 492 and 560 us; 515 and
-// 573): it reads an x block once, not once per component.
-constexpr int kSplitSlices = 2500;
-inline bool rows_split(const SellView &v)
+// Block products, pressure-column residuals and triangular levels of few slices
+// take a work-group of B waves per slice, a wave per component (k_spmv_rows,
+// k_pcol_residual_rows, k_bilu_rows), others a wave per slice, four to a
+// work-group.  On small matrices a wave per slice leaves most of the chip idle
+// and works through B B loads per entry in turn: inside a solve, 1000 rows, the
+// product takes 11.8 us (6.9 with a wave per component) at b = 4 and 79 (10) at
+// b = 7.  On large ones it is bound by bandwidth and faster, as it reads an x
+// block once (1,048,576 rows, b = 7: 492 and 515 us).  Between the two its time
+// goes up in steps, where a work-group more per compute unit begins (1024 and
+// 2048 slices), the other's evenly, so they cross once in each step.  Products
+// inside FGMRES solves, us a wave per slice / per component:
+//   slices        1000      1250      1600      2000      2150      2500
+//   b = 4      16.3/15.7 21.0/18.0 22.5/22.3 25.0/26.5 32.7/28.8 34.4/32.4
+//   b = 6      32.1/28.7 38.5/37.4 42.0/46.0 47.0/56.2 63.5/62.3 65.9/70.5
+// The lines lie where both take the same time (sizes in steps of 50 slices for
+// products and residuals, of 100 a level for the solves).
+struct SplitRange {
+    int one, two;  // split up to `one` slices, and from 2049 to `two`
+};
+constexpr SplitRange kSplitProduct[9] = {{0, 0},       {2500, 2500}, {2500, 2500},
+                                         {1536, 2400}, {1600, 2500}, {1500, 2300},
+                                         {1350, 2200}, {2500, 2500}, {1850, 2350}};
+constexpr SplitRange kSplitSolve64[9] = {{0, 0},       {2500, 2500}, {2500, 2500},
+                                         {1600, 0},    {1550, 2350}, {1750, 2350},
+                                         {2500, 2500}, {1500, 0},    {1650, 2300}};
+constexpr SplitRange kSplitSolve32[9] = {{0, 0},       {2500, 2500}, {2500, 2500},
+                                         {2400, 2400}, {1300, 0},    {1200, 0},
+                                         {1200, 2200}, {1550, 2250}, {1500, 2350}};
+inline bool rows_split(const SellView &v, const SplitRange &r)
 {
-    return v.slice_end - v.slice_begin <= kSplitSlices;
+    const int s = v.slice_end - v.slice_begin;
+    return s <= r.one || (s > 2048 && s <= r.two);
+}
+// The residual reads one column of the blocks, in FP64 over the same lines as
+// the whole block: its lines lie lower.
+inline bool residual_split(const SellView &v, int b, bool f32)
+{
+    return v.slice_end - v.slice_begin <= (b <= 2 ? 2500 : f32 ? 2048 : 1500);
+}
+template <typename T>
+inline bool solve_split(const SellView &v, int b)
+{
+    return rows_split(v, sizeof(T) == 8 ? kSplitSolve64[b] : kSplitSolve32[b]);
 }
 inline unsigned slice_blocks(const SellView &v)
 {
@@ -2577,7 +2604,7 @@ hipError_t launch_spmv(int b, const SellView &A, const double *val, const double
 {
     unsigned nb = slice_blocks(A);
     if (!nb) return hipSuccess;
-    if (rows_split(A)) {
+    if (rows_split(A, kSplitProduct[b])) {
         MSP_SWITCH_B(b, (k_spmv_rows<B><<<A.slice_end - A.slice_begin, 64 * B, 0, st>>>(
                             A.slices, A.col, A.slice_begin, val, x, sub, y)));
         return hipGetLastError();
@@ -2824,7 +2851,7 @@ hipError_t launch_pcol_residual(int b, int p, const SellView &A, const double *v
 {
     unsigned nb = slice_blocks(A);
     if (!nb) return hipSuccess;
-    if (rows_split(A)) {
+    if (residual_split(A, b, pcol32 != nullptr)) {
         const int ns = A.slice_end - A.slice_begin;
         if (pcol32) {
             MSP_SWITCH_B(b, (k_pcol_residual_rows<B, T, true><<<ns, 64 * B, 0, st>>>(
@@ -2855,7 +2882,7 @@ hipError_t launch_bilu_fwd(int b, const SellView &L, const int *rows, const T *L
 {
     unsigned nb = slice_blocks(L);
     if (!nb) return hipSuccess;
-    if (rows_split(L)) {
+    if (solve_split<T>(L, b)) {
         const int ns = L.slice_end - L.slice_begin;
         if (Dval) {
             MSP_SWITCH_B(b, (k_bilu_rows<B, T, 1><<<ns, 64 * B, 0, st>>>(
@@ -2885,7 +2912,7 @@ hipError_t launch_bilu_bwd(int b, const SellView &U, const int *rows, const T *U
 {
     unsigned nb = slice_blocks(U);
     if (!nb) return hipSuccess;
-    if (rows_split(U)) {
+    if (solve_split<T>(U, b)) {
         MSP_SWITCH_B(b, (k_bilu_rows<B, T, 2><<<U.slice_end - U.slice_begin, 64 * B, 0, st>>>(
                             U.slices, U.col, U.slice_begin, rows, Uval, Dval, z, 0, 0)));
         return hipGetLastError();
