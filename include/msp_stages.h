@@ -120,6 +120,12 @@ int msp_stage_set_timing(msp_ctx *ctx, int on);
  * off.  Errors: MSP_ERR_ARG (a NULL pointer). */
 int msp_stage_get_timing(msp_ctx *ctx, double *ms, int *calls);
 
+/* Kernels of the graph that holds the captured preconditioner apply (HOST
+ * output); 0 while there is none: before the first apply of a regeneration, and
+ * where applies are launched kernel by kernel (use_graphs in msp.h).  Errors:
+ * MSP_ERR_ARG (a NULL pointer). */
+int msp_stage_apply_nodes(msp_ctx *ctx, int *nodes);
+
 /* Limits of a context's bounded waits, for tests of what follows when one runs
  * out; value 0 restores the library's own.
  * MSP_LIMIT_MATCH_LOOKS: looks of a row of the pairwise matching at undecided

@@ -205,6 +205,7 @@ struct msp_ctx {
     // streams and events of the coarsest-level solver
     GjLookAhead gj{};
     hipGraphExec_t apply_exec = nullptr;
+    int apply_nodes = 0;  // kernels in it
     // krylov workspace (allocated by the first msp_solve of a size)
     long long wsN = 0;
     int wsm = 0;
@@ -1660,7 +1661,10 @@ void capture_apply(msp_ctx *c)
     }
     c->stream = user;
     HIPCHK(hipStreamEndCapture(c->cap_stream, &g));
-    hipError_t e = hipGraphInstantiate(&c->apply_exec, g, nullptr, nullptr, 0);
+    size_t nodes = 0;
+    hipError_t e = hipGraphGetNodes(g, nullptr, &nodes);
+    if (e == hipSuccess) e = hipGraphInstantiate(&c->apply_exec, g, nullptr, nullptr, 0);
+    c->apply_nodes = (int)nodes;
     (void)hipGraphDestroy(g);
     if (e != hipSuccess) {
         c->apply_exec = nullptr;
@@ -2796,6 +2800,13 @@ int msp_stage_repeat(msp_ctx *c, int stage, int reps, const double *in, double *
         }
         return c->waits_end();
     });
+}
+
+int msp_stage_apply_nodes(msp_ctx *c, int *nodes)
+{
+    if (!c || !nodes) return MSP_ERR_ARG;
+    *nodes = c->apply_exec ? c->apply_nodes : 0;
+    return MSP_OK;
 }
 
 int msp_stage_set_limit(msp_ctx *c, int limit, int value)
