@@ -135,6 +135,10 @@ int msp_stage_apply_nodes(msp_ctx *ctx, int *nodes);
 /* MSP_LIMIT_SWEEP_POLLS: looks at a pending value in the sweeps that run as one
  * launch; a wait that needs more ends the call with MSP_ERR_STALL. */
 #define MSP_LIMIT_SWEEP_POLLS 1
+/* MSP_LIMIT_ND_REJECTS: not a wait: so many of the next nested-dissection
+ * factorisations of the coarsest level count as having failed their check, and
+ * the natural-order solver takes their place. */
+#define MSP_LIMIT_ND_REJECTS 2
 /* Sets one limit for the later calls on the context.  Errors: MSP_ERR_ARG (ctx
  * NULL, unknown limit, value < 0). */
 int msp_stage_set_limit(msp_ctx *ctx, int limit, int value);

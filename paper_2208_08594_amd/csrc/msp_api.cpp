@@ -230,6 +230,7 @@ struct msp_ctx {
     // apply, Gram-Schmidt step): summed ms and counts over the last solve
     bool timing = false;
     int match_looks = kMatchLooks, sweep_polls = kSweepPolls;  // msp_stage_set_limit
+    int nd_rejects = 0;  // likewise
     hipEvent_t tev[4] = {nullptr, nullptr, nullptr, nullptr};
     hipEvent_t ev_step[2] = {nullptr, nullptr};  // ends of the solve's last two queued steps
     double t_ms[kTimedParts] = {0, 0, 0};
@@ -1368,7 +1369,11 @@ void rebuild_B(msp_ctx *c, const double *vals, bool nd_ok = true)
     HIPCHK(hipStreamWaitEvent(c->stream, c->ev_side, 0));
     const int bad_bilu = c->read_flag(1) | (c->ns.on ? c->read_flag(2) : 0);
     phase(6);
-    const int bad_coarse = (natural && c->read_flag(0)) || !coarse_solve_accurate(c, tmp);
+    bool bad_coarse = (natural && c->read_flag(0)) || !coarse_solve_accurate(c, tmp);
+    if (!natural && c->nd_rejects > 0) {
+        --c->nd_rejects;
+        bad_coarse = true;
+    }
     c->release(tmp);
     if (bad_bilu) fail(MSP_ERR_SINGULAR);
     if (bad_coarse) {
@@ -2818,6 +2823,7 @@ int msp_stage_set_limit(msp_ctx *c, int limit, int value)
         drop_graph(c);  // (holds the limit)
         c->sweep_polls = value ? value - 1 : kSweepPolls;
         break;
+    case MSP_LIMIT_ND_REJECTS: c->nd_rejects = value; break;
     default: return MSP_ERR_ARG;
     }
     return MSP_OK;

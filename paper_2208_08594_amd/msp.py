@@ -93,7 +93,7 @@ SIGNATURES = {
 STAGE_SPMV, STAGE_GS0, STAGE_PRECOND, STAGE_BILU, STAGE_VCYCLE, STAGE_COARSE, STAGE_TRI_SWEEP = \
     range(7)
 
-LIMIT_MATCH_LOOKS, LIMIT_SWEEP_POLLS = range(2)
+LIMIT_MATCH_LOOKS, LIMIT_SWEEP_POLLS, LIMIT_ND_REJECTS = range(3)
 
 _LIB = None
 _LOCK = threading.Lock()
