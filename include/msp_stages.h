@@ -120,6 +120,11 @@ int msp_stage_set_timing(msp_ctx *ctx, int on);
  * off.  Errors: MSP_ERR_ARG (a NULL pointer). */
 int msp_stage_get_timing(msp_ctx *ctx, double *ms, int *calls);
 
+/* Arnoldi steps that the last solve queued on the device (HOST output): those
+ * of msp_info.iterations and any queued ahead in vain.  Errors: MSP_ERR_ARG (a
+ * NULL pointer). */
+int msp_stage_steps_queued(msp_ctx *ctx, int *steps);
+
 /* Kernels of the graph that holds the captured preconditioner apply (HOST
  * output); 0 while there is none: before the first apply of a regeneration, and
  * where applies are launched kernel by kernel (use_graphs in msp.h).  Errors:

@@ -231,6 +231,7 @@ struct msp_ctx {
     bool timing = false;
     int match_looks = kMatchLooks, sweep_polls = kSweepPolls;  // msp_stage_set_limit
     int nd_rejects = 0;  // likewise
+    int steps_queued = 0;  // Arnoldi steps that the last solve queued
     hipEvent_t tev[4] = {nullptr, nullptr, nullptr, nullptr};
     hipEvent_t ev_step[2] = {nullptr, nullptr};  // ends of the solve's last two queued steps
     double t_ms[kTimedParts] = {0, 0, 0};
@@ -1801,13 +1802,20 @@ void ensure_workspace(msp_ctx *c)
 // unless its graph already exists, so the solve itself creates nothing on the
 // device.
 // An Arnoldi step needs nothing from the host's part of the step before it
-// (its vector is scaled by the norm on the device), so while the residual is
-// still kAheadFactor above the tolerance the next step is queued before the
-// host has seen this one, which hides the host's turn (25 us of about 120 us
-// per step on 4,000 unknowns).  A step queued past the end of a cycle leaves
-// only entries of V, Z and w that nothing reads.
+// (its vector is scaled by the norm on the device), so the next step is queued
+// before the host has seen this one, which hides the host's turn (25 us of about
+// 120 us per step on 4,000 unknowns), where this step will surely not be the
+// last: if a step that reduces the residual kAheadFactor times, or as much as
+// the step before did, still leaves it above the tolerance.  A solve's first
+// step has none before it: the next is queued behind it only where a step in
+// vain costs less than the launches that the host saves elsewhere (up to
+// kAheadFirst unknowns).  Systems that converge in one step, 64x64x32 cells, b
+// = 4: 0.54 ms with the second step queued, 0.35 without; 128x128x64, b = 7: 4.7
+// and 3.0 ms.  A step queued past the end of a cycle leaves only entries of V, Z
+// and w that nothing reads.
 struct Fgmres {
     static constexpr double kAheadFactor = 20.0;
+    static constexpr long long kAheadFirst = 131072;
     msp_ctx *c = nullptr;
     Krylov K;
     bool graph_ok = true;
@@ -1820,6 +1828,8 @@ struct Fgmres {
     double bnorm = 0.0, tol = 0.0, beta = 0.0, relres = 0.0;
     int iters = 0, restarts = 0, j = 0, status = MSP_OK;
     int queued = -1;  // last Arnoldi step of the cycle that is queued
+    int steps = 0;    // Arnoldi steps queued in all
+    double rate = 0.0;  // residual reduction of the last step, 0 before the first
     enum Stage { kStart, kBeta, kStep, kDone } stage = kStart;
     double t0 = 0.0, ms = 0.0;
 
@@ -1909,13 +1919,19 @@ struct Fgmres {
         if (c->timing) HIPCHK(hipEventRecord(c->tev[3], c->stream));
         mark(q);
         queued = q;
+        ++steps;
     }
     // The step after the last queued one, if it will surely be taken as far
     // as is known.  (Timed solves read each step's events before the next.)
     void queue_ahead()
     {
         if (c->timing || queued != j || j + 1 >= m || iters + 1 >= c->opt.max_iter) return;
-        if (!(std::fabs(g[j]) > kAheadFactor * tol)) return;
+        double cut = 1.0 / kAheadFactor;
+        if (rate > 0.0)
+            cut = std::min(cut, rate);
+        else if (N > kAheadFirst)
+            return;
+        if (!(std::fabs(g[j]) * cut > tol)) return;
         queue_step(j + 1, hn());
     }
     // x += Z y for the k steps of the cycle, then the true residual's norm
@@ -1994,6 +2010,7 @@ struct Fgmres {
         H[(size_t)(j + 1) * m + j] = 0.0;
         g[j + 1] = -sn[j] * g[j];
         g[j] = cs[j] * g[j];
+        rate = std::fabs(sn[j]);
         ++iters;
         if (hnorm == 0.0 || std::fabs(g[j + 1]) <= tol || iters >= c->opt.max_iter ||
             j + 1 == m)
@@ -2140,6 +2157,7 @@ int record_solve(const Fgmres &r, msp_info *info)
     c->info.restarts = r.restarts;
     c->info.rel_true_residual = r.relres;
     c->info.solve_ms = r.ms;
+    c->steps_queued = r.steps;
     c->solves++;
     c->info.solves = c->solves;
     c->it_prev = r.iters;
@@ -2805,6 +2823,13 @@ int msp_stage_repeat(msp_ctx *c, int stage, int reps, const double *in, double *
         }
         return c->waits_end();
     });
+}
+
+int msp_stage_steps_queued(msp_ctx *c, int *steps)
+{
+    if (!c || !steps) return MSP_ERR_ARG;
+    *steps = c->steps_queued;
+    return MSP_OK;
 }
 
 int msp_stage_apply_nodes(msp_ctx *c, int *nodes)

@@ -88,6 +88,7 @@ SIGNATURES = {
     "msp_stage_set_timing": ([_vp, _i], _i),
     "msp_stage_get_timing": ([_vp, C.POINTER(_d), C.POINTER(_i)], _i),
     "msp_stage_set_limit": ([_vp, _i, _i], _i),
+    "msp_stage_steps_queued": ([_vp, C.POINTER(_i)], _i),
     "msp_stage_apply_nodes": ([_vp, C.POINTER(_i)], _i),
 }
 STAGE_SPMV, STAGE_GS0, STAGE_PRECOND, STAGE_BILU, STAGE_VCYCLE, STAGE_COARSE, STAGE_TRI_SWEEP = \
@@ -322,6 +323,12 @@ class Solver:
         calls = (C.c_int * 3)()
         _check(self._lib.msp_stage_get_timing(self.h, ms, calls), "get_timing")
         return {k: (ms[i], calls[i]) for i, k in enumerate(("spmv", "apply", "gram_schmidt"))}
+
+    def steps_queued(self):
+        """msp_stage_steps_queued: Arnoldi steps that the last solve queued."""
+        out = C.c_int()
+        _check(self._lib.msp_stage_steps_queued(self.h, C.byref(out)), "steps_queued")
+        return out.value
 
     def apply_nodes(self):
         """msp_stage_apply_nodes: kernels of the captured apply, 0 without one."""
