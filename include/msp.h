@@ -77,10 +77,10 @@ typedef struct {
                          1 (default): the groups of Alg. 4.2 on the block adjacency graph
                          one after another (two dependency levels on a 7-point grid);
                          0: natural block order (nx+ny+nz-2 levels on a 7-point grid) */
-    int use_graphs;   /* 1 (default): a preconditioner apply of many launches (above all
-                         the dependency levels of bilu_order = 0) is captured once per
-                         regeneration into a HIP graph and replayed every iteration;
-                         0: every kernel is launched eagerly.  Same results. */
+    int use_graphs;   /* 1 (default): a preconditioner apply of many launches (several
+                         sweeps per level, Jacobi sweeps or many levels) is captured
+                         once per regeneration into a HIP graph and replayed every
+                         iteration; 0: every kernel is launched eagerly.  Same results. */
     void *stream;     /* hipStream_t for all work; NULL = the default stream */
     /* Optional device allocator (e.g. a framework caching allocator); both NULL =
      * hipMalloc/hipFree.  dev_alloc returns NULL on failure. */

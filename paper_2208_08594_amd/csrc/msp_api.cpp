@@ -1678,31 +1678,56 @@ void capture_apply(msp_ctx *c)
     }
 }
 
-// Kernel launches of one apply (the N stage's groups included).
+// Kernel launches of one apply.
 int apply_launches(const msp_ctx *c)
 {
-    int k = 6;
-    for (const Level &L : c->lev)
-        k += (L.sweep ? 2 : (c->opt.nu_pre + c->opt.nu_post) * L.g) + 4;
-    if (c->opt.full_smoother == 0)
-        k += c->bilu.sweep ? 3 : c->bilu.L.nseg() + c->bilu.U.nseg();
-    if (c->ns.on) k += (int)c->ns.grp_ptr.size() + 4;
+    const msp_options &o = c->opt;
+    int k = 5;  // decoupling, coarsest solve, residual, combination
+    for (size_t l = 0; l + 1 < c->lev.size(); ++l) {
+        const Level &L = c->lev[l];
+        if (L.sweep) {
+            k += 4;
+            continue;
+        }
+        // the first color comes with the kernel before; without pre-smoothing x is
+        // cleared
+        k += (o.nu_pre + o.nu_post) * (o.smoother == 1 ? 2 : L.g) + (o.nu_pre > 0 ? -1 : 1);
+        k += (L.ru_ptr ? 1 : 2) + (fold_prolong(c, L) ? 0 : 1);
+    }
+    if (!natural_out(c)) ++k;
+    const BiluData &D = c->bilu;
+    if (o.full_smoother == 1)
+        ++k;
+    else if (D.sweep)
+        k += 3;
+    else
+        k += (int)std::count(D.fwd_live.begin(), D.fwd_live.end(), (char)1) + D.U.nseg() -
+             (D.turn ? 1 : 0);
+    if (c->ns.on) k += (int)c->ns.grp_ptr.size() + 3;
     return k;
 }
 
-// Applies of up to this many launches are launched one by one: a step queued
-// ahead keeps the stream filled, and a graph launch costs 20 to 30 us of idle
-// device around it (eight 20^3 systems solved together, 11 launches each:
-// 7.4 ms with graphs, 4.3 without; 60x220x85 cells layered, 140 launches:
-// 111.3 and 110.4 ms).  Longer ones (several sweeps per level of a hierarchy of
-// many colors) would keep the host busy for as long as they run (an apply of
-// 190 launches: 3.06 ms a solve with graphs, 3.17 without).
-constexpr int kEagerLaunches = 160;
+// Applies of few launches are launched one by one: a step queued ahead keeps the
+// stream filled, a graph's launch costs 20 to 30 us of idle device around it, and
+// its capture 150 to 200 us a regeneration (20^3 cells, b = 4, alone, seven
+// launches: 0.54 ms a solve, 0.58 with a graph).  But a launch takes the host 3 us:
+// of many launches on a small system it is the host that runs behind, above all
+// with several systems solved together, and a replayed graph's kernels follow
+// each other at half of that.  With a graph / one by one: 10^3 cells, b = 4, 60
+// launches 1.14 / 1.42 ms a solve, 4.1 / 9.3 ms for six together; 43 launches 1.34 /
+// 1.32 and 4.6 / 6.5; 32^3, b = 3, 35 launches 2.29 / 2.31 and 6.9 / 7.6; 96
+// launches 2.6 / 3.1 and 6.5 / 16.4.  On large systems the launches hide behind the
+// kernels: 80x80x50, b = 4, 62 launches 5.06 / 5.07, 60x220x85 layered, 140
+// launches 111.3 / 110.4 ms; 48^3, b = 4, 172 launches 5.74 / 5.90.
+constexpr int kEagerLaunches = 40;
+constexpr int kEagerLaunchesLarge = 160;
+constexpr long long kEagerLarge = 262144;  // unknowns
 
 bool apply_by_graph(const msp_ctx *c, bool capture_ok)
 {
     return c->opt.use_graphs && (c->apply_exec || capture_ok) &&
-           apply_launches(c) > kEagerLaunches;
+           apply_launches(c) >
+               ((long long)c->n * c->b > kEagerLarge ? kEagerLaunchesLarge : kEagerLaunches);
 }
 
 // Basis vectors of up to this many entries are scaled by the first kernel of the

@@ -71,11 +71,26 @@ def test_replays_match_eager(name):
         gg.close()
 
 
-def test_a_short_apply_is_not_captured():
-    s = synth.config(0)
-    g = msp.Solver(max_coarse=64)
+# Small systems: a graph from some 40 launches on (the host takes longer to launch
+# them than the device to run them); large ones: from some 160 on.
+@pytest.mark.parametrize("dims,opt,graph", [
+    ((10, 10, 10), dict(), False),
+    ((10, 10, 10), dict(max_coarse=64, nu_pre=2), True),
+    ((10, 10, 10), dict(max_coarse=12, smoother=1), True),
+    ((24, 24, 24), dict(max_coarse=1500), False),
+    ((24, 24, 24), dict(max_coarse=1500, nu_pre=4, nu_post=4), True),
+    ((48, 48, 32), dict(max_coarse=3000, nu_pre=2, nu_post=1), False),
+    ((48, 48, 32), dict(max_coarse=300, nu_pre=8, nu_post=8), True)])
+def test_which_applies_are_captured(dims, opt, graph):
+    s = synth.lognormal_grid(*dims, 4, 12, 1.5, 0.1, "lateral4")
+    g = msp.Solver(**opt)
+    e = msp.Solver(use_graphs=False, **opt)
     g.setup(s)
-    g.apply(s.rhs)
-    g.solve(s.rhs)
-    assert g.apply_nodes() == 0
+    e.setup(s)
+    x, _ = g.solve(s.rhs)
+    assert torch.equal(x, e.solve(s.rhs)[0])
+    assert (g.apply_nodes() > 0) == graph
+    if graph:
+        assert g.apply_nodes() > (40 if s.N <= 262144 else 160)
     g.close()
+    e.close()
