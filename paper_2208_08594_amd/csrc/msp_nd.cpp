@@ -156,8 +156,10 @@ struct Cutter {
         Forest fl, fr;
         if ((int)std::min(L.size(), R.size()) >= kParallelSet) {
             // no vertex of one side is adjacent to the other side, so the two
-            // touch disjoint marks
-            auto job = std::async(std::launch::async, [&]() { return cut(std::move(L), lab + 3); });
+            // touch disjoint marks.  (Deferred where no thread can be had: it then
+            // runs in the get below.)
+            auto job = std::async(std::launch::async | std::launch::deferred,
+                                  [&]() { return cut(std::move(L), lab + 3); });
             fr = cut(std::move(R), lab + 4);
             fl = job.get();
         } else {
