@@ -246,9 +246,8 @@ def main():
     gsch_ms, gsch_calls = summed(timings, "gram_schmidt")
     b_spmv = spmv_bytes(sys_)
     t_spmv = spmv_ms / max(spmv_calls, 1)
-    # (up to 2500 slices of 64 rows the library takes a wave per component)
-    name = "k_spmv" if sys_.n > 2500 * 64 else "k_spmv_rows"
-    roofline = {"kernel": f"{name}<{sys_.b}> (block SpMV w = A z of every Arnoldi step)",
+    roofline = {"kernel": f"k_spmv<{sys_.b}> (block SpMV w = A z of every Arnoldi step; on "
+                          "small matrices k_spmv_rows)",
                 "bound": "hbm", "achieved": gbs(b_spmv, t_spmv), "peak": HBM_PEAK_GBS,
                 "unit": "GB/s", "frac": gbs(b_spmv, t_spmv) / HBM_PEAK_GBS,
                 "traffic": None, "bytes_per_launch": b_spmv,

@@ -35,6 +35,17 @@ using PinnedBuffer = std::function<void *(int l, size_t bytes)>;
 // Called with every HIP error; must not return (it throws).
 using HipFail = void (*)(hipError_t);
 
+// Exclusive scan of in[0..n) in tiles of kScanTile entries: entry i's scan is
+// out[i] + tiles[i / kScanTile], *total the sum (tiles: scan_tiles(n) ints).
+constexpr int kScanTile = 1024;
+int scan_tiles(int n);
+hipError_t launch_tile_scan(const int *in, int *out, int *tiles, int *total, int n,
+                            hipStream_t st);
+
+// Bytes of the one device allocation the chain makes for a level 0 of n0
+// rows and nnz0 entries (freed with the setup's other temporaries).
+size_t device_chain_bytes(int n0, long long nnz0);
+
 // Looks of a row at undecided rows before the matching kernel gives it up and is
 // run again (about 15 ms).
 constexpr int kMatchLooks = 32768;
@@ -50,29 +61,17 @@ constexpr int kMatchLooks = 32768;
 // coarsest-level work can start first.  A0's values may still be on their
 // way to the host: level0_values() is called (and must return only once they
 // are there) before they are read here, and before returning when level 0 is
-// the coarsest level.  Returns 1 without touching
-// A0 or H when the level-0 pattern is not structurally symmetric (the pass
-// reads a_ji through the mirror entry); the caller then runs the host chain.
-// `pinned` is a host-pinned buffer of at
-// least 16 ints.  With `staging`, each new level is copied to page-locked
-// memory first (a fast DMA), on_smoothed gets its pattern there (so the
-// level's host work starts before the copy into H.A is done), and H.A is
+// the coarsest level.  Returns 1 without touching A0 or H when the level-0
+// pattern is not structurally symmetric (the pass reads a_ji through the mirror
+// entry); the caller then runs the host chain.  `pinned` is a host-pinned
+// buffer of at least 16 ints.  With `staging`, each new level is copied to
+// page-locked memory first (a fast DMA), on_smoothed gets its pattern there (so
+// the level's host work starts before the copy into H.A is done), and H.A is
 // filled from it.  A stalled level (the two passes keep more than 90% of its
 // rows) is finished on the host with absorb_singletons and galerkin, and its
 // coarse matrix uploaded.  last_rp, last_ci, last_val (if given) receive the
 // coarsest level on the device (in the chain's own memory, or level 0 itself).
 // looks (>= 1): see kMatchLooks.
-// Exclusive scan of in[0..n) in tiles of kScanTile entries: entry i's scan is
-// out[i] + tiles[i / kScanTile], *total the sum (tiles: scan_tiles(n) ints).
-constexpr int kScanTile = 1024;
-int scan_tiles(int n);
-hipError_t launch_tile_scan(const int *in, int *out, int *tiles, int *total, int n,
-                            hipStream_t st);
-
-// Bytes of the one device allocation the chain makes for a level 0 of n0
-// rows and nnz0 entries (freed with the setup's other temporaries).
-size_t device_chain_bytes(int n0, long long nnz0);
-
 int device_hierarchy(Csr &A0, const int *rp0, const int *ci0, const double *val0,
                      int max_coarse, int max_levels, int max_dense, Hierarchy &H,
                      const LevelCallback &on_smoothed, const std::function<void()> &level0_values,

@@ -1,4 +1,4 @@
-"""The aggregation chain on the device (pairwise passes as matching rounds,
+"""The aggregation chain on the device (pairwise passes in one launch each,
 Galerkin products per coarse row) against the host chain and the oracle:
 the same aggregates and the same coarse matrices, bit for bit.  A block
 pattern that is not structurally symmetric takes the host chain."""

@@ -1,8 +1,7 @@
 """The Krylov part of the solve at the sizes where its launches change: the
-reduction in a pass's last work-group (up to 262,144 unknowns) and in a launch
+reduction in a pass's last work-group (up to 786,432 unknowns) and in a launch
 of its own beyond, restart lengths beyond the fused passes, steps queued ahead
-of the host, and the captured preconditioner apply of a natural elimination
-order.  Against the oracle's iteration count and the true residual; repeated
+of the host, and a captured preconditioner apply.  Against the oracle's iteration count and the true residual; repeated
 solves bit for bit."""
 import numpy as np
 import pytest
